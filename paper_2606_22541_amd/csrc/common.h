@@ -27,6 +27,9 @@ constexpr uint32_t kDefaultIngestSpins = 1u << 19;   // about a second of pollin
 // per row.
 constexpr int kBM = 256;
 constexpr int kBN = 256;
+// bf16 large tiles: 32-row blocks of each half of a tile.
+constexpr int kHalfBlocks = 5;
+constexpr int kTileBlocks = 2 * kHalfBlocks;
 
 // Cache-policy operand of the raw buffer loads: non-temporal (streaming)
 // data, read once, evicted first and kept out of the last-level cache.
@@ -37,6 +40,7 @@ constexpr int kErrBadId = 1;
 constexpr int kErrBadLayer = 2;
 constexpr int kErrIngestTimeout = 4;
 constexpr int kErrBadCount = 8;       // pre-grouped counts negative or past the rows buffer
+constexpr int kErrStalled = 16;       // a work item's inputs never became ready (ffn_sched.h)
 
 // Groups with at most this many rows ("small": a DeepSeek EP32 share at
 // T=4096 has ~128 rows per expert) take one full-height tile in the bf16
@@ -50,36 +54,11 @@ constexpr int kSmallRows = 192;
 // skewed routing have, stream their weights faster in the small kernel).
 constexpr int kSmallRowsDown = 64;
 
-// Device-side tables written by the dispatch scan, read by the GEMMs.
+// Device-side tables of the groups, written by the dispatch, read by the GEMMs.
 struct GroupTable {
     int32_t *row0;      // [G] first row of the group in its A matrix
     int32_t *rows;      // [G] rows of the group
-    int32_t *lt_base;   // [G+1] prefix of ceil(rows / kBM) over groups with rows > kSmallRows
-    int32_t *st_base;   // [G+1] prefix of 1 per group with 1 <= rows <= kSmallRows
-    // Tile order of the 256-row bf16 GEMM: the full row tiles of every group
-    // first, then the partial ones (rows % kBM != 0), largest first, so the
-    // cheap partial tiles fill the last round of the persistent grid.
-    int32_t *fl_base;   // [G+1] prefix of rows / kBM over groups with rows > kSmallRows
-    int32_t *pl_list;   // [G+1] groups with rows > kSmallRows and a partial row tile,
-                        //       by descending rows % kBM (ties: lower index first); count at [G]
-    // The same partition at kSmallRowsDown rows (the down product's):
-    int32_t *lt_base_d; // [G+1] as lt_base, groups with rows > kSmallRowsDown
-    int32_t *st_base_d; // [G+1] as st_base, groups with 1 <= rows <= kSmallRowsDown
-    int32_t *fl_base_d; // [G+1] as fl_base, groups with rows > kSmallRowsDown
-    int32_t *pl_list_d; // [G+1] as pl_list, groups with rows > kSmallRowsDown
 };
-
-// The tables a GEMM launch reads for the down product: the partition at
-// kSmallRowsDown in place of the one at kSmallRows.
-__host__ __device__ inline GroupTable down_partition(const GroupTable &g)
-{
-    GroupTable d = g;
-    d.lt_base = g.lt_base_d;
-    d.st_base = g.st_base_d;
-    d.fl_base = g.fl_base_d;
-    d.pl_list = g.pl_list_d;
-    return d;
-}
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
@@ -112,50 +91,6 @@ __device__ __forceinline__ void swap_halves(uint32_t &x, uint32_t &y)
     const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
     x = r[0];
     y = r[1];
-}
-
-// Output of one 32x32 block of the transposed product D[feature][token]
-// (v_mfma_f32_32x32x16_bf16 with the weights as its row operand): lane l
-// holds token l % 32, and register r holds feature 8 (r/4) + 4 (l/32) + r%4
-// of the block.  Lanes l and l ^ 32 hold the same token, so after swapping
-// halves each lane has 8 consecutive features and writes 16 bytes.
-//
-// store_block_bf16: the block's 32 features as bf16 at row[0..31] (row =
-// the token's output row at the block's first column); lane l writes
-// features 8 (l/32) .. +7 and 16 + 8 (l/32) .. +7.
-__device__ __forceinline__ void store_block_bf16(const f32x16 &v, bf16 *row, bool valid)
-{
-    uint32_t p[8];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        p[2 * q] = pack_bf16x2(v[4 * q], v[4 * q + 1]);
-        p[2 * q + 1] = pack_bf16x2(v[4 * q + 2], v[4 * q + 3]);
-    }
-    swap_halves(p[0], p[2]);
-    swap_halves(p[1], p[3]);
-    swap_halves(p[4], p[6]);
-    swap_halves(p[5], p[7]);
-    const int hi = (__lane_id() >> 5) * 8;
-    if (valid) {
-        *(u32x4 *)(row + hi) = (u32x4){p[0], p[1], p[2], p[3]};
-        *(u32x4 *)(row + 16 + hi) = (u32x4){p[4], p[5], p[6], p[7]};
-    }
-}
-
-// store_block_swiglu: the packed gate/up weights interleave by 16, so
-// features 0..15 of a block are gate rows and 16..31 the matching up rows:
-// register r (r < 8) and r + 8 of a lane are gate and up of one h column
-// 8 (r/4) + 4 (l/32) + r%4.  The block's 16 h columns go to hrow[0..15];
-// lane l writes h columns 8 (l/32) .. +7.
-__device__ __forceinline__ void store_block_swiglu(const f32x16 &v, bf16 *hrow, bool valid)
-{
-    uint32_t p[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        p[q] = pack_bf16x2(silu_mul(v[2 * q], v[2 * q + 8]), silu_mul(v[2 * q + 1], v[2 * q + 9]));
-    swap_halves(p[0], p[2]);
-    swap_halves(p[1], p[3]);
-    if (valid) *(u32x4 *)(hrow + (__lane_id() >> 5) * 8) = (u32x4){p[0], p[1], p[2], p[3]};
 }
 
 // e4m3 (OCP E4M3FN) code of v, round to nearest even.  |v| is clamped to 448

@@ -89,76 +89,118 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int &total)
     return x - v;
 }
 
-// Grouped-GEMM tile tables over G = E_loc (+1 shared) groups (GroupTable),
-// built by one wave in chunks of 64 groups with shuffle scans, so no
-// workgroup barrier sits in the dispatch for them.  rows[i] is the local
+// The groups' rows and the row tiles of the FFN pass (ffn_sched.h) over G =
+// E_loc (+1 shared) groups, built by one workgroup; rows[i] is the local
 // expert's token count (tot), or T for the shared expert.
-__device__ void build_group_tables(const GroupTable &g, const int32_t *tot, int E_loc,
-                                   int has_shared, int T, int lane)
+//
+// A large group's row tiles are as few as hold its 32-row blocks, of even
+// size.  When the items of the gate/up product would not fill the grid once,
+// the groups are split into as many times more row tiles as still fit in one
+// round: the round lasts as long as its largest tile (EP32 share at T = 8191,
+// about 261 rows an expert: two tiles of 160 and 128 rows instead of one of
+// 288).  With more items than workgroups the largest tiles are kept: they do
+// the most work per weight read.
+struct SchedBuildLds {
+    int32_t row0[kMaxLocalExperts + 1];
+    int32_t tiles[kMaxLocalExperts + 1];      // class << 24 | row tiles
+    int32_t cls[3];                           // row tiles: large, small > kSmallRowsDown rows, small
+    int32_t small_items, fit[4];
+};
+
+__device__ __forceinline__ int split_tiles(int nb, int k)
 {
-    const int G = E_loc + (has_shared ? 1 : 0);
-    int c_row = 0;
-    int c_lt[2] = {0, 0}, c_st[2] = {0, 0}, c_fl[2] = {0, 0}, c_pl[2] = {0, 0};
-    int32_t *lt_base[2] = {g.lt_base, g.lt_base_d}, *st_base[2] = {g.st_base, g.st_base_d};
-    int32_t *fl_base[2] = {g.fl_base, g.fl_base_d}, *pl_list[2] = {g.pl_list, g.pl_list_d};
-    constexpr int kThresh[2] = {kSmallRows, kSmallRowsDown};
-    for (int c0 = 0; c0 < G; c0 += 64) {
-        const int i = c0 + lane;
-        const int rows = i < E_loc ? tot[i] : (i < G ? T : 0);
-        const int m = (rows + kBM - 1) / kBM;
-        const int fm = rows / kBM, rem = rows - fm * kBM;
-        int t_row;
-        const int p_row = wave_excl_scan(i < E_loc ? rows : 0, lane, t_row);
-        if (i < G) {
-            g.row0[i] = i < E_loc ? c_row + p_row : 0;
-            g.rows[i] = rows;
+    return max(1, min((nb + kTileBlocks - 1) / kTileBlocks * k, nb / 2));
+}
+
+__device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedPlan &plan, const int32_t *tot,
+                               int E_loc, int has_shared, int T, SchedBuildLds &l)
+{
+    const int G = E_loc + (has_shared ? 1 : 0), tid = threadIdx.x;
+    // counters of the next pass
+    for (int i = tid; i < kSchedTicks; i += kDispatchThreads) s.tick[i] = 0;
+    for (int i = tid; i < kMaxSchedCus; i += kDispatchThreads) s.claim[i] = 0;
+    if (tid < 3) l.cls[tid] = 0;
+    if (tid < 4) l.fit[tid] = 0;
+    if (tid == 0) l.small_items = 0;
+    if (tid < 64) {
+        int carry = 0;
+        for (int c0 = 0; c0 < E_loc; c0 += 64) {
+            const int i = c0 + tid;
+            int t;
+            const int p = wave_excl_scan(i < E_loc ? tot[i] : 0, tid, t);
+            if (i < E_loc) l.row0[i] = carry + p;
+            carry += t;
         }
-        // the two partitions into small groups (the small-group kernel) and
-        // large ones (the 256-row kernel): gate/up at kSmallRows, down at
-        // kSmallRowsDown
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const bool large = rows > kThresh[q];
-            int t_lt, t_st, t_fl, t_pl;
-            const int p_lt = wave_excl_scan(large ? m : 0, lane, t_lt);
-            const int p_st = wave_excl_scan(rows > 0 && !large ? 1 : 0, lane, t_st);
-            const int p_fl = wave_excl_scan(large ? fm : 0, lane, t_fl);
-            wave_excl_scan(rem > 0 && large ? 1 : 0, lane, t_pl);
-            if (i < G) {
-                lt_base[q][i] = c_lt[q] + p_lt;
-                st_base[q][i] = c_st[q] + p_st;
-                fl_base[q][i] = c_fl[q] + p_fl;
-            }
-            c_lt[q] += t_lt;
-            c_st[q] += t_st;
-            c_fl[q] += t_fl;
-            c_pl[q] += t_pl;
-        }
-        if (i < G && rem > 0) {
-            // rank among the large groups' partial row tiles: more rows first,
-            // then lower index
-            int rank_l[2] = {0, 0};
-            for (int j = 0; j < G; ++j) {
-                const int rj = j < E_loc ? tot[j] : T;
-                const int qj = rj % kBM;
-                const bool before = qj > 0 && (qj > rem || (qj == rem && j < i));
-                rank_l[0] += (before && rj > kThresh[0]) ? 1 : 0;
-                rank_l[1] += (before && rj > kThresh[1]) ? 1 : 0;
-            }
-            if (rows > kThresh[0]) pl_list[0][rank_l[0]] = i;
-            if (rows > kThresh[1]) pl_list[1][rank_l[1]] = i;
-        }
-        c_row += t_row;
+        if (tid == 0 && has_shared) l.row0[E_loc] = 0;
     }
-    if (lane == 0) {
+    __syncthreads();
+    for (int i = tid; i < G; i += kDispatchThreads) {
+        const int rows = i < E_loc ? tot[i] : T;
+        g.row0[i] = l.row0[i];
+        g.rows[i] = rows;
+        const int nb = (rows + 31) >> 5;
+        if (rows > kSmallRows) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            lt_base[q][G] = c_lt[q];
-            st_base[q][G] = c_st[q];
-            fl_base[q][G] = c_fl[q];
-            pl_list[q][G] = c_pl[q];
+            for (int k = 1; k <= 4; ++k) atomicAdd(&l.fit[k - 1], split_tiles(nb, k) * plan.nt_large);
+        } else if (rows > 0) {
+            atomicAdd(&l.small_items, plan.nt_small);
         }
     }
+    __syncthreads();
+    int split = 1;
+#pragma unroll
+    for (int k = 2; k <= 4; ++k)
+        if (l.fit[k - 1] + l.small_items <= plan.grid) split = k;
+    for (int i = tid; i < G; i += kDispatchThreads) {
+        const int rows = i < E_loc ? tot[i] : T;
+        const int c = rows > kSmallRows ? 0 : rows > kSmallRowsDown ? 1 : 2;
+        const int m = c == 0 ? split_tiles((rows + 31) >> 5, split) : rows > 0 ? 1 : 0;
+        l.tiles[i] = c << 24 | m;
+        if (m) atomicAdd(&l.cls[c], m);
+    }
+    __syncthreads();
+    const int base1 = l.cls[0], base2 = base1 + l.cls[1], n = base2 + l.cls[2];
+    for (int i = tid; i < G; i += kDispatchThreads) {
+        const int rows = i < E_loc ? tot[i] : T;
+        const int c = l.tiles[i] >> 24, m = l.tiles[i] & 0xffffff;
+        int at = c == 0 ? 0 : c == 1 ? base1 : base2;
+        for (int j = 0; j < i; ++j) {
+            const int e = l.tiles[j];
+            at += (e >> 24) == c ? e & 0xffffff : 0;
+        }
+        if (!m) continue;
+        const int nb = (rows + 31) >> 5, q = nb / m, r = nb - q * m;
+        int4 *rt = (int4 *)s.rt;
+        int done = 0;                   // rows placed so far
+        for (int k = 0; k < m; ++k) {
+            const int h = min(32 * (q + (k < r ? 1 : 0)), rows - done);
+            rt[at + k] = make_int4(i | (m == 1 ? 1 << 30 : 0), l.row0[i] + done, h | m << 9, at);
+            done += h;
+        }
+    }
+    for (int i = tid; i < n; i += kDispatchThreads) s.dep[i] = 0;
+    if (tid == 0) {
+        s.hdr[0] = n;
+        s.hdr[1] = base1;
+        s.hdr[2] = base2;
+    }
+}
+
+// The counters of a schedule as the build leaves them, for a second pass over
+// the same row tiles.
+__global__ __launch_bounds__(kDispatchThreads)
+void k_reset_schedule(Sched s)
+{
+    for (int i = threadIdx.x; i < kSchedTicks; i += kDispatchThreads) s.tick[i] = 0;
+    for (int i = threadIdx.x; i < kMaxSchedCus; i += kDispatchThreads) s.claim[i] = 0;
+    const int n = s.hdr[0];
+    for (int i = threadIdx.x; i < n; i += kDispatchThreads) s.dep[i] = 0;
+}
+
+hipError_t launch_reset_schedule(const Sched &s, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_reset_schedule, dim3(1), dim3(kDispatchThreads), 0, st, s);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -177,8 +219,8 @@ __global__ __launch_bounds__(kDispatchThreads)
 void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, int32_t E,
              int32_t e0, int32_t E_loc, int32_t T, int32_t has_shared,
              const int32_t *__restrict__ blk_counts, int32_t *__restrict__ counts,
-             int32_t *__restrict__ offsets, GroupTable g, int32_t *__restrict__ slot_of_row,
-             int32_t *__restrict__ row_of_slot)
+             int32_t *__restrict__ offsets, GroupTable g, Sched sched, SchedPlan plan,
+             int32_t *__restrict__ slot_of_row, int32_t *__restrict__ row_of_slot)
 {
     __shared__ int32_t tot[kMaxLocalExperts], pre[kMaxLocalExperts];
     __shared__ int32_t wbase[kWaves][kMaxLocalExperts];
@@ -295,46 +337,53 @@ void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, 
             if (pos >= 0) slot_of_row[pos] = (int32_t)sl;
         }
     }
-    // the last workgroup owns no slots (the launch adds it for this): its
-    // first wave builds the tables while the others place their slots
-    if (b == (int)gridDim.x - 1 && wave == 0) build_group_tables(g, tot, E_loc, has_shared, T, lane);
+    // the last workgroup owns no slots (the launch adds it for this): it
+    // builds the FFN's row tiles while the others place their slots
+    if (b == (int)gridDim.x - 1 && g.rows) {
+        __shared__ SchedBuildLds sb;
+        build_schedule(g, sched, plan, tot, E_loc, has_shared, T, sb);
+    }
 }
 
-// Tile tables for pre-grouped rows (the receive region of section 3.2.1 in
-// its grouped form: the senders supply the per-expert counts).  One wave:
-// validate the counts in order, then the same table build as the dispatch.
-__global__ __launch_bounds__(64)
+// Row tiles for pre-grouped rows (the receive region of section 3.2.1 in
+// its grouped form: the senders supply the per-expert counts).  One
+// workgroup: its first wave validates the counts in order, then the same
+// build as the dispatch.
+__global__ __launch_bounds__(kDispatchThreads)
 void k_group_tables_from_counts(const int32_t *__restrict__ counts, int32_t E_loc,
-                                int32_t n_rows_max, GroupTable g, int32_t *__restrict__ err)
+                                int32_t n_rows_max, GroupTable g, Sched sched, SchedPlan plan,
+                                int32_t *__restrict__ err)
 {
     __shared__ int32_t tot[kMaxLocalExperts];
+    __shared__ SchedBuildLds sb;
     const int lane = threadIdx.x;
-    int carry = 0, bad = 0;
-    for (int c0 = 0; c0 < E_loc; c0 += 64) {
-        const int i = c0 + lane;
-        int c = i < E_loc ? counts[i] : 0;
-        bad |= c < 0;
-        c = c < 0 ? 0 : c;
-        int t;
-        const int before = carry + wave_excl_scan(c, lane, t);
-        // rows past n_rows_max are dropped: the group keeps what fits
-        const int keep = min(c, max(0, n_rows_max - before));
-        bad |= keep != c;
-        if (i < E_loc) tot[i] = keep;
-        carry += t;
+    if (lane < 64) {
+        int carry = 0, bad = 0;
+        for (int c0 = 0; c0 < E_loc; c0 += 64) {
+            const int i = c0 + lane;
+            int c = i < E_loc ? counts[i] : 0;
+            bad |= c < 0;
+            c = c < 0 ? 0 : c;
+            int t;
+            const int before = carry + wave_excl_scan(c, lane, t);
+            // rows past n_rows_max are dropped: the group keeps what fits
+            const int keep = min(c, max(0, n_rows_max - before));
+            bad |= keep != c;
+            if (i < E_loc) tot[i] = keep;
+            carry += t;
+        }
+        if (__any(bad) && lane == 0) atomicOr(err, kErrBadCount);
     }
-    if (__any(bad) && lane == 0) atomicOr(err, kErrBadCount);
-    __builtin_amdgcn_s_waitcnt((15) | (3 << 14) | (7 << 4) | (0 << 8));   // LDS stores done
-    __builtin_amdgcn_wave_barrier();
-    build_group_tables(g, tot, E_loc, 0, 0, lane);
+    __syncthreads();
+    build_schedule(g, sched, plan, tot, E_loc, 0, 0, sb);
 }
 
 hipError_t launch_group_tables_from_counts(const int32_t *counts, int32_t E_loc,
-                                           int32_t n_rows_max, GroupTable g, int32_t *err,
-                                           hipStream_t s)
+                                           int32_t n_rows_max, GroupTable g, const Sched &sched,
+                                           const SchedPlan &plan, int32_t *err, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_group_tables_from_counts, dim3(1), dim3(64), 0, s, counts, E_loc,
-                       n_rows_max, g, err);
+    hipLaunchKernelGGL(k_group_tables_from_counts, dim3(1), dim3(kDispatchThreads), 0, s, counts, E_loc,
+                       n_rows_max, g, sched, plan, err);
     return hipGetLastError();
 }
 
@@ -345,10 +394,10 @@ hipError_t launch_dispatch_index(const DispatchArgs &a, hipStream_t s)
         hipLaunchKernelGGL(k_hist, dim3(nb), dim3(kDispatchThreads), 0, s, a.ids, a.n_slots, a.E,
                            a.blk_counts, a.err);
     }
-    // one workgroup per histogram row, plus one without slots for the tables
+    // one workgroup per histogram row, plus one without slots for the row tiles
     hipLaunchKernelGGL(k_place, dim3(nb + 1), dim3(kDispatchThreads), 0, s, a.ids,
                        a.n_slots, nb, a.E, a.e0, a.E_loc, a.T, a.has_shared, a.blk_counts,
-                       a.counts, a.offsets, a.groups, a.slot_of_row, a.row_of_slot);
+                       a.counts, a.offsets, a.groups, a.sched, a.plan, a.slot_of_row, a.row_of_slot);
     return hipGetLastError();
 }
 

@@ -1,0 +1,402 @@
+// Device-side schedule of the expert FFN's persistent kernels: the row tiles
+// of a pass, built by the dispatch, and the work lists that the workgroups of
+// one launch take items from.
+//
+// Row tiles (int4 {group | only << 30, row0, rows | m << 9, first}: the group
+// has m row tiles from `first` on): the large groups' tiles, group by group,
+// then the small groups'.
+// An item of a product is (row tile, column tile); items are numbered group
+// by group, within a large group in bands of kBandM row tiles (row tiles
+// fastest, so that one band's weight panels and token rows are shared in an
+// L2).
+//
+// Lists.  Workgroups are placed round-robin on the 8 XCDs, so the items of a
+// product are dealt to 8 lists in runs of P / 8 consecutive items (P = the
+// grid), one list per XCD: the workgroups of an XCD take them in order.  The
+// first P / 8 gate/up items of a list are fixed, one per workgroup (no ticket
+// has to come back before the first loads); later items are taken with an
+// atomic ticket per list, requested while the previous item runs.  A
+// workgroup whose list is empty takes from the others'.
+//
+// A down item waits until every gate/up tile of its rows is written (a count
+// per row tile).  Waiting cannot deadlock, whatever else runs on the GPU and
+// however few workgroups are resident: a workgroup takes a down item only
+// after its own list's gate/up items are taken, and one that has to wait
+// looks for gate/up items that nobody has taken (in other lists, or fixed to
+// workgroups that have not started) and runs those first.  So every gate/up
+// item not yet finished is being run by a resident workgroup, which never
+// waits.
+#pragma once
+
+#include "common.h"
+
+namespace moe {
+
+constexpr int kMaxSchedCus = 512;     // workgroups of one launch
+constexpr int kBandM = 4;             // row tiles per raster band
+constexpr int kTickStride = 32;       // ints between ticket counters (128 bytes)
+constexpr int kListsLog2 = 3;
+constexpr int kLists = 1 << kListsLog2;
+// Polls of one wait before it gives up (seconds; a wait takes microseconds).
+constexpr int kMaxPolls = 1 << 22;
+
+struct Sched {
+    int32_t *rt;       // [n] int4 row tiles
+    int32_t *hdr;      // row tiles, large ones of gate/up, large ones of down
+    int32_t *dep;      // [n] gate/up tiles written, per row tile
+    int32_t *claim;    // [kMaxSchedCus] fixed first item taken, per workgroup
+    int32_t *tick;     // [2][kLists] tickets, kTickStride apart
+};
+
+// The schedule as a kernel argument, in the kernel-argument segment.
+typedef const __attribute__((address_space(4))) Sched ArgSched;
+
+constexpr int kSchedHdr = 64;
+constexpr int kSchedTicks = 2 * kLists * kTickStride;
+
+// Row tiles that G groups with `rows` rows in all can make.
+__host__ __device__ inline int64_t sched_max_tiles(int64_t rows, int64_t G)
+{
+    return rows / kBM + G + kMaxSchedCus;
+}
+// Ints of a schedule, and its arrays in one allocation.
+inline int64_t sched_ints(int64_t max_tiles)
+{
+    return kSchedHdr + kSchedTicks + kMaxSchedCus + ((5 * max_tiles + 63) & ~(int64_t)63);
+}
+inline Sched sched_at(int32_t *base, int64_t max_tiles)
+{
+    Sched s;
+    s.hdr = base;
+    s.tick = base + kSchedHdr;
+    s.claim = s.tick + kSchedTicks;
+    s.rt = s.claim + kMaxSchedCus;
+    s.dep = s.rt + 4 * max_tiles;
+    return s;
+}
+
+struct RowTile {
+    int group, row0, rows;
+    bool only;         // the group's only row tile
+};
+
+// What a workgroup keeps of the schedule in LDS (its registers belong to the
+// tiles' loops).
+constexpr int kSchedLdsTiles = 64;
+struct SchedLds {
+    int4 rt[kSchedLdsTiles];
+    int32_t hdr[4];
+    int32_t item, wait;
+    int32_t stage;     // thread 0: list being drained (0 gate/up, 1 down, 2 the others')
+    uint64_t w[2];     // weights of the two products
+};
+
+__device__ __forceinline__ int agent_load(const int32_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int agent_add(int32_t *p, int v)
+{
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int agent_swap(int32_t *p, int v)
+{
+    return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Column tiles of the two products, in the kernel's arguments.
+struct FfnTiles {
+    int32_t ntl[2];    // of a large row tile (256 columns)
+    int32_t nts[2];    // of a small row tile (128 columns)
+};
+
+typedef const __attribute__((address_space(4))) FfnTiles ArgTiles;
+
+// The items of a launch and how they are dealt to lists.
+struct Items {
+    int lg, C, x;              // log2 of the lists, workgroups per list, this workgroup's list
+    int C1;                    // run length of the down product's items
+    int nrt, nl0, nl1;         // row tiles, large ones of gate/up and of down
+    int ntl0, ntl1, nts0, nts1;
+    int total0, total1;
+
+    template <bool LARGE>
+    __device__ __forceinline__ void load(const SchedLds &l, int phases, int a0, int a1, int b0, int b1)
+    {
+        const int P = gridDim.x;
+        lg = (P & (kLists - 1)) ? 0 : kListsLog2;
+        C = P >> lg;
+        x = blockIdx.x & ((1 << lg) - 1);
+        nrt = __builtin_amdgcn_readfirstlane(l.hdr[0]);
+        nl0 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[1]) : 0;
+        nl1 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[2]) : 0;
+        ntl0 = a0;
+        ntl1 = a1;
+        nts0 = b0;
+        nts1 = b1;
+        const int g = nl0 * ntl0 + (nrt - nl0) * nts0, d = nl1 * ntl1 + (nrt - nl1) * nts1;
+        total0 = (phases & 1) ? g : 0;
+        total1 = (phases & 2) ? d : 0;
+        // a list's down items are those of the row tiles that it did the
+        // gate/up items of (as far as runs of one length allow): they are ready
+        // when its own gate/up items are
+        C1 = max(1, (int)((float)C * (float)d / (float)max(g, 1) + 0.5f));
+        C1 = __builtin_amdgcn_readfirstlane(C1);
+    }
+    // Length of list y, and its j-th item, of product p: the items are dealt
+    // to the lists in runs of R.
+    __device__ __forceinline__ int len(int p, int y) const
+    {
+        const int R = p ? C1 : C, total = p ? total1 : total0;
+        const int full = total / (R << lg), rem = total - full * (R << lg);
+        return full * R + min(R, max(0, rem - y * R));
+    }
+    __device__ __forceinline__ int item(int j, int y, int p) const
+    {
+        const int R = p ? C1 : C, r = j / R;
+        return r * (R << lg) + y * R + (j - r * R);
+    }
+    // gate/up tiles of a row tile
+    __device__ __forceinline__ int need(int rt) const { return rt < nl0 ? ntl0 : nts0; }
+};
+
+// One workgroup's place in the lists.
+template <bool LARGE>
+struct Worker {
+    int pending;                 // a down item put off for a gate/up item, or -1
+    int first;                   // the fixed first item, or -1
+    bool all_done;               // every row tile's gate/up tiles are written
+    // current item
+    bool down, large;
+    int rti, nt;
+    int pre;                     // thread 0: requested ticket, or -1
+
+    __device__ __forceinline__ bool begin(ArgSched &s, SchedLds &l, int phases, ArgTiles &ct)
+    {
+        const int tid = threadIdx.x, b = blockIdx.x;
+        if (tid < kSchedLdsTiles) l.rt[tid] = ((const int4 *)s.rt)[tid];
+        else if (tid < kSchedLdsTiles + 3) l.hdr[tid - kSchedLdsTiles] = s.hdr[tid - kSchedLdsTiles];
+        else if (tid == 128) l.item = (phases & 1) ? agent_swap(&s.claim[b], 1) : 1;
+        __syncthreads();
+        Items q;
+        q.load<LARGE>(l, phases, ct.ntl[0], ct.ntl[1], ct.nts[0], ct.nts[1]);
+        all_done = false;
+        pending = -1;
+        pre = -1;
+        const int run = q.C << q.lg;
+        first = q.x * q.C + (b >> q.lg);
+        if (__builtin_amdgcn_readfirstlane(l.item) != 0 || first >= q.total0) first = -1;
+        if (tid == 0) l.stage = run + q.x * q.C < q.total0 ? 0 : 1;   // a second run of this list
+        return q.total0 + q.total1 > 0;
+    }
+
+    static __device__ __forceinline__ int32_t *tick_of(ArgSched &s, int p, int y)
+    {
+        return s.tick + (p * kLists + y) * kTickStride;
+    }
+
+    // An item of another list, product in bit 30, or -1 (thread 0).
+    __device__ __forceinline__ static int steal(ArgSched &s, const Items &q)
+    {
+        const int nx = 1 << q.lg;
+        for (;;) {
+            int t0[kLists], t1[kLists];
+#pragma unroll
+            for (int y = 0; y < kLists; ++y) {
+                t0[y] = y < nx ? agent_load(tick_of(s, 0, y)) : 0;
+                t1[y] = y < nx ? agent_load(tick_of(s, 1, y)) : 0;
+            }
+            int found = -1;
+#pragma unroll
+            for (int y = 0; y < kLists; ++y)
+                if (y < nx && t1[y] < q.len(1, y)) found = kLists + y;
+#pragma unroll
+            for (int y = 0; y < kLists; ++y)
+                if (y < nx && q.C + t0[y] < q.len(0, y)) found = y;
+            if (found < 0) return -1;
+            const int p = found >> kListsLog2, y = found & (kLists - 1);
+            const int j = agent_add(tick_of(s, p, y), 1) + (p ? 0 : q.C);
+            if (j < q.len(p, y)) return q.item(j, y, p) | p << 30;
+        }
+    }
+    // Next item (thread 0).
+    __device__ __forceinline__ int take(ArgSched &s, SchedLds &l, const Items &q)
+    {
+        int stage = l.stage;
+        if (stage == 0) {
+            const int j = q.C + (pre >= 0 ? pre : agent_add(tick_of(s, 0, q.x), 1));
+            pre = -1;
+            if (j < q.len(0, q.x)) return q.item(j, q.x, 0);
+            l.stage = stage = 1;
+        }
+        if (stage == 1) {
+            const int n = q.len(1, q.x);
+            if (n > 0) {
+                const int j = pre >= 0 ? pre : agent_add(tick_of(s, 1, q.x), 1);
+                pre = -1;
+                if (j < n) return q.item(j, q.x, 1) | 1 << 30;
+            }
+            l.stage = 2;
+        }
+        return steal(s, q);
+    }
+
+    // Wave 0: waits until the rows of row tile rt are ready.  -1: they are,
+    // -2: the rows of every row tile are, >= 0: a gate/up item to run first.
+    static __device__ __forceinline__ int wait_or_help(ArgSched &s, const Items &q, int rt, int32_t *err)
+    {
+        const int lane = threadIdx.x & 63, nx = 1 << q.lg;
+        for (int polls = 0;; ++polls) {
+            const int v = agent_load(&s.dep[rt]);
+            bool mine = q.nrt <= 256;
+            if (mine) {
+                int d[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[i] = agent_load(&s.dep[min(lane + 64 * i, q.nrt - 1)]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mine &= d[i] >= q.need(min(lane + 64 * i, q.nrt - 1));
+            }
+            if (__all(mine)) return -2;
+            if (__builtin_amdgcn_readfirstlane(v) >= q.need(rt)) return -1;
+            if (polls > 2) {
+                // gate/up items that no workgroup has taken: tickets ...
+                const int y = lane & (kLists - 1);
+                const bool open = lane < nx && q.C + agent_load(tick_of(s, 0, y)) < q.len(0, y);
+                const uint64_t m = __ballot(open);
+                if (m) {
+                    const int yy = __ffsll((unsigned long long)m) - 1;
+                    int j = 0;
+                    if (lane == 0) j = q.C + agent_add(tick_of(s, 0, yy), 1);
+                    j = __builtin_amdgcn_readfirstlane(j);
+                    if (j < q.len(0, yy)) return q.item(j, yy, 0);
+                    continue;
+                }
+                // ... and the fixed ones of workgroups that have not started
+                for (int b0 = 0; b0 < (int)gridDim.x; b0 += 64) {
+                    const int b = b0 + lane;
+                    const bool idle = b < (int)gridDim.x && (b & (nx - 1)) * q.C + (b >> q.lg) < q.total0 &&
+                                      agent_load(&s.claim[min(b, (int)gridDim.x - 1)]) == 0;
+                    const uint64_t c = __ballot(idle);
+                    if (c) {
+                        const int bb = b0 + __ffsll((unsigned long long)c) - 1;
+                        int old = 0;
+                        if (lane == 0) old = agent_swap(&s.claim[bb], 1);
+                        old = __builtin_amdgcn_readfirstlane(old);
+                        if (old == 0) return (bb & (nx - 1)) * q.C + (bb >> q.lg);
+                    }
+                }
+            }
+            if (polls >= kMaxPolls) {
+                if (lane == 0) atomicOr(err, kErrStalled);
+                return -1;
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+    }
+
+    __device__ __forceinline__ static int4 entry(ArgSched &s, const SchedLds &l, int rt)
+    {
+        int4 v;
+        if (rt < kSchedLdsTiles) v = l.rt[rt];
+        else v = ((const int4 *)s.rt)[rt];
+        return v;
+    }
+
+    // Row tile and column tile of item `it` of product p.
+    __device__ __forceinline__ void decode(ArgSched &s, const SchedLds &l, const Items &q, int it, int p)
+    {
+        const int nl = p ? q.nl1 : q.nl0, wl = p ? q.ntl1 : q.ntl0, ws = p ? q.nts1 : q.nts0;
+        large = it < nl * wl;
+        if (large) {
+            // the items of a group's m row tiles from the first on, in bands
+            const int r0 = it / wl;
+            const int4 e = entry(s, l, r0);
+            const int rt0 = __builtin_amdgcn_readfirstlane(e.w), m = __builtin_amdgcn_readfirstlane(e.z) >> 9;
+            const int i = it - rt0 * wl;
+            if (m <= kBandM) {
+                rti = i % m;
+                nt = i / m;
+            } else {
+                const int band = i / (kBandM * wl), r = i - band * kBandM * wl;
+                const int bm = min(kBandM, m - band * kBandM);
+                rti = band * kBandM + r % bm;
+                nt = r / bm;
+            }
+            rti += rt0;
+        } else {
+            const int i = it - nl * wl;
+            const int j = i / ws;
+            rti = nl + j;
+            nt = i - j * ws;
+        }
+        rti = __builtin_amdgcn_readfirstlane(rti);
+        nt = __builtin_amdgcn_readfirstlane(nt);
+    }
+
+    // The workgroup's next item; false: none is left.
+    __device__ __forceinline__ bool next(ArgSched &s, SchedLds &l, int phases, ArgTiles &ct, int32_t *err)
+    {
+        Items q;
+        q.load<LARGE>(l, phases, ct.ntl[0], ct.ntl[1], ct.nts[0], ct.nts[1]);
+        int it = pending;
+        if (first >= 0) {
+            it = first;
+            first = -1;
+        } else if (it < 0) {
+            __syncthreads();             // every thread has read the last item
+            if (threadIdx.x == 0) l.item = take(s, l, q);
+            __syncthreads();
+            it = __builtin_amdgcn_readfirstlane(l.item);
+            if (it < 0) return false;
+        }
+        pending = -1;
+        const int p = it >> 30;
+        it &= ~(1 << 30);
+        down = p != 0;
+        decode(s, l, q, it, p);
+        if (p && phases == 3 && !all_done) {
+            if (threadIdx.x < 64) {
+                const int r = wait_or_help(s, q, rti, err);
+                if (threadIdx.x == 0) l.wait = r;
+            }
+            __syncthreads();
+            const int r = __builtin_amdgcn_readfirstlane(l.wait);
+            if (r == -2) all_done = true;
+            if (r >= 0) {
+                pending = it | 1 << 30;
+                down = false;
+                decode(s, l, q, r, 0);
+            }
+        }
+        // request the next ticket now: it comes back while this item runs
+        if (threadIdx.x == 0 && pending < 0 && pre < 0) {
+            if (l.stage == 0) pre = agent_add(tick_of(s, 0, q.x), 1);
+            else if (l.stage == 1 && q.total1 > 0) pre = agent_add(tick_of(s, 1, q.x), 1);
+        }
+        return true;
+    }
+
+    __device__ __forceinline__ RowTile row_tile(ArgSched &s, const SchedLds &l) const
+    {
+        const int4 v = entry(s, l, rti);
+        RowTile r;
+        const int g = __builtin_amdgcn_readfirstlane(v.x);
+        r.group = g & 0xffff;
+        r.only = g >> 30;
+        r.row0 = __builtin_amdgcn_readfirstlane(v.y);
+        r.rows = __builtin_amdgcn_readfirstlane(v.z) & 511;
+        return r;
+    }
+
+    // The item's output is stored: a gate/up tile is counted once every
+    // wave's stores have reached memory.  Past it every LDS read of the item
+    // is done.
+    __device__ __forceinline__ void done(ArgSched &s)
+    {
+        if (!down) __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
+        __syncthreads();
+        if (!down && threadIdx.x == 0) agent_add(&s.dep[rti], 1);
+    }
+};
+
+}  // namespace moe

@@ -5,8 +5,16 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "ffn_sched.h"
 
 namespace moe {
+
+// What the row-tile build knows of the launch that will run them: its
+// workgroups, and the column tiles of the gate/up product (of 256 and of 128
+// columns).
+struct SchedPlan {
+    int32_t grid, nt_large, nt_small;
+};
 
 struct DispatchArgs {
     const int32_t *ids;      // [T*k]
@@ -16,23 +24,27 @@ struct DispatchArgs {
     int32_t *blk_counts;     // [nb][E]
     int32_t *counts;         // [E]
     int32_t *offsets;        // [E_loc+1]
-    GroupTable groups;       // G = E_loc + has_shared groups
+    GroupTable groups;       // G = E_loc + has_shared groups (null: not wanted)
+    Sched sched;             // the FFN's row tiles (unused without groups)
+    SchedPlan plan;
     int32_t *slot_of_row;    // [cap]
     int32_t *row_of_slot;    // [T*k]
     int32_t *err;            // sticky error word
 };
 
-// Histogram -> scan (+ GEMM tile table) -> stable scatter.
+// Histogram -> scan (+ the FFN's row tiles) -> stable scatter.
 hipError_t launch_dispatch_index(const DispatchArgs &a, hipStream_t s);
 
-// Tile tables (GroupTable over the E_loc routed groups, no shared group) for
-// rows that arrive already grouped by local expert: counts[i] rows of expert
+// Row tiles (over the E_loc routed groups, no shared group) for rows that arrive already grouped by local expert: counts[i] rows of expert
 // i, consecutive.  Counts are read on the device; a negative count is taken
 // as 0 and the running total is capped at n_rows_max (later groups lose
 // their rows), both reported through kErrBadCount in *err.
 hipError_t launch_group_tables_from_counts(const int32_t *counts, int32_t E_loc,
-                                           int32_t n_rows_max, GroupTable g, int32_t *err,
-                                           hipStream_t s);
+                                           int32_t n_rows_max, GroupTable g, const Sched &sched,
+                                           const SchedPlan &plan, int32_t *err, hipStream_t s);
+
+// Clears a schedule's counters for another pass over the same row tiles.
+hipError_t launch_reset_schedule(const Sched &s, hipStream_t st);
 
 // fp8: the token scales of the routed rows, transposed: x_perm_scales[g *
 // scale_ld + r] = x_scales[(slot_of_row[r] / k) * n_scales + g] for r <
@@ -120,16 +132,42 @@ __device__ __forceinline__ void resolve_weights(const GemmArgs &a, const void *&
     }
 }
 
-// bf16 grouped GEMM.  swiglu = true: B is the packed [gate|up] matrix
-// (N = 2f) and C receives SiLU(gate) * up as [rows][f] bf16; otherwise C
-// receives the product as [rows][N] bf16.  mt_max bounds the number of
-// 256-row tiles over all groups (the grid is sized from it).
-hipError_t launch_gemm_bf16(const GemmArgs &a, bool swiglu, int mt_max, int num_cus,
-                            hipStream_t s);
-// bf16 grouped GEMM for the groups with 1..kSmallRows rows: one 256-row x
-// 128-column tile per (group, column block); g_max bounds the group count.
-hipError_t launch_gemm_bf16_small(const GemmArgs &a, bool swiglu, int g_max, int num_cus,
-                                  hipStream_t s);
+// One product of an FFN pass, as a work item sees it.
+struct FfnProduct {
+    const void *A_routed, *A_shared;   // token rows (x or pre-grouped rows), or H; [rows][K]
+    void *C_routed, *C_shared;         // H, or Y
+    const void *W;                     // packed weights of layer 0, [G][N][K]
+    int32_t N, K;
+    int32_t ldc;                       // elements of an output row
+};
+
+struct FfnArgs {
+    FfnProduct p1, p2;                 // gate/up, down
+    // When A_index is set, routed row r of p1 is row A_index[r] / A_index_div
+    // of p1.A_routed, which has A_routed_rows rows (the row gather happens in
+    // the token-row loads; A_index = slot_of_row).
+    const int32_t *A_index;
+    int32_t A_index_div;
+    int64_t A_routed_rows;
+    int32_t shared_group;              // index of the shared group, -1 if none
+    int32_t phases;                    // 1: gate/up items, 2: down items, 3: both
+    Sched sched;
+    FfnTiles tiles;
+    // Layer-oblivious weights: with layer_id set, the weights are taken on the
+    // device from layers[*layer_id]; an id outside [0, n_layers) is clamped
+    // and flagged in err.
+    const int32_t *layer_id;
+    const LayerWeights *layers;
+    int32_t n_layers;
+    int32_t *err;
+};
+
+// bf16 expert FFN over the row tiles of a.sched (ffn_bf16.h).  rt_max bounds
+// the row tiles, grid is the workgroups the row tiles were planned for (at
+// most one per CU).  launch_ffn_bf16_small is for passes all of whose groups
+// have at most kSmallRows rows.
+hipError_t launch_ffn_bf16(const FfnArgs &a, int grid, hipStream_t s);
+hipError_t launch_ffn_bf16_small(const FfnArgs &a, int grid, hipStream_t s);
 
 // e4m3 grouped GEMM with 128-block scales (same conventions; the A scales
 // are transposed, [K/128][ld] with ld = lds_rows_routed / lds_rows_shared).

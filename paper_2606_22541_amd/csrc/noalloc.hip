@@ -3,10 +3,9 @@
 // grouping of section 3.2.1), for callers that cannot allocate device memory
 // (code under HIP graph capture, serving loops, harnesses that forbid it).
 //
-// The kernels are the stage's own (k_hist, k_place).  What the stage keeps in
-// a slot's workspace -- one histogram row per 1024-slot workgroup and the
-// grouped-GEMM tile tables the placement kernel writes -- lives here in one
-// file-scope device array.  Its device address is looked up once per device
+// The kernels are the stage's own (k_hist, k_place; no row tiles are asked
+// for).  What the stage keeps in a slot's workspace -- one histogram row per
+// 1024-slot workgroup -- lives here in one file-scope device array.  Its device address is looked up once per device
 // with hipGetSymbolAddress (in host code the array's name is not a device
 // address) and only that address is ever handed to a kernel.
 //
@@ -25,12 +24,8 @@ namespace {
 
 // Histogram rows: ceil(T*k / 1024) rows of n_experts counts.
 constexpr int64_t kHistInts = int64_t(1) << 20;                  // 4 MiB
-// Tile tables: two arrays of G and eight of G + 1 entries, G <= 256.
-constexpr int64_t kTableStride = kMaxLocalExperts + 64;          // >= G + 1, 256-byte multiple
-constexpr int kTables = 10;
-constexpr int64_t kTableInts = kTables * kTableStride;
 constexpr int64_t kErrInts = 64;                                 // the fallback error word
-constexpr int64_t kScratchInts = kHistInts + kTableInts + kErrInts;
+constexpr int64_t kScratchInts = kHistInts + kErrInts;
 constexpr int kMaxDevices = 64;
 
 }  // namespace
@@ -86,7 +81,6 @@ extern "C" moe_status moe_dispatch_index_noalloc(const int32_t *topk_ids, int32_
     int32_t *base = nullptr;
     const moe_status st = scratch_for_current_device(&base);
     if (st != MOE_OK) return st;
-    int32_t *tables = base + kHistInts;
     DispatchArgs a{};
     a.ids = topk_ids;
     a.n_slots = (int32_t)n_slots;
@@ -99,14 +93,8 @@ extern "C" moe_status moe_dispatch_index_noalloc(const int32_t *topk_ids, int32_
     a.blk_counts = base;
     a.counts = counts;
     a.offsets = offsets;
-    a.groups = GroupTable{tables + 0 * kTableStride, tables + 1 * kTableStride,
-                          tables + 2 * kTableStride, tables + 3 * kTableStride,
-                          tables + 4 * kTableStride, tables + 5 * kTableStride,
-                          tables + 6 * kTableStride, tables + 7 * kTableStride,
-                          tables + 8 * kTableStride, tables + 9 * kTableStride};
-    static_assert(kTables == 10, "one array per GroupTable member");
     a.slot_of_row = slot_of_row;
     a.row_of_slot = row_of_slot;
-    a.err = err ? err : base + kHistInts + kTableInts;
+    a.err = err ? err : base + kHistInts;
     return launch_dispatch_index(a, (hipStream_t)stream) == hipSuccess ? MOE_OK : MOE_EHIP;
 }

@@ -22,15 +22,14 @@ namespace {
 struct SlotWs {
     int32_t *blk_counts = nullptr, *counts = nullptr, *offsets = nullptr;
     int32_t *g_row0 = nullptr, *g_rows = nullptr;
-    int32_t *g_lt_base = nullptr, *g_st_base = nullptr;
-    int32_t *g_fl_base = nullptr, *g_pl_list = nullptr;
-    int32_t *g_lt_base_d = nullptr, *g_st_base_d = nullptr, *g_fl_base_d = nullptr,
-            *g_pl_list_d = nullptr;
-    GroupTable tables() const
-    {
-        return GroupTable{g_row0,    g_rows,      g_lt_base,   g_st_base,   g_fl_base,
-                          g_pl_list, g_lt_base_d, g_st_base_d, g_fl_base_d, g_pl_list_d};
-    }
+    Sched sched{};
+    // The schedule's counters are as the dispatch left them: an FFN pass takes
+    // the work they count out, and a second one on the same dispatch has to
+    // clear them first.  Once a pass of this slot was captured in a graph the
+    // host no longer knows, and every pass that no dispatch precedes in its
+    // own call clears them.
+    bool sched_fresh = false, captured = false;
+    GroupTable tables() const { return GroupTable{g_row0, g_rows}; }
     int32_t *slot_of_row = nullptr, *row_of_slot = nullptr;
     float *x_perm_s = nullptr;     // fp8: the routed rows' x scales, transposed
     void *h = nullptr;
@@ -47,7 +46,7 @@ struct SlotWs {
 };
 
 struct Sizes {
-    int64_t G, cap, nb_max, eb, n_slots_tok;
+    int64_t G, cap, nb_max, eb, n_slots_tok, rt_max;
     int64_t w1, w2, s1, s2;                 // bytes, all layers
     int64_t w1l, w2l, s1l, s2l;             // bytes of one layer
     int64_t per_slot;                       // bytes
@@ -115,7 +114,8 @@ Sizes sizes_of(const moe_stage_desc *d)
     const int64_t T1 = T > 0 ? T : 1;
     int64_t b = 0;
     b += align256(s.nb_max * E * 4) + align256(E * 4) + align256((El + 1) * 4);
-    b += 2 * align256(s.G * 4) + 8 * align256((s.G + 1) * 4);
+    s.rt_max = sched_max_tiles(cap1 + (d->has_shared_expert ? T1 : 0), s.G);
+    b += 2 * align256(s.G * 4) + align256(sched_ints(s.rt_max) * 4);
     b += align256(cap1 * 4) + align256((s.n_slots_tok > 0 ? s.n_slots_tok : 1) * 4);
     if (fp8) b += align256(cap1 * (D / 128) * 4);   // gathered token scales (fp8 only)
     b += align256(cap1 * F * s.eb) + (fp8 ? align256(cap1 * (F / 128) * 4) : 0);
@@ -374,15 +374,12 @@ moe_status moe_stage_create(const moe_stage_desc *desc, const moe_weights *w, mo
     for (auto &sl : st->slots) {
         ok = alloc(st, &sl.blk_counts, z.nb_max * E * 4) && alloc(st, &sl.counts, E * 4) &&
              alloc(st, &sl.offsets, (El + 1) * 4) &&
-             alloc(st, &sl.g_row0, z.G * 4) && alloc(st, &sl.g_rows, z.G * 4) &&
-             alloc(st, &sl.g_lt_base, (z.G + 1) * 4) && alloc(st, &sl.g_st_base, (z.G + 1) * 4) &&
-             alloc(st, &sl.g_fl_base, (z.G + 1) * 4) &&
-             alloc(st, &sl.g_pl_list, (z.G + 1) * 4) && alloc(st, &sl.g_lt_base_d, (z.G + 1) * 4) &&
-             alloc(st, &sl.g_st_base_d, (z.G + 1) * 4) && alloc(st, &sl.g_fl_base_d, (z.G + 1) * 4) &&
-             alloc(st, &sl.g_pl_list_d, (z.G + 1) * 4) && alloc(st, &sl.slot_of_row, cap1 * 4) &&
+             alloc(st, &sl.g_row0, z.G * 4) && alloc(st, &sl.g_rows, z.G * 4) && alloc(st, &sl.sched.hdr, sched_ints(z.rt_max) * 4) &&
+             alloc(st, &sl.slot_of_row, cap1 * 4) &&
              alloc(st, &sl.row_of_slot, (z.n_slots_tok > 0 ? z.n_slots_tok : 1) * 4) &&
              alloc(st, &sl.h, cap1 * F * z.eb) &&
              alloc(st, &sl.y_perm, cap1 * D * 2);
+        if (ok) sl.sched = sched_at(sl.sched.hdr, z.rt_max);
         // no X_perm: the gate/up GEMM gathers the token rows itself; fp8 keeps
         // the gathered token scales
         if (ok && fp8) ok = alloc(st, &sl.x_perm_s, cap1 * (D / 128) * 4) &&
@@ -442,6 +439,20 @@ static int stream_cus(const moe_stage *st, hipStream_t s)
     return (n > 0 && n < st->num_cus) ? n : st->num_cus;
 }
 
+// Workgroups of an FFN pass on `cus` compute units: one per CU, a multiple of
+// the 8 XCDs' lists.
+static int ffn_grid(int cus)
+{
+    const int g = cus < kMaxSchedCus ? cus : kMaxSchedCus;
+    return g >= kLists ? g & ~(kLists - 1) : g;
+}
+
+static SchedPlan sched_plan(const moe_stage *st, int cus)
+{
+    const int n1 = 2 * st->desc.d_ff;
+    return SchedPlan{ffn_grid(cus), (n1 + 255) / 256, (n1 + 127) / 128};
+}
+
 // The three phases.  `rec` records the slot's event at the end; a submit
 // records it once, after the combine, since every record is a release that
 // stalls the stream for several microseconds.
@@ -470,6 +481,9 @@ static moe_status dispatch_impl(moe_stage *st, int32_t slot, const moe_microbatc
     a.counts = sl.counts;
     a.offsets = sl.offsets;
     a.groups = sl.tables();
+    a.sched = sl.sched;
+    a.plan = sched_plan(st, stream_cus(st, s));
+    sl.sched_fresh = true;
     a.slot_of_row = sl.slot_of_row;
     a.row_of_slot = sl.row_of_slot;
     a.err = st->err;
@@ -494,45 +508,129 @@ static moe_status dispatch_impl(moe_stage *st, int32_t slot, const moe_microbatc
     return rec ? record(sl, s) : MOE_OK;
 }
 
+// What one FFN pass reads and writes, beside the slot's workspace.
+struct FfnPass {
+    const void *rows;                 // x, or pre-grouped rows
+    const void *rows_shared;          // x when the shared expert runs, else null
+    const int32_t *index;             // slot_of_row when `rows` is x, else null
+    int64_t n_rows;                   // rows of x (indexed)
+    void *y;                          // Y_perm, or the caller's y
+    const int32_t *layer_id;
+    int64_t max_group;                // no group has more rows than this
+    int64_t mt_max;                   // bound on the 256-row tiles of all groups
+    int32_t G;
+};
+
 // The two grouped GEMMs of one FFN pass on `s`: gate/up with the fused
-// SiLU*up epilogue (fp8: and the quantisation of h), then down.  mt_max bounds
-// the 256-row tiles of all groups together (grid sizes only).
-static moe_status launch_ffn(moe_stage *st, GemmArgs &g1, GemmArgs &g2, int64_t mt_max,
+// SiLU*up epilogue (fp8: and the quantisation of h), then down.
+// `after_dispatch`: the dispatch was enqueued by the same call, so the
+// schedule's counters are as it leaves them.
+static moe_status launch_ffn(moe_stage *st, SlotWs &sl, const FfnPass &f, bool after_dispatch,
                              hipStream_t s)
 {
     const moe_stage_desc &d = st->desc;
     const bool fp8 = d.dtype == MOE_DTYPE_FP8_E4M3_B128;
-    const int mt = mt_max > 0x7fffffff ? 0x7fffffff : (int)mt_max;
-    const int32_t cap = (int32_t)st->sz.cap, tmax = d.max_tokens;
-    hipError_t e;
-    // bf16: groups of at most kSmallRows rows run in the small-group kernel,
-    // the others in the 256x256-tile kernel (either may find no tiles).
-    const int gmax = (int)st->sz.G;
+    const int mt = f.mt_max > 0x7fffffff ? 0x7fffffff : (int)f.mt_max;
     const int cus = stream_cus(st, s);
+    const int32_t shared_group = f.rows_shared ? d.n_local_experts : -1;
+    hipError_t e = hipSuccess;
+    if (!fp8) {
+        if (!after_dispatch) {
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(s, &cs) != hipSuccess) (void)hipGetLastError();
+            sl.captured |= cs != hipStreamCaptureStatusNone;
+            if ((!sl.sched_fresh || sl.captured) && launch_reset_schedule(sl.sched, s) != hipSuccess)
+                return MOE_EHIP;
+        }
+        sl.sched_fresh = false;
+        FfnArgs a{};
+        a.p1 = FfnProduct{f.rows, f.rows_shared, sl.h, sl.h_sh, st->w1, 2 * d.d_ff, d.d_model, d.d_ff};
+        a.p2 = FfnProduct{sl.h, sl.h_sh, f.y, sl.y_sh, st->w2, d.d_model, d.d_ff, d.d_model};
+        a.A_index = f.index;
+        a.A_index_div = d.top_k;
+        a.A_routed_rows = f.n_rows;
+        a.shared_group = shared_group;
+        a.sched = sl.sched;
+        a.tiles = FfnTiles{{(2 * d.d_ff + 255) / 256, (d.d_model + 255) / 256},
+                           {(2 * d.d_ff + 127) / 128, (d.d_model + 127) / 128}};
+        a.layer_id = f.layer_id;       // weights named on the device (null: layer 0)
+        a.layers = st->layers;
+        a.n_layers = d.n_layers;
+        a.err = st->err;
+        const bool small = f.max_group <= kSmallRows;
+        const int grid = ffn_grid(cus);
+        auto run = [&](int phases) {
+            a.phases = phases;
+            return small ? launch_ffn_bf16_small(a, grid, s) : launch_ffn_bf16(a, grid, s);
+        };
+        if (st->prof_on) {             // timed by product: one launch each
+            {
+                ProfScope ps(st, 2, s);
+                e = run(1);
+            }
+            if (e == hipSuccess) {
+                ProfScope ps(st, 3, s);
+                e = run(2);
+            }
+        } else {
+            e = run(3);
+        }
+        return e == hipSuccess ? MOE_OK : MOE_EHIP;
+    }
+
+    const int32_t cap = (int32_t)st->sz.cap, tmax = d.max_tokens;
+    GemmArgs g1{};
+    g1.A_routed = f.rows;
+    g1.A_shared = f.rows_shared;
+    g1.A_index = f.index;              // routed row r = token slot_of_row[r] / k of x
+    g1.A_index_div = d.top_k;
+    g1.A_routed_rows = f.n_rows;
+    g1.As_routed = sl.x_perm_s;
+    g1.As_shared = sl.xsh_s;
+    g1.B = st->w1;
+    g1.Bs = st->s1;
+    g1.C_routed = sl.h;                // e4m3 codes, with their scales in Cs
+    g1.C_shared = sl.h_sh;
+    g1.Cs_routed = sl.h_s;
+    g1.Cs_shared = sl.h_sh_s;
+    g1.N = 2 * d.d_ff;
+    g1.K = d.d_model;
+    g1.shared_group = shared_group;
+    g1.groups = sl.tables();
+    g1.G = f.G;
+    g1.layer_id = f.layer_id;
+    g1.layers = st->layers;
+    g1.n_layers = d.n_layers;
+    g1.down = 0;
+    g1.err = st->err;
+
+    GemmArgs g2 = g1;
+    g2.A_index = nullptr;              // H rows are already grouped by expert
+    g2.A_index_div = 0;
+    g2.A_routed_rows = 0;
+    g2.Cs_routed = nullptr;            // the down product writes bf16 Y
+    g2.Cs_shared = nullptr;
+    g2.A_routed = sl.h;
+    g2.A_shared = sl.h_sh;
+    g2.As_routed = sl.h_s;
+    g2.As_shared = sl.h_sh_s;
+    g2.B = st->w2;
+    g2.Bs = st->s2;
+    g2.down = 1;
+    g2.C_routed = f.y;
+    g2.C_shared = sl.y_sh;
+    g2.N = d.d_model;
+    g2.K = d.d_ff;
     {
         ProfScope ps(st, 2, s);
-        if (fp8) {
-            e = launch_gemm_fp8(g1, true, mt, gmax, cus, cap, tmax, s);
-        } else {
-            e = launch_gemm_bf16_small(g1, true, gmax, cus, s);
-            if (e == hipSuccess) e = launch_gemm_bf16(g1, true, mt, cus, s);
-        }
+        e = launch_gemm_fp8(g1, true, mt, f.G, cus, cap, tmax, s);
     }
     if (e == hipSuccess) {
         ProfScope ps(st, 3, s);
-        if (fp8) {
-            e = launch_gemm_fp8(g2, false, mt, gmax, cus, cap, tmax, s);
-        } else {
-            // the down product partitions the groups at kSmallRowsDown rows
-            GemmArgs g2d = g2;
-            g2d.groups = down_partition(g2.groups);
-            e = launch_gemm_bf16_small(g2d, false, gmax, cus, s);
-            if (e == hipSuccess) e = launch_gemm_bf16(g2d, false, mt, cus, s);
-        }
+        e = launch_gemm_fp8(g2, false, mt, f.G, cus, cap, tmax, s);
     }
     if (e == hipErrorNotSupported) return MOE_EUNSUPPORTED;
-    if (e != hipSuccess) return MOE_EHIP;
-    return MOE_OK;
+    return e == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 
 static moe_status ffn_impl(moe_stage *st, int32_t slot, void *stream, bool rec)
@@ -544,55 +642,18 @@ static moe_status ffn_impl(moe_stage *st, int32_t slot, void *stream, bool rec)
     const int32_t T = sl.mb.n_tokens;
     hipStream_t s = (hipStream_t)stream;
     if (T == 0) return rec ? record(sl, s) : MOE_OK;
-    const bool fp8 = d.dtype == MOE_DTYPE_FP8_E4M3_B128;
-    const int64_t max_rows = (int64_t)T * d.top_k;
-    int64_t mt_max = (max_rows + kBM - 1) / kBM + d.n_local_experts;
-    if (d.has_shared_expert) mt_max += (T + kBM - 1) / kBM;
-
-    GemmArgs g1{};
-    g1.A_routed = sl.mb.x;           // routed row r = token slot_of_row[r] / k of x
-    g1.A_shared = sl.mb.x;
-    g1.A_index = sl.slot_of_row;
-    g1.A_index_div = d.top_k;
-    g1.A_routed_rows = T;
-    g1.As_routed = sl.x_perm_s;
-    g1.As_shared = sl.xsh_s;
-    g1.B = st->w1;
-    g1.Bs = st->s1;
-    g1.C_routed = sl.h;             // fp8: e4m3 codes, with their scales in Cs
-    g1.C_shared = sl.h_sh;
-    g1.Cs_routed = sl.h_s;
-    g1.Cs_shared = sl.h_sh_s;
-    g1.N = 2 * d.d_ff;
-    g1.K = d.d_model;
-    g1.shared_group = d.has_shared_expert ? d.n_local_experts : -1;
-    g1.groups = sl.tables();
-    g1.G = (int32_t)st->sz.G;
-    g1.layer_id = sl.mb.layer_id;   // weights named on the device (NULL: layer 0)
-    g1.layers = st->layers;
-    g1.n_layers = d.n_layers;
-    g1.down = 0;
-    g1.err = st->err;
-
-    GemmArgs g2 = g1;
-    g2.A_index = nullptr;            // H rows are already grouped by expert
-    g2.A_index_div = 0;
-    g2.A_routed_rows = 0;
-    g2.Cs_routed = nullptr;          // the down product writes bf16 Y
-    g2.Cs_shared = nullptr;
-    g2.A_routed = sl.h;
-    g2.A_shared = sl.h_sh;
-    g2.As_routed = sl.h_s;
-    g2.As_shared = sl.h_sh_s;
-    g2.B = st->w2;
-    g2.Bs = st->s2;
-    g2.down = 1;
-    g2.C_routed = sl.y_perm;
-    g2.C_shared = sl.y_sh;
-    g2.N = d.d_model;
-    g2.K = d.d_ff;
-
-    const moe_status r = launch_ffn(st, g1, g2, mt_max, s);
+    FfnPass f{};
+    f.rows = sl.mb.x;
+    f.rows_shared = d.has_shared_expert ? sl.mb.x : nullptr;
+    f.index = sl.slot_of_row;
+    f.n_rows = T;
+    f.y = sl.y_perm;
+    f.layer_id = sl.mb.layer_id;
+    f.max_group = (int64_t)T * d.top_k;       // a token may repeat an id
+    f.mt_max = (f.max_group + kBM - 1) / kBM + d.n_local_experts;
+    if (d.has_shared_expert) f.mt_max += (T + kBM - 1) / kBM;
+    f.G = (int32_t)st->sz.G;
+    const moe_status r = launch_ffn(st, sl, f, !rec, s);
     if (r != MOE_OK) return r;
     return rec ? record(sl, s) : MOE_OK;
 }
@@ -616,8 +677,8 @@ static moe_status ffn_grouped_impl(moe_stage *st, int32_t slot, const moe_groupe
     const GroupTable gt = sl.tables();
     {
         ProfScope ps(st, 0, s);
-        if (launch_group_tables_from_counts(gb->counts, d.n_local_experts, n, gt, st->err, s) !=
-            hipSuccess)
+        if (launch_group_tables_from_counts(gb->counts, d.n_local_experts, n, gt, sl.sched,
+                                            sched_plan(st, stream_cus(st, s)), st->err, s) != hipSuccess)
             return MOE_EHIP;
     }
     if (fp8) {                       // row scales, transposed as the fp8 GEMM reads them
@@ -626,34 +687,15 @@ static moe_status ffn_grouped_impl(moe_stage *st, int32_t slot, const moe_groupe
                                     (int32_t)st->sz.cap, s) != hipSuccess)
             return MOE_EHIP;
     }
-    GemmArgs g1{};
-    g1.A_routed = gb->rows;
-    g1.As_routed = fp8 ? sl.x_perm_s : nullptr;
-    g1.B = st->w1;
-    g1.Bs = st->s1;
-    g1.C_routed = sl.h;
-    g1.Cs_routed = sl.h_s;
-    g1.N = 2 * d.d_ff;
-    g1.K = d.d_model;
-    g1.shared_group = -1;
-    g1.groups = gt;
-    g1.G = d.n_local_experts;
-    g1.layer_id = gb->layer_id;
-    g1.layers = st->layers;
-    g1.n_layers = d.n_layers;
-    g1.down = 0;
-    g1.err = st->err;
-    GemmArgs g2 = g1;
-    g2.A_routed = sl.h;
-    g2.As_routed = sl.h_s;
-    g2.B = st->w2;
-    g2.Bs = st->s2;
-    g2.C_routed = gb->y;
-    g2.Cs_routed = nullptr;
-    g2.N = d.d_model;
-    g2.K = d.d_ff;
-    g2.down = 1;
-    const moe_status r = launch_ffn(st, g1, g2, ((int64_t)n + kBM - 1) / kBM + d.n_local_experts, s);
+    FfnPass f{};
+    f.rows = gb->rows;
+    f.n_rows = n;
+    f.y = gb->y;
+    f.layer_id = gb->layer_id;
+    f.max_group = n;
+    f.mt_max = ((int64_t)n + kBM - 1) / kBM + d.n_local_experts;
+    f.G = d.n_local_experts;
+    const moe_status r = launch_ffn(st, sl, f, true, s);
     if (r != MOE_OK) return r;
     return record(sl, s);
 }
@@ -860,6 +902,7 @@ moe_status moe_stage_sync(moe_stage *st)
         return (err & kErrBadId)      ? MOE_EBADID
                : (err & kErrBadLayer) ? MOE_EBADLAYER
                : (err & kErrBadCount) ? MOE_EBADCOUNT
+               : (err & kErrStalled)  ? MOE_EHIP
                                       : MOE_ETIMEOUT;
     }
     return MOE_OK;
