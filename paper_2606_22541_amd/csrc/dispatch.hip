@@ -93,24 +93,20 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int &total)
 // E_loc (+1 shared) groups, built by one workgroup; rows[i] is the local
 // expert's token count (tot), or T for the shared expert.
 //
-// A large group's row tiles are as few as hold its 32-row blocks, of even
-// size.  When the items of the gate/up product would not fill the grid once,
-// the groups are split into as many times more row tiles as still fit in one
-// round: the round lasts as long as its largest tile (EP32 share at T = 8191,
-// about 261 rows an expert: two tiles of 160 and 128 rows instead of one of
-// 288).  With more items than workgroups the largest tiles are kept: they do
-// the most work per weight read.
+// A large group is split evenly into as few row tiles of at most h 32-row
+// blocks as hold its rows.  h is kTileBlocks, the size that does the most
+// work per weight read, unless the gate/up product then leaves workgroups
+// without an item: the pass would last as long as its largest tile, so h is
+// the smallest for which the items still fit in one round (a small item
+// counted as a third of a large one: it takes 50 to 80 us at d = 7168, against
+// 150 to 200).  EP32 share at T = 8191, about 261 rows an expert: two tiles of
+// 160 and 128 rows instead of one of 288.
 struct SchedBuildLds {
     int32_t row0[kMaxLocalExperts + 1];
     int32_t tiles[kMaxLocalExperts + 1];      // class << 24 | row tiles
     int32_t cls[3];                           // row tiles: large, small > kSmallRowsDown rows, small
-    int32_t small_items, fit[4];
+    int32_t small_items, fit[kTileBlocks + 1];   // large items when split to h blocks
 };
-
-__device__ __forceinline__ int split_tiles(int nb, int k)
-{
-    return max(1, min((nb + kTileBlocks - 1) / kTileBlocks * k, nb / 2));
-}
 
 __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedPlan &plan, const int32_t *tot,
                                int E_loc, int has_shared, int T, SchedBuildLds &l)
@@ -120,7 +116,7 @@ __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedP
     for (int i = tid; i < kSchedTicks; i += kDispatchThreads) s.tick[i] = 0;
     for (int i = tid; i < kMaxSchedCus; i += kDispatchThreads) s.claim[i] = 0;
     if (tid < 3) l.cls[tid] = 0;
-    if (tid < 4) l.fit[tid] = 0;
+    if (tid <= kTileBlocks) l.fit[tid] = 0;
     if (tid == 0) l.small_items = 0;
     if (tid < 64) {
         int carry = 0;
@@ -141,20 +137,20 @@ __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedP
         const int nb = (rows + 31) >> 5;
         if (rows > kSmallRows) {
 #pragma unroll
-            for (int k = 1; k <= 4; ++k) atomicAdd(&l.fit[k - 1], split_tiles(nb, k) * plan.nt_large);
+            for (int h = 2; h <= kTileBlocks; ++h) atomicAdd(&l.fit[h], (nb + h - 1) / h * plan.nt_large);
         } else if (rows > 0) {
             atomicAdd(&l.small_items, plan.nt_small);
         }
     }
     __syncthreads();
-    int split = 1;
+    int h = kTileBlocks;
 #pragma unroll
-    for (int k = 2; k <= 4; ++k)
-        if (l.fit[k - 1] + l.small_items <= plan.grid) split = k;
+    for (int k = kTileBlocks - 1; k >= 2; --k)
+        if (l.fit[k] + l.small_items / 3 <= plan.grid) h = k;
     for (int i = tid; i < G; i += kDispatchThreads) {
         const int rows = i < E_loc ? tot[i] : T;
         const int c = rows > kSmallRows ? 0 : rows > kSmallRowsDown ? 1 : 2;
-        const int m = c == 0 ? split_tiles((rows + 31) >> 5, split) : rows > 0 ? 1 : 0;
+        const int m = c == 0 ? (((rows + 31) >> 5) + h - 1) / h : rows > 0 ? 1 : 0;
         l.tiles[i] = c << 24 | m;
         if (m) atomicAdd(&l.cls[c], m);
     }
@@ -173,9 +169,9 @@ __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedP
         int4 *rt = (int4 *)s.rt;
         int done = 0;                   // rows placed so far
         for (int k = 0; k < m; ++k) {
-            const int h = min(32 * (q + (k < r ? 1 : 0)), rows - done);
-            rt[at + k] = make_int4(i | (m == 1 ? 1 << 30 : 0), l.row0[i] + done, h | m << 9, at);
-            done += h;
+            const int n_rows = min(32 * (q + (k < r ? 1 : 0)), rows - done);
+            rt[at + k] = make_int4(i | (m == 1 ? 1 << 30 : 0), l.row0[i] + done, n_rows | m << 9, at);
+            done += n_rows;
         }
     }
     for (int i = tid; i < n; i += kDispatchThreads) s.dep[i] = 0;

@@ -274,9 +274,9 @@ __device__ __forceinline__ void pp_step(const Tile &t, const WaveConst &w, const
 // fills its share of the weight fragments).  Both halves pass the same
 // barriers.  row_h: tile row of the half's first block; col_w: the wave's
 // first weight column; N: columns of the product.
-template <int NMB, bool STREAM, bool LEAD>
+template <int NMB, bool STREAM, bool LEAD, typename Request>
 __device__ __forceinline__ void run_large(const Tile &t, const WaveConst &w, const Lds &l, const Out &o,
-                                          int row_h, int col_w, int N, int lane)
+                                          int row_h, int col_w, int N, int lane, Request request)
 {
     f32x16 acc[NMB > 0 ? NMB : 1][2];
 #pragma unroll
@@ -303,6 +303,7 @@ __device__ __forceinline__ void run_large(const Tile &t, const WaveConst &w, con
     if constexpr (!LEAD) mma_step<NMB, STREAM, false>(t, w, nullptr, nullptr, 0, acc, a0, a1, b0, b1);
     __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0): the look-ahead fills
     __syncthreads();                                     // landed before the ring is reused
+    request();
     if constexpr (NMB > 0) {
 #pragma unroll
         for (int mb = 0; mb < NMB; ++mb)
@@ -313,26 +314,26 @@ __device__ __forceinline__ void run_large(const Tile &t, const WaveConst &w, con
     }
 }
 
-template <bool STREAM>
+template <bool STREAM, typename Request>
 __device__ __forceinline__ void run_large_any(const Tile &t, const WaveConst &w, const Lds &l, const Out &o,
-                                              int nmb, int row_h, int col_w, int N, int lane)
+                                              int nmb, int row_h, int col_w, int N, int lane, Request request)
 {
     if (w.wave < 4) {
         switch (nmb) {
-        case 1: run_large<1, STREAM, true>(t, w, l, o, row_h, col_w, N, lane); break;
-        case 2: run_large<2, STREAM, true>(t, w, l, o, row_h, col_w, N, lane); break;
-        case 3: run_large<3, STREAM, true>(t, w, l, o, row_h, col_w, N, lane); break;
-        case 4: run_large<4, STREAM, true>(t, w, l, o, row_h, col_w, N, lane); break;
-        default: run_large<5, STREAM, true>(t, w, l, o, row_h, col_w, N, lane); break;
+        case 1: run_large<1, STREAM, true>(t, w, l, o, row_h, col_w, N, lane, request); break;
+        case 2: run_large<2, STREAM, true>(t, w, l, o, row_h, col_w, N, lane, request); break;
+        case 3: run_large<3, STREAM, true>(t, w, l, o, row_h, col_w, N, lane, request); break;
+        case 4: run_large<4, STREAM, true>(t, w, l, o, row_h, col_w, N, lane, request); break;
+        default: run_large<5, STREAM, true>(t, w, l, o, row_h, col_w, N, lane, request); break;
         }
     } else {
         switch (nmb) {
-        case 0: run_large<0, STREAM, false>(t, w, l, o, row_h, col_w, N, lane); break;
-        case 1: run_large<1, STREAM, false>(t, w, l, o, row_h, col_w, N, lane); break;
-        case 2: run_large<2, STREAM, false>(t, w, l, o, row_h, col_w, N, lane); break;
-        case 3: run_large<3, STREAM, false>(t, w, l, o, row_h, col_w, N, lane); break;
-        case 4: run_large<4, STREAM, false>(t, w, l, o, row_h, col_w, N, lane); break;
-        default: run_large<5, STREAM, false>(t, w, l, o, row_h, col_w, N, lane); break;
+        case 0: run_large<0, STREAM, false>(t, w, l, o, row_h, col_w, N, lane, [] {}); break;
+        case 1: run_large<1, STREAM, false>(t, w, l, o, row_h, col_w, N, lane, [] {}); break;
+        case 2: run_large<2, STREAM, false>(t, w, l, o, row_h, col_w, N, lane, [] {}); break;
+        case 3: run_large<3, STREAM, false>(t, w, l, o, row_h, col_w, N, lane, [] {}); break;
+        case 4: run_large<4, STREAM, false>(t, w, l, o, row_h, col_w, N, lane, [] {}); break;
+        default: run_large<5, STREAM, false>(t, w, l, o, row_h, col_w, N, lane, [] {}); break;
         }
     }
 }
@@ -433,57 +434,63 @@ __device__ __forceinline__ void small_fill(const SmallTile &t, const Lds &l, con
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Sum of the K quarters and output of row blocks 2 R and 2 R + 1: block c =
-// 2 (mb % 2) + column block is finished by wave (c, ch), which the other three
-// quarters hand their partials (4 KB each) through stage c of the ring.
-template <int NMB, int R, int KQ>
+// Sum of the K quarters and output of row blocks 2 R and 2 R + 1: every wave
+// puts its partials (4 KB a block) into stage c = 2 (mb % 2) + column block,
+// and wave (c, ch) sums the four quarters in order and writes the block.  All
+// waves run the same instructions: a workgroup often runs one small tile of a
+// launch, and then each line of this code is fetched from HBM.
+template <int NMB, int R>
 __device__ __forceinline__ void small_round(const Lds &l, const SmallWave &w, const f32x16 (&acc)[NMB][2],
                                             const Out &o, int col)
 {
     __syncthreads();                       // the stages are free
+    const int part = w.ch * 4 + w.kq;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        if (c == KQ || 2 * R + (c >> 1) >= NMB) continue;
+        if (2 * R + (c >> 1) >= NMB) continue;
         const f32x16 &v = acc[2 * R + (c >> 1) < NMB ? 2 * R + (c >> 1) : 0][c & 1];
-        f32x4 *part = (f32x4 *)(l.s[c] + (w.ch * 3 + (KQ - (KQ > c))) * 2048) + w.lane;
+        f32x4 *p = (f32x4 *)(l.s[c] + part * 2048) + w.lane;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            part[g * 64] = (f32x4){v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-        __builtin_amdgcn_sched_barrier(0);
+        for (int g = 0; g < 4; ++g) p[g * 64] = (f32x4){v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
     }
     __syncthreads();
-    if constexpr (2 * R + (KQ >> 1) < NMB) {
-        f32x16 v = acc[2 * R + (KQ >> 1)][KQ & 1];
+    const int mb = 2 * R + (w.kq >> 1);
+    if (mb < NMB) {
+        const bf16 *st = w.kq == 0 ? l.s[0] : w.kq == 1 ? l.s[1] : w.kq == 2 ? l.s[2] : l.s[3];
+        const f32x4 *p = (const f32x4 *)(st + w.ch * 4 * 2048) + w.lane;
+        f32x16 v;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const f32x4 *part = (const f32x4 *)(l.s[KQ] + (w.ch * 3 + q) * 2048) + w.lane;
+        for (int g = 0; g < 4; ++g) {
+            f32x4 x = p[g * 64];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 p = part[g * 64];
+            for (int q = 1; q < 4; ++q) {
+                const f32x4 y = p[q * 256 + g * 64];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * g + e] += p[e];
+                for (int e = 0; e < 4; ++e) x[e] += y[e];
             }
-            __builtin_amdgcn_sched_barrier(0);   // one partial's registers at a time
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * g + e] = x[e];
+            __builtin_amdgcn_sched_barrier(0);
         }
-        store_block(v, o, (2 * R + (KQ >> 1)) * 32 + (w.lane & 31), col + (KQ & 1) * 32, true);
+        store_block(v, o, mb * 32 + (w.lane & 31), col + (w.kq & 1) * 32, true);
     }
 }
 
-template <int NMB, int KQ>
+template <int NMB>
 __device__ __forceinline__ void small_finish(const Lds &l, const SmallWave &w, const f32x16 (&acc)[NMB][2],
                                              const Out &o, int col)
 {
-    small_round<NMB, 0, KQ>(l, w, acc, o, col);
-    if constexpr (NMB > 2) small_round<NMB, 1, KQ>(l, w, acc, o, col);
-    if constexpr (NMB > 4) small_round<NMB, 2, KQ>(l, w, acc, o, col);
+    small_round<NMB, 0>(l, w, acc, o, col);
+    if constexpr (NMB > 2) small_round<NMB, 1>(l, w, acc, o, col);
+    if constexpr (NMB > 4) small_round<NMB, 2>(l, w, acc, o, col);
 }
 
 // One tile with NMB 32-row blocks: K loop, sum of the K quarters and
 // epilogue, fully unrolled over the row blocks so no accumulator crosses a
 // branch.  col: the wave's first weight column.
-template <int NMB>
+template <int NMB, typename Request>
 __device__ __forceinline__ void run_small(const SmallTile &t, const Lds &l, const SmallWave &w,
-                                          const Out &o, int col)
+                                          const Out &o, int col, Request request)
 {
     f32x16 acc[NMB][2];
 #pragma unroll
@@ -507,12 +514,8 @@ __device__ __forceinline__ void run_small(const SmallTile &t, const Lds &l, cons
     // The look-ahead fills (clamped re-reads of the last step) may still be
     // landing in the ring, which the partials overwrite next.
     __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
-    switch (w.kq) {
-    case 0: small_finish<NMB, 0>(l, w, acc, o, col); break;
-    case 1: small_finish<NMB, 1>(l, w, acc, o, col); break;
-    case 2: small_finish<NMB, 2>(l, w, acc, o, col); break;
-    default: small_finish<NMB, 3>(l, w, acc, o, col); break;
-    }
+    request();
+    small_finish<NMB>(l, w, acc, o, col);
 }
 
 // Tiles of more than 160 rows: the accumulators of the 4 x 2 grid do not fit
@@ -605,8 +608,9 @@ __device__ __forceinline__ void tall_finish(const Lds &l, const SmallWave &w, co
     }
 }
 
+template <typename Request>
 __device__ __forceinline__ void run_tall(const SmallTile &t, const Lds &l, const SmallWave &w, const Out &o,
-                                         int col)
+                                         int col, Request request)
 {
     f32x16 acc[kTallBlocks];
 #pragma unroll
@@ -627,6 +631,7 @@ __device__ __forceinline__ void run_tall(const SmallTile &t, const Lds &l, const
         tall_step<1>(t, l, w, acc, k + 1, breg);
     }
     __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0): look-ahead fills
+    request();
     __syncthreads();
     if (w.wave < 4) tall_finish<0>(l, w, acc, o, col); else tall_finish<1>(l, w, acc, o, col);
 }
@@ -660,13 +665,12 @@ void k_ffn_bf16(FfnArgs)
 
     int tid = threadIdx.x;
     Worker<LARGE> wk;
-    if (!wk.begin(args->sched, sl, args->phases, args->tiles)) return;
-    if (tid == 0) {
+    if (tid == 192) {                     // the layer's weights, while begin() loads
         const void *W1 = args->p1.W, *W2 = args->p2.W;
         if (args->layer_id) {
             int ly = *args->layer_id;
             if (ly < 0 || ly >= args->n_layers) {
-                if (blockIdx.x == 0) atomicOr(args->err, kErrBadLayer);
+                if (blockIdx.x == 0 && args->sched.hdr[0] > 0) atomicOr(args->err, kErrBadLayer);
                 ly = ly < 0 ? 0 : args->n_layers - 1;
             }
             W1 = args->layers[ly].w1;
@@ -675,10 +679,11 @@ void k_ffn_bf16(FfnArgs)
         sl.w[0] = (uint64_t)W1;
         sl.w[1] = (uint64_t)W2;
     }
-    __syncthreads();
+    if (!wk.begin(args->sched, sl, args->phases, args->tiles)) return;
 
     for (;;) {
         args = reload(args);
+        asm volatile("" : "+v"(tid));
         if (!wk.next(args->sched, sl, args->phases, args->tiles, args->err)) break;
         args = reload(args);
         // nothing that a lane derives from its number is kept over the items
@@ -686,6 +691,7 @@ void k_ffn_bf16(FfnArgs)
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const bool down = wk.down;
+        auto request = [&] { wk.request(); };
         const RowTile rt = wk.row_tile(args->sched, sl);
         const bool sh = rt.group == args->shared_group;
         const int N = down ? args->p2.N : args->p1.N, K = down ? args->p2.K : args->p1.K;
@@ -743,8 +749,8 @@ void k_ffn_bf16(FfnArgs)
                     t.va[i] = hr[i] < hrows ? src[i] * K * 2 + chunk : (int)0x80000000u;
             }
             const int col_w = n0 + (wave & 3) * 64;
-            if (rt.only) run_large_any<true>(t, w, l, o, nmb, row_h, col_w, N, lane);
-            else run_large_any<false>(t, w, l, o, nmb, row_h, col_w, N, lane);
+            if (rt.only) run_large_any<true>(t, w, l, o, nmb, row_h, col_w, N, lane, request);
+            else run_large_any<false>(t, w, l, o, nmb, row_h, col_w, N, lane, request);
         } else {
             const int n0 = wk.nt * 128;
             SmallWave sw{wave, lane, wave >> 1, wave & 1};
@@ -777,17 +783,17 @@ void k_ffn_bf16(FfnArgs)
             }
             if (nb == kTallBlocks) {
                 t.vb = (wave >> 2) * ncb * 2048 + (4 * half + (wave & 3)) * 2048 + lane * 16;
-                run_tall(t, l, sw, o, n0 + (wave & 3) * 32);
+                run_tall(t, l, sw, o, n0 + (wave & 3) * 32, request);
                 wk.done(args->sched);
                 continue;
             }
             const int col = n0 + sw.ch * 64;
             switch (nb) {
-            case 1: run_small<1>(t, l, sw, o, col); break;
-            case 2: run_small<2>(t, l, sw, o, col); break;
-            case 3: run_small<3>(t, l, sw, o, col); break;
-            case 4: run_small<4>(t, l, sw, o, col); break;
-            default: run_small<5>(t, l, sw, o, col); break;
+            case 1: run_small<1>(t, l, sw, o, col, request); break;
+            case 2: run_small<2>(t, l, sw, o, col, request); break;
+            case 3: run_small<3>(t, l, sw, o, col, request); break;
+            case 4: run_small<4>(t, l, sw, o, col, request); break;
+            default: run_small<5>(t, l, sw, o, col, request); break;
             }
         }
         wk.done(args->sched);

@@ -169,6 +169,7 @@ struct Worker {
     // current item
     bool down, large;
     int rti, nt;
+    int32_t *next_tick;          // counter of the next ticket, or null
     int pre;                     // thread 0: requested ticket, or -1
 
     __device__ __forceinline__ bool begin(ArgSched &s, SchedLds &l, int phases, ArgTiles &ct)
@@ -195,50 +196,68 @@ struct Worker {
         return s.tick + (p * kLists + y) * kTickStride;
     }
 
-    // An item of another list, product in bit 30, or -1 (thread 0).
-    __device__ __forceinline__ static int steal(ArgSched &s, const Items &q)
+    __device__ __forceinline__ static int4 entry(ArgSched &s, const SchedLds &l, int rt)
     {
-        const int nx = 1 << q.lg;
+        int4 v;
+        if (rt < kSchedLdsTiles) v = l.rt[rt];
+        else v = ((const int4 *)s.rt)[rt];
+        return v;
+    }
+
+    // A ticket of product p, list y (wave 0; every lane gets it).
+    static __device__ __forceinline__ int ticket(ArgSched &s, int p, int y)
+    {
+        int j = 0;
+        if ((threadIdx.x & 63) == 0) j = agent_add(tick_of(s, p, y), 1);
+        return __builtin_amdgcn_readfirstlane(j);
+    }
+    // An item of another list, product in bit 30, or -1 (wave 0): lane
+    // kLists p + y looks at list y of product p.  Items that can run at once
+    // (gate/up items, and down items whose rows are ready) come first.
+    static __device__ __forceinline__ int steal(ArgSched &s, const SchedLds &l, const Items &q)
+    {
+        const int lane = threadIdx.x & 63, p = lane >> kListsLog2 & 1, y = lane & (kLists - 1);
+        const int first = p ? 0 : q.C;
+        const int n = lane < 2 * kLists && y < 1 << q.lg ? q.len(p, y) : 0;
         for (;;) {
-            int t0[kLists], t1[kLists];
-#pragma unroll
-            for (int y = 0; y < kLists; ++y) {
-                t0[y] = y < nx ? agent_load(tick_of(s, 0, y)) : 0;
-                t1[y] = y < nx ? agent_load(tick_of(s, 1, y)) : 0;
+            const int j = n > 0 ? first + agent_load(tick_of(s, p, y)) : 0;
+            const bool open = j < n;
+            const uint64_t any = __ballot(open);
+            if (!any) return -1;
+            bool ready = open;
+            if (open && p) {
+                int rt, nt;
+                find(s, l, q, q.item(j, y, 1), 1, rt, nt);
+                ready = agent_load(&s.dep[rt]) >= q.need(rt);
             }
-            int found = -1;
-#pragma unroll
-            for (int y = 0; y < kLists; ++y)
-                if (y < nx && t1[y] < q.len(1, y)) found = kLists + y;
-#pragma unroll
-            for (int y = 0; y < kLists; ++y)
-                if (y < nx && q.C + t0[y] < q.len(0, y)) found = y;
-            if (found < 0) return -1;
-            const int p = found >> kListsLog2, y = found & (kLists - 1);
-            const int j = agent_add(tick_of(s, p, y), 1) + (p ? 0 : q.C);
-            if (j < q.len(p, y)) return q.item(j, y, p) | p << 30;
+            const uint64_t now = __ballot(ready);
+            const int v = __ffsll((unsigned long long)(now ? now : any)) - 1;
+            const int pp = v >> kListsLog2, yy = v & (kLists - 1);
+            const int t = ticket(s, pp, yy) + (pp ? 0 : q.C);
+            if (t < q.len(pp, yy)) return q.item(t, yy, pp) | pp << 30;
         }
     }
-    // Next item (thread 0).
+    // Next item (wave 0).
     __device__ __forceinline__ int take(ArgSched &s, SchedLds &l, const Items &q)
     {
-        int stage = l.stage;
+        int stage = __builtin_amdgcn_readfirstlane(l.stage);
+        int want = __builtin_amdgcn_readfirstlane(pre);
+        pre = -1;
         if (stage == 0) {
-            const int j = q.C + (pre >= 0 ? pre : agent_add(tick_of(s, 0, q.x), 1));
-            pre = -1;
+            const int j = q.C + (want >= 0 ? want : ticket(s, 0, q.x));
+            want = -1;
             if (j < q.len(0, q.x)) return q.item(j, q.x, 0);
             l.stage = stage = 1;
         }
         if (stage == 1) {
             const int n = q.len(1, q.x);
             if (n > 0) {
-                const int j = pre >= 0 ? pre : agent_add(tick_of(s, 1, q.x), 1);
-                pre = -1;
+                const int j = want >= 0 ? want : ticket(s, 1, q.x);
                 if (j < n) return q.item(j, q.x, 1) | 1 << 30;
             }
             l.stage = 2;
         }
-        return steal(s, q);
+        return steal(s, l, q);
     }
 
     // Wave 0: waits until the rows of row tile rt are ready.  -1: they are,
@@ -265,9 +284,7 @@ struct Worker {
                 const uint64_t m = __ballot(open);
                 if (m) {
                     const int yy = __ffsll((unsigned long long)m) - 1;
-                    int j = 0;
-                    if (lane == 0) j = q.C + agent_add(tick_of(s, 0, yy), 1);
-                    j = __builtin_amdgcn_readfirstlane(j);
+                    const int j = q.C + ticket(s, 0, yy);
                     if (j < q.len(0, yy)) return q.item(j, yy, 0);
                     continue;
                 }
@@ -294,43 +311,41 @@ struct Worker {
         }
     }
 
-    __device__ __forceinline__ static int4 entry(ArgSched &s, const SchedLds &l, int rt)
-    {
-        int4 v;
-        if (rt < kSchedLdsTiles) v = l.rt[rt];
-        else v = ((const int4 *)s.rt)[rt];
-        return v;
-    }
-
-    // Row tile and column tile of item `it` of product p.
-    __device__ __forceinline__ void decode(ArgSched &s, const SchedLds &l, const Items &q, int it, int p)
+    // Row tile and column tile of item `it` of product p (any lane's own).
+    static __device__ __forceinline__ bool find(ArgSched &s, const SchedLds &l, const Items &q, int it, int p,
+                                                int &rt, int &nt)
     {
         const int nl = p ? q.nl1 : q.nl0, wl = p ? q.ntl1 : q.ntl0, ws = p ? q.nts1 : q.nts0;
-        large = it < nl * wl;
+        const bool large = it < nl * wl;
         if (large) {
             // the items of a group's m row tiles from the first on, in bands
             const int r0 = it / wl;
             const int4 e = entry(s, l, r0);
-            const int rt0 = __builtin_amdgcn_readfirstlane(e.w), m = __builtin_amdgcn_readfirstlane(e.z) >> 9;
+            const int rt0 = e.w, m = e.z >> 9;
             const int i = it - rt0 * wl;
             if (m <= kBandM) {
-                rti = i % m;
                 nt = i / m;
+                rt = rt0 + i - nt * m;
             } else {
                 const int band = i / (kBandM * wl), r = i - band * kBandM * wl;
                 const int bm = min(kBandM, m - band * kBandM);
-                rti = band * kBandM + r % bm;
                 nt = r / bm;
+                rt = rt0 + band * kBandM + r - nt * bm;
             }
-            rti += rt0;
         } else {
             const int i = it - nl * wl;
             const int j = i / ws;
-            rti = nl + j;
+            rt = nl + j;
             nt = i - j * ws;
         }
-        rti = __builtin_amdgcn_readfirstlane(rti);
-        nt = __builtin_amdgcn_readfirstlane(nt);
+        return large;
+    }
+    __device__ __forceinline__ void decode(ArgSched &s, const SchedLds &l, const Items &q, int it, int p)
+    {
+        int rt, n;
+        large = __builtin_amdgcn_readfirstlane((int)find(s, l, q, it, p, rt, n)) != 0;
+        rti = __builtin_amdgcn_readfirstlane(rt);
+        nt = __builtin_amdgcn_readfirstlane(n);
     }
 
     // The workgroup's next item; false: none is left.
@@ -344,7 +359,7 @@ struct Worker {
             first = -1;
         } else if (it < 0) {
             __syncthreads();             // every thread has read the last item
-            if (threadIdx.x == 0) l.item = take(s, l, q);
+            if (threadIdx.x < 64) l.item = take(s, l, q);
             __syncthreads();
             it = __builtin_amdgcn_readfirstlane(l.item);
             if (it < 0) return false;
@@ -368,12 +383,19 @@ struct Worker {
                 decode(s, l, q, r, 0);
             }
         }
-        // request the next ticket now: it comes back while this item runs
-        if (threadIdx.x == 0 && pending < 0 && pre < 0) {
-            if (l.stage == 0) pre = agent_add(tick_of(s, 0, q.x), 1);
-            else if (l.stage == 1 && q.total1 > 0) pre = agent_add(tick_of(s, 1, q.x), 1);
-        }
+        // where the next ticket comes from (see request())
+        const int stage = __builtin_amdgcn_readfirstlane(l.stage);
+        next_tick = nullptr;
+        if (pending < 0 && stage < 2 && (stage == 0 || q.total1 > 0)) next_tick = tick_of(s, stage, q.x);
         return true;
+    }
+
+    // Requests the next ticket: before an item's epilogue, so that it comes
+    // back meanwhile.  Not earlier: an item that is taken long before it can
+    // run keeps the workgroups that wait for it waiting.
+    __device__ __forceinline__ void request()
+    {
+        if (next_tick && threadIdx.x == 0 && pre < 0) pre = agent_add(next_tick, 1);
     }
 
     __device__ __forceinline__ RowTile row_tile(ArgSched &s, const SchedLds &l) const
