@@ -66,41 +66,51 @@ struct Out {
 // (v_mfma_f32_32x32x16_bf16 with the weights as its row operand): lane l
 // holds token l % 32, and register r holds feature 8 (r/4) + 4 (l/32) + r%4
 // of the block.  Lanes l and l ^ 32 hold the same token, so after swapping
-// halves each lane has 8 consecutive features and writes 16 bytes.
+// halves each lane has 8 consecutive features, 16 bytes.
 //
-// SwiGLU: the packed gate/up weights interleave by 16, so register r (r < 8)
-// and r + 8 of a lane are gate and up of one h column.  H goes past this
-// XCD's L2 (the stores carry the agent scope): the down items that read it
-// run on other XCDs in the same launch.  tok: the lane's tile row; rows past
-// the tile's fall outside the buffer range and are dropped.
-__device__ __forceinline__ void store_block(const f32x16 &v, const Out &o, int tok, int col, bool present)
+// y_block: the block's 32 features, to memory.  tok: the lane's tile row; rows
+// past the tile's fall outside the buffer range and are dropped.
+__device__ __forceinline__ void y_block(const f32x16 &v, const Out &o, int tok, int col, bool present)
+{
+    const int hi = (__lane_id() >> 5) * 8;
+    uint32_t p[8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        p[2 * q] = pack_bf16x2(v[4 * q], v[4 * q + 1]);
+        p[2 * q + 1] = pack_bf16x2(v[4 * q + 2], v[4 * q + 3]);
+    }
+    swap_halves(p[0], p[2]);
+    swap_halves(p[1], p[3]);
+    swap_halves(p[4], p[6]);
+    swap_halves(p[5], p[7]);
+    const int off = present ? (tok * o.ld + col + hi) * 2 : (int)0x80000000u;
+    __builtin_amdgcn_raw_buffer_store_b128((u32x4){p[0], p[1], p[2], p[3]}, o.r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128((u32x4){p[4], p[5], p[6], p[7]}, o.r, off + 32, 0, 0);
+}
+
+// h_block: SwiGLU.  The packed gate/up weights interleave by 16, so register
+// r (r < 8) and r + 8 of a lane are gate and up of one h column; lane l returns
+// h columns 8 (l / 32) .. + 7 of the block's 16.
+__device__ __forceinline__ u32x4 h_block(const f32x16 &v)
+{
+    uint32_t p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        p[q] = pack_bf16x2(silu_mul(v[2 * q], v[2 * q + 8]), silu_mul(v[2 * q + 1], v[2 * q + 9]));
+    swap_halves(p[0], p[2]);
+    swap_halves(p[1], p[3]);
+    return (u32x4){p[0], p[1], p[2], p[3]};
+}
+
+// H goes past this XCD's L2 to memory (agent scope): the down items that read
+// it run on other XCDs in the same launch, and an item is counted as written
+// only when memory has taken its stores.  The rows are staged in LDS so that
+// they leave as whole 128-byte lines: written 32 bytes at a time, with HBM
+// busy, some tiles' stores took 10 us to be taken.
+__device__ __forceinline__ void h_store(u32x4 v, const Out &o, int off)
 {
     constexpr int kAgentScope = 16;     // sc1
-    const int hi = (__lane_id() >> 5) * 8;
-    if (o.swiglu) {
-        uint32_t p[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            p[q] = pack_bf16x2(silu_mul(v[2 * q], v[2 * q + 8]), silu_mul(v[2 * q + 1], v[2 * q + 9]));
-        swap_halves(p[0], p[2]);
-        swap_halves(p[1], p[3]);
-        const int off = (tok * o.ld + col / 2 + hi) * 2;
-        __builtin_amdgcn_raw_buffer_store_b128((u32x4){p[0], p[1], p[2], p[3]}, o.r, off, 0, kAgentScope);
-    } else {
-        uint32_t p[8];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            p[2 * q] = pack_bf16x2(v[4 * q], v[4 * q + 1]);
-            p[2 * q + 1] = pack_bf16x2(v[4 * q + 2], v[4 * q + 3]);
-        }
-        swap_halves(p[0], p[2]);
-        swap_halves(p[1], p[3]);
-        swap_halves(p[4], p[6]);
-        swap_halves(p[5], p[7]);
-        const int off = present ? (tok * o.ld + col + hi) * 2 : (int)0x80000000u;
-        __builtin_amdgcn_raw_buffer_store_b128((u32x4){p[0], p[1], p[2], p[3]}, o.r, off, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b128((u32x4){p[4], p[5], p[6], p[7]}, o.r, off + 32, 0, 0);
-    }
+    __builtin_amdgcn_raw_buffer_store_b128(v, o.r, off, 0, kAgentScope);
 }
 
 // ---------------------------------------------------------------------------
@@ -148,6 +158,16 @@ struct WaveConst {
 // Token-row loads of a wave whose half holds NMB blocks: its half's 2 NMB
 // groups of 16 rows are loaded by four waves.
 constexpr int row_loads(int nmb) { return (nmb + 1) / 2; }
+
+// Staging of a gate/up tile's h in the ring after the K loop: row block i
+// (first half 0.., second kHalfBlocks..) of 32 rows x 128 columns, padded so
+// that neither side conflicts, three blocks to a stage.
+constexpr int kHStride = 128 + 8;
+static_assert(3 * 32 * kHStride <= kStageElems && 4 * 3 >= kTileBlocks, "h fits the ring");
+__device__ __forceinline__ bf16 *h_stage(const Lds &l, int i)
+{
+    return l.s[i / 3] + (i % 3) * 32 * kHStride;
+}
 
 // Fills of step j, row_loads(NMB) + 2 per wave:
 //  * row groups of 16 rows x 64 bytes, lane l -> row l / 4 of the group,
@@ -305,12 +325,40 @@ __device__ __forceinline__ void run_large(const Tile &t, const WaveConst &w, con
     __syncthreads();                                     // landed before the ring is reused
     request();
     if constexpr (NMB > 0) {
+        if (o.swiglu) {
+            // row block mb of the half at h_stage(): 128 h columns a row
 #pragma unroll
-        for (int mb = 0; mb < NMB; ++mb)
+            for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-                store_block(acc[mb][nb], o, row_h + mb * 32 + (lane & 31), col_w + nb * 32,
+                for (int nb = 0; nb < 2; ++nb) {
+                    bf16 *p = h_stage(l, LEAD ? mb : kHalfBlocks + mb) + (lane & 31) * kHStride +
+                              (w.wave & 3) * 32 + nb * 16 + (lane >> 5) * 8;
+                    *(u32x4 *)p = h_block(acc[mb][nb]);
+                }
+        } else {
+#pragma unroll
+            for (int mb = 0; mb < NMB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                    y_block(acc[mb][nb], o, row_h + mb * 32 + (lane & 31), col_w + nb * 32,
                             col_w + nb * 32 < N);
+        }
+    }
+}
+
+// The staged h of a large tile to memory: a block of 32 rows x 256 bytes is
+// one 16-byte store of every thread.  nb0, nb: row blocks of the first half,
+// of the tile; n0: the tile's first weight column.
+__device__ __forceinline__ void store_h_large(const Lds &l, const Out &o, int nb0, int nb, int n0, int tid)
+{
+    __syncthreads();
+    const int r = tid >> 4, c = tid & 15;
+#pragma unroll
+    for (int i = 0; i < kTileBlocks; ++i) {
+        const int b = i < kHalfBlocks ? i : nb0 + i - kHalfBlocks;       // row block of the tile
+        if (i < kHalfBlocks ? b >= nb0 : b >= nb) continue;
+        const u32x4 v = *(const u32x4 *)(h_stage(l, i) + r * kHStride + c * 8);
+        h_store(v, o, ((b * 32 + r) * o.ld + n0 / 2 + c * 8) * 2);
     }
 }
 
@@ -439,9 +487,10 @@ __device__ __forceinline__ void small_fill(const SmallTile &t, const Lds &l, con
 // and wave (c, ch) sums the four quarters in order and writes the block.  All
 // waves run the same instructions: a workgroup often runs one small tile of a
 // launch, and then each line of this code is fetched from HBM.
+constexpr int kHStrideS = 64 + 8;         // staged h row of a small tile: 64 columns, padded
 template <int NMB, int R>
 __device__ __forceinline__ void small_round(const Lds &l, const SmallWave &w, const f32x16 (&acc)[NMB][2],
-                                            const Out &o, int col)
+                                            const Out &o, int n0, bf16 *hst)
 {
     __syncthreads();                       // the stages are free
     const int part = w.ch * 4 + w.kq;
@@ -454,7 +503,7 @@ __device__ __forceinline__ void small_round(const Lds &l, const SmallWave &w, co
         for (int g = 0; g < 4; ++g) p[g * 64] = (f32x4){v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
     }
     __syncthreads();
-    const int mb = 2 * R + (w.kq >> 1);
+    const int mb = 2 * R + (w.kq >> 1), tok = (w.kq >> 1) * 32 + (w.lane & 31);
     if (mb < NMB) {
         const bf16 *st = w.kq == 0 ? l.s[0] : w.kq == 1 ? l.s[1] : w.kq == 2 ? l.s[2] : l.s[3];
         const f32x4 *p = (const f32x4 *)(st + w.ch * 4 * 2048) + w.lane;
@@ -472,25 +521,34 @@ __device__ __forceinline__ void small_round(const Lds &l, const SmallWave &w, co
             for (int e = 0; e < 4; ++e) v[4 * g + e] = x[e];
             __builtin_amdgcn_sched_barrier(0);
         }
-        store_block(v, o, mb * 32 + (w.lane & 31), col + (w.kq & 1) * 32, true);
+        if (o.swiglu)
+            *(u32x4 *)(hst + tok * kHStrideS + w.ch * 32 + (w.kq & 1) * 16 + (w.lane >> 5) * 8) = h_block(v);
+        else
+            y_block(v, o, R * 64 + tok, n0 + w.ch * 64 + (w.kq & 1) * 32, true);
+    }
+    if (o.swiglu) {
+        __syncthreads();
+        // 64 rows x 128 bytes: one 16-byte store of every thread
+        const int t = w.wave * 64 + w.lane, r = t >> 3, c = t & 7;
+        h_store(*(const u32x4 *)(hst + r * kHStrideS + c * 8), o, ((R * 64 + r) * o.ld + n0 / 2 + c * 8) * 2);
     }
 }
 
 template <int NMB>
 __device__ __forceinline__ void small_finish(const Lds &l, const SmallWave &w, const f32x16 (&acc)[NMB][2],
-                                             const Out &o, int col)
+                                             const Out &o, int n0, bf16 *hst)
 {
-    small_round<NMB, 0>(l, w, acc, o, col);
-    if constexpr (NMB > 2) small_round<NMB, 1>(l, w, acc, o, col);
-    if constexpr (NMB > 4) small_round<NMB, 2>(l, w, acc, o, col);
+    small_round<NMB, 0>(l, w, acc, o, n0, hst);
+    if constexpr (NMB > 2) small_round<NMB, 1>(l, w, acc, o, n0, hst);
+    if constexpr (NMB > 4) small_round<NMB, 2>(l, w, acc, o, n0, hst);
 }
 
 // One tile with NMB 32-row blocks: K loop, sum of the K quarters and
 // epilogue, fully unrolled over the row blocks so no accumulator crosses a
-// branch.  col: the wave's first weight column.
+// branch.  n0: the tile's first weight column.
 template <int NMB, typename Request>
 __device__ __forceinline__ void run_small(const SmallTile &t, const Lds &l, const SmallWave &w,
-                                          const Out &o, int col, Request request)
+                                          const Out &o, int n0, bf16 *hst, Request request)
 {
     f32x16 acc[NMB][2];
 #pragma unroll
@@ -515,7 +573,7 @@ __device__ __forceinline__ void run_small(const SmallTile &t, const Lds &l, cons
     // landing in the ring, which the partials overwrite next.
     __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
     request();
-    small_finish<NMB>(l, w, acc, o, col);
+    small_finish<NMB>(l, w, acc, o, n0, hst);
 }
 
 // Tiles of more than 160 rows: the accumulators of the 4 x 2 grid do not fit
@@ -604,7 +662,9 @@ __device__ __forceinline__ void tall_finish(const Lds &l, const SmallWave &w, co
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[4 * g + e] += p[e];
         }
-        store_block(v, o, mb * 32 + (w.lane & 31), col, true);
+        const int tok = mb * 32 + (w.lane & 31);
+        if (o.swiglu) h_store(h_block(v), o, (tok * o.ld + col / 2 + (w.lane >> 5) * 8) * 2);
+        else y_block(v, o, tok, col, true);
     }
 }
 
@@ -660,6 +720,7 @@ void k_ffn_bf16(FfnArgs)
     __shared__ __attribute__((aligned(1024))) bf16 lds_1[kStageElems];
     __shared__ __attribute__((aligned(1024))) bf16 lds_2[kStageElems];
     __shared__ __attribute__((aligned(1024))) bf16 lds_3[kStageElems];
+    __shared__ __attribute__((aligned(16))) bf16 lds_h[64 * kHStrideS];
     __shared__ SchedLds sl;
     const Lds l{{lds_0, lds_1, lds_2, lds_3}};
 
@@ -751,6 +812,7 @@ void k_ffn_bf16(FfnArgs)
             const int col_w = n0 + (wave & 3) * 64;
             if (rt.only) run_large_any<true>(t, w, l, o, nmb, row_h, col_w, N, lane, request);
             else run_large_any<false>(t, w, l, o, nmb, row_h, col_w, N, lane, request);
+            if (o.swiglu) store_h_large(l, o, nb0, nb, n0, tid);
         } else {
             const int n0 = wk.nt * 128;
             SmallWave sw{wave, lane, wave >> 1, wave & 1};
@@ -787,13 +849,12 @@ void k_ffn_bf16(FfnArgs)
                 wk.done(args->sched);
                 continue;
             }
-            const int col = n0 + sw.ch * 64;
             switch (nb) {
-            case 1: run_small<1>(t, l, sw, o, col, request); break;
-            case 2: run_small<2>(t, l, sw, o, col, request); break;
-            case 3: run_small<3>(t, l, sw, o, col, request); break;
-            case 4: run_small<4>(t, l, sw, o, col, request); break;
-            default: run_small<5>(t, l, sw, o, col, request); break;
+            case 1: run_small<1>(t, l, sw, o, n0, lds_h, request); break;
+            case 2: run_small<2>(t, l, sw, o, n0, lds_h, request); break;
+            case 3: run_small<3>(t, l, sw, o, n0, lds_h, request); break;
+            case 4: run_small<4>(t, l, sw, o, n0, lds_h, request); break;
+            default: run_small<5>(t, l, sw, o, n0, lds_h, request); break;
             }
         }
         wk.done(args->sched);
