@@ -89,6 +89,13 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int &total)
     return x - v;
 }
 
+__device__ __forceinline__ int wave_sum(int v)
+{
+#pragma unroll
+    for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o);
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
 // The groups' rows and the row tiles of the FFN pass (ffn_sched.h) over G =
 // E_loc (+1 shared) groups, built by one workgroup; rows[i] is the local
 // expert's token count (tot), or T for the shared expert.
@@ -101,84 +108,106 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int &total)
 // counted as a third of a large one: it takes 50 to 80 us at d = 7168, against
 // 150 to 200).  EP32 share at T = 8191, about 261 rows an expert: two tiles of
 // 160 and 128 rows instead of one of 288.
-struct SchedBuildLds {
-    int32_t row0[kMaxLocalExperts + 1];
-    int32_t tiles[kMaxLocalExperts + 1];      // class << 24 | row tiles
-    int32_t cls[3];                           // row tiles: large, small > kSmallRowsDown rows, small
-    int32_t small_items, fit[kTileBlocks + 1];   // large items when split to h blocks
-};
-
+// The first wave builds (in chunks of 64 groups, with shuffle scans and no
+// workgroup barrier: the other workgroups place their slots meanwhile), the
+// other waves clear the counters of the next pass.
 __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedPlan &plan, const int32_t *tot,
-                               int E_loc, int has_shared, int T, SchedBuildLds &l)
+                               int E_loc, int has_shared, int T)
 {
-    const int G = E_loc + (has_shared ? 1 : 0), tid = threadIdx.x;
-    // counters of the next pass
-    for (int i = tid; i < kSchedTicks; i += kDispatchThreads) s.tick[i] = 0;
-    for (int i = tid; i < kMaxSchedCus; i += kDispatchThreads) s.claim[i] = 0;
-    if (tid < 3) l.cls[tid] = 0;
-    if (tid <= kTileBlocks) l.fit[tid] = 0;
-    if (tid == 0) l.small_items = 0;
-    if (tid < 64) {
-        int carry = 0;
-        for (int c0 = 0; c0 < E_loc; c0 += 64) {
-            const int i = c0 + tid;
-            int t;
-            const int p = wave_excl_scan(i < E_loc ? tot[i] : 0, tid, t);
-            if (i < E_loc) l.row0[i] = carry + p;
-            carry += t;
-        }
-        if (tid == 0 && has_shared) l.row0[E_loc] = 0;
+    const int G = E_loc + (has_shared ? 1 : 0);
+    if (threadIdx.x >= 64) {
+        for (int i = threadIdx.x - 64; i < kSchedTicks; i += kDispatchThreads - 64) s.tick[i] = 0;
+        for (int i = threadIdx.x - 64; i < kMaxSchedCus; i += kDispatchThreads - 64) s.claim[i] = 0;
+        return;
     }
-    __syncthreads();
-    for (int i = tid; i < G; i += kDispatchThreads) {
-        const int rows = i < E_loc ? tot[i] : T;
-        g.row0[i] = l.row0[i];
-        g.rows[i] = rows;
-        const int nb = (rows + 31) >> 5;
-        if (rows > kSmallRows) {
-#pragma unroll
-            for (int h = 2; h <= kTileBlocks; ++h) atomicAdd(&l.fit[h], (nb + h - 1) / h * plan.nt_large);
-        } else if (rows > 0) {
-            atomicAdd(&l.small_items, plan.nt_small);
-        }
+    const int lane = threadIdx.x;
+    auto rows_of = [&](int i) { return i < E_loc ? tot[i] : (i < G ? T : 0); };
+    // the gate/up items with the largest tiles, and, if they leave workgroups
+    // idle, the smallest height with which they still fit one round
+    int n_small = 0, n10 = 0;
+    bool any_large = false;
+    for (int c0 = 0; c0 < G; c0 += 64) {
+        const int rows = rows_of(c0 + lane);
+        n_small += __popcll(__ballot(rows > 0 && rows <= kSmallRows));
+        any_large |= __ballot(rows > kSmallRows) != 0;
+        n10 += rows > kSmallRows ? (((rows + 31) >> 5) + kTileBlocks - 1) / kTileBlocks : 0;
     }
-    __syncthreads();
+    const int room = plan.grid - n_small * plan.nt_small / 3;
     int h = kTileBlocks;
+    if (any_large && wave_sum(n10) * plan.nt_large <= room) {
+        // lane h: the items with tiles of h blocks (few groups: each makes one
+        // row tile at least)
+        const int hl = min(max(lane, 2), kTileBlocks);
+        int n = 0;
+        for (int i = 0; i < G; ++i) {
+            const int rows = rows_of(i);
+            n += rows > kSmallRows ? (((rows + 31) >> 5) + hl - 1) / hl : 0;
+        }
+        const uint64_t fits = __ballot(lane >= 2 && lane <= kTileBlocks && n * plan.nt_large <= room);
+        h = __ffsll((unsigned long long)fits) - 1;
+    }
+    // row tiles of each class (large, small above kSmallRowsDown rows, small),
+    // then every group's first row and first row tile
+    auto tiles_of = [&](int rows) { return rows > kSmallRows ? (((rows + 31) >> 5) + h - 1) / h : rows > 0 ? 1 : 0; };
+    auto class_of = [](int rows) { return rows > kSmallRows ? 0 : rows > kSmallRowsDown ? 1 : 2; };
+    int n_large = 0, n_mid = 0, n_all = 0;
+    for (int c0 = 0; c0 < G; c0 += 64) {
+        const int rows = rows_of(c0 + lane), m = tiles_of(rows);
+        int t;
+        wave_excl_scan(class_of(rows) == 0 ? m : 0, lane, t);
+        n_large += t;
+        n_mid += __popcll(__ballot(m > 0 && class_of(rows) == 1));
+        n_all += t + __popcll(__ballot(m > 0 && class_of(rows) != 0));
+    }
+    int c_row = 0, c_large = 0, c_mid = n_large, c_small = n_large + n_mid;
+    int4 *rt = (int4 *)s.rt;
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    for (int c0 = 0; c0 < G; c0 += 64) {
+        const int i = c0 + lane, rows = rows_of(i), m = tiles_of(rows), c = class_of(rows);
+        int t_row, t_large;
+        const int p_row = wave_excl_scan(i < E_loc ? rows : 0, lane, t_row);
+        const int p_large = wave_excl_scan(c == 0 ? m : 0, lane, t_large);
+        const uint64_t mid = __ballot(m > 0 && c == 1), small = __ballot(m > 0 && c == 2);
+        const int row0 = i < E_loc ? c_row + p_row : 0;
+        if (i < G) {
+            g.row0[i] = row0;
+            g.rows[i] = rows;
+        }
+        if (m > 0) {
+            const int at = c == 0 ? c_large + p_large : c == 1 ? c_mid + __popcll(mid & below)
+                                                               : c_small + __popcll(small & below);
+            const int nb = (rows + 31) >> 5, q = nb / m, r = nb - q * m;
 #pragma unroll
-    for (int k = kTileBlocks - 1; k >= 2; --k)
-        if (l.fit[k] + l.small_items / 3 <= plan.grid) h = k;
-    for (int i = tid; i < G; i += kDispatchThreads) {
-        const int rows = i < E_loc ? tot[i] : T;
-        const int c = rows > kSmallRows ? 0 : rows > kSmallRowsDown ? 1 : 2;
-        const int m = c == 0 ? (((rows + 31) >> 5) + h - 1) / h : rows > 0 ? 1 : 0;
-        l.tiles[i] = c << 24 | m;
-        if (m) atomicAdd(&l.cls[c], m);
-    }
-    __syncthreads();
-    const int base1 = l.cls[0], base2 = base1 + l.cls[1], n = base2 + l.cls[2];
-    for (int i = tid; i < G; i += kDispatchThreads) {
-        const int rows = i < E_loc ? tot[i] : T;
-        const int c = l.tiles[i] >> 24, m = l.tiles[i] & 0xffffff;
-        int at = c == 0 ? 0 : c == 1 ? base1 : base2;
-        for (int j = 0; j < i; ++j) {
-            const int e = l.tiles[j];
-            at += (e >> 24) == c ? e & 0xffffff : 0;
+            for (int k = 0; k < 4; ++k) {
+                const int first = 32 * (k * q + min(k, r));
+                if (k < m)
+                    rt[at + k] = make_int4(i | (m == 1 ? 1 << 30 : 0), row0 + first,
+                                           min(32 * (q + (k < r ? 1 : 0)), rows - first) | m << 9, at);
+            }
         }
-        if (!m) continue;
-        const int nb = (rows + 31) >> 5, q = nb / m, r = nb - q * m;
-        int4 *rt = (int4 *)s.rt;
-        int done = 0;                   // rows placed so far
-        for (int k = 0; k < m; ++k) {
-            const int n_rows = min(32 * (q + (k < r ? 1 : 0)), rows - done);
-            rt[at + k] = make_int4(i | (m == 1 ? 1 << 30 : 0), l.row0[i] + done, n_rows | m << 9, at);
-            done += n_rows;
+        // the further row tiles of groups of more than four: the wave together
+        for (uint64_t todo = __ballot(m > 4); todo; todo &= todo - 1) {
+            const int v = __ffsll((unsigned long long)todo) - 1;
+            const int vr = __builtin_amdgcn_readlane(rows, v), vm = __builtin_amdgcn_readlane(m, v);
+            const int v0 = __builtin_amdgcn_readlane(row0, v);
+            const int va = c_large + __builtin_amdgcn_readlane(p_large, v);
+            const int nb = (vr + 31) >> 5, q = nb / vm, r = nb - q * vm;
+            for (int k = 4 + lane; k < vm; k += 64) {
+                const int first = 32 * (k * q + min(k, r));
+                rt[va + k] = make_int4(c0 + v, v0 + first,
+                                       min(32 * (q + (k < r ? 1 : 0)), vr - first) | vm << 9, va);
+            }
         }
+        c_row += t_row;
+        c_large += t_large;
+        c_mid += __popcll(mid);
+        c_small += __popcll(small);
     }
-    for (int i = tid; i < n; i += kDispatchThreads) s.dep[i] = 0;
-    if (tid == 0) {
-        s.hdr[0] = n;
-        s.hdr[1] = base1;
-        s.hdr[2] = base2;
+    for (int i = lane; i < n_all; i += 64) s.dep[i] = 0;
+    if (lane == 0) {
+        s.hdr[0] = n_all;
+        s.hdr[1] = n_large;
+        s.hdr[2] = n_large + n_mid;
     }
 }
 
@@ -261,11 +290,24 @@ void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, 
         const int tpe = E_loc < kDispatchThreads ? kDispatchThreads / E_loc : 1;
         const int i = tid / tpe, sub = tid - i * tpe;
         if (i < E_loc) {
-            int t = 0, p = 0;
-            for (int bb = sub; bb < nb_hist; bb += tpe) {
+            // eight loads in flight: a thread's rows are tpe apart
+            int t = 0, p = 0, bb = sub;
+            for (; bb + 3 * tpe < nb_hist; bb += 8 * tpe) {
+                int c[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    c[u] = blk_counts[(int64_t)min(bb + u * tpe, nb_hist - 1) * E + e0 + i];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int r = bb + u * tpe;
+                    t += r < nb_hist ? c[u] : 0;
+                    p += r < min(nb_hist, b) ? c[u] : 0;
+                }
+            }
+            for (; bb < nb_hist; bb += tpe) {
                 const int c = blk_counts[(int64_t)bb * E + e0 + i];
                 t += c;
-                if (bb < b) p += c;
+                p += bb < b ? c : 0;
             }
             atomicAdd(&tot[i], t);
             atomicAdd(&pre[i], p);
@@ -292,6 +334,13 @@ void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, 
     __syncthreads();
     for (int q = tid; q < n_my; q += kDispatchThreads) counts[b + q * (int)gridDim.x] = cnt_my[q];
 
+    // the last workgroup owns no slots (the launch adds it for this): it
+    // builds the FFN's row tiles while the others place their slots
+    if (b == (int)gridDim.x - 1 && b > 0) {
+        if (g.rows) build_schedule(g, sched, plan, tot, E_loc, has_shared, T);
+        return;
+    }
+
     // offsets (E_loc <= 256: one local expert per thread) and wave bases
     int total = 0;
     const int off_i = block_excl_scan(tid < E_loc ? tot[tid] : 0, wsum, total);
@@ -310,35 +359,36 @@ void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, 
     }
     __syncthreads();
 
+    // Lanes of a step that hold the same expert find each other by one ballot
+    // for each bit of the local index (a loop over the step's distinct experts
+    // took a round trip through LDS for each of them), and rank by lane order.
     volatile int32_t *mybase = wbase[wave];
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int bits = 32 - __clz(E_loc - 1 | 1);
 #pragma unroll
     for (int j = 0; j < kSteps; ++j) {
         const int64_t sl = wstart + j * 64;
         const int i = li[j];
-        const bool loc = i >= 0;
-        uint64_t pending = __ballot(loc);
+        uint64_t peers = __ballot(i >= 0);
+        for (int t = 0; t < bits; ++t) {
+            const bool one = i >> t & 1;
+            const uint64_t m = __ballot(one);
+            peers &= one ? m : ~m;
+        }
         int pos = -1;
-        while (pending) {
-            const int leader = __ffsll((unsigned long long)pending) - 1;
-            const int il = __shfl(i, leader);
-            const uint64_t m = __ballot(loc && i == il);
-            const int bse = mybase[il];
-            if (loc && i == il) pos = bse + __popcll(m & lt_mask);
-            if (lane == leader) mybase[il] = bse + __popcll(m);
-            pending &= ~m;
+        if (i >= 0) {
+            const int bse = mybase[i];
+            const int rank = __popcll(peers & lt_mask);
+            pos = bse + rank;
+            if (rank == 0) mybase[i] = bse + __popcll(peers);
         }
         if (sl < n_slots) {
             row_of_slot[sl] = pos;
             if (pos >= 0) slot_of_row[pos] = (int32_t)sl;
         }
     }
-    // the last workgroup owns no slots (the launch adds it for this): it
-    // builds the FFN's row tiles while the others place their slots
-    if (b == (int)gridDim.x - 1 && g.rows) {
-        __shared__ SchedBuildLds sb;
-        build_schedule(g, sched, plan, tot, E_loc, has_shared, T, sb);
-    }
+    // without slots there is one workgroup only
+    if (gridDim.x == 1 && g.rows) build_schedule(g, sched, plan, tot, E_loc, has_shared, T);
 }
 
 // Row tiles for pre-grouped rows (the receive region of section 3.2.1 in
@@ -351,7 +401,6 @@ void k_group_tables_from_counts(const int32_t *__restrict__ counts, int32_t E_lo
                                 int32_t *__restrict__ err)
 {
     __shared__ int32_t tot[kMaxLocalExperts];
-    __shared__ SchedBuildLds sb;
     const int lane = threadIdx.x;
     if (lane < 64) {
         int carry = 0, bad = 0;
@@ -371,7 +420,7 @@ void k_group_tables_from_counts(const int32_t *__restrict__ counts, int32_t E_lo
         if (__any(bad) && lane == 0) atomicOr(err, kErrBadCount);
     }
     __syncthreads();
-    build_schedule(g, sched, plan, tot, E_loc, 0, 0, sb);
+    build_schedule(g, sched, plan, tot, E_loc, 0, 0);
 }
 
 hipError_t launch_group_tables_from_counts(const int32_t *counts, int32_t E_loc,

@@ -482,17 +482,28 @@ __device__ __forceinline__ void small_fill(const SmallTile &t, const Lds &l, con
     __builtin_amdgcn_sched_barrier(0);
 }
 
+constexpr int kHStrideS = 64 + 8;         // staged h row of a small tile: 64 columns, padded
+
+// The staged h of row blocks 2 r and 2 r + 1 to memory: 64 rows x 128 bytes,
+// one 16-byte store of every thread.
+__device__ __forceinline__ void small_store_h(const SmallWave &w, const Out &o, int n0, const bf16 *hst, int r)
+{
+    if (!o.swiglu) return;
+    const int t = w.wave * 64 + w.lane, row = t >> 3, c = t & 7;
+    h_store(*(const u32x4 *)(hst + row * kHStrideS + c * 8), o, ((r * 64 + row) * o.ld + n0 / 2 + c * 8) * 2);
+}
+
 // Sum of the K quarters and output of row blocks 2 R and 2 R + 1: every wave
 // puts its partials (4 KB a block) into stage c = 2 (mb % 2) + column block,
 // and wave (c, ch) sums the four quarters in order and writes the block.  All
 // waves run the same instructions: a workgroup often runs one small tile of a
 // launch, and then each line of this code is fetched from HBM.
-constexpr int kHStrideS = 64 + 8;         // staged h row of a small tile: 64 columns, padded
 template <int NMB, int R>
 __device__ __forceinline__ void small_round(const Lds &l, const SmallWave &w, const f32x16 (&acc)[NMB][2],
                                             const Out &o, int n0, bf16 *hst)
 {
-    __syncthreads();                       // the stages are free
+    __syncthreads();                       // the stages are free, the last round's h is staged
+    if constexpr (R > 0) small_store_h(w, o, n0, hst, R - 1);
     const int part = w.ch * 4 + w.kq;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -526,12 +537,6 @@ __device__ __forceinline__ void small_round(const Lds &l, const SmallWave &w, co
         else
             y_block(v, o, R * 64 + tok, n0 + w.ch * 64 + (w.kq & 1) * 32, true);
     }
-    if (o.swiglu) {
-        __syncthreads();
-        // 64 rows x 128 bytes: one 16-byte store of every thread
-        const int t = w.wave * 64 + w.lane, r = t >> 3, c = t & 7;
-        h_store(*(const u32x4 *)(hst + r * kHStrideS + c * 8), o, ((R * 64 + r) * o.ld + n0 / 2 + c * 8) * 2);
-    }
 }
 
 template <int NMB>
@@ -541,6 +546,8 @@ __device__ __forceinline__ void small_finish(const Lds &l, const SmallWave &w, c
     small_round<NMB, 0>(l, w, acc, o, n0, hst);
     if constexpr (NMB > 2) small_round<NMB, 1>(l, w, acc, o, n0, hst);
     if constexpr (NMB > 4) small_round<NMB, 2>(l, w, acc, o, n0, hst);
+    __syncthreads();
+    small_store_h(w, o, n0, hst, (NMB - 1) / 2);
 }
 
 // One tile with NMB 32-row blocks: K loop, sum of the K quarters and
