@@ -23,13 +23,14 @@ constexpr int kMaxLayers = 1024;
 constexpr int kMaxIngestWords = 4096;            // ready words one ingest wait may poll
 constexpr uint32_t kDefaultIngestSpins = 1u << 19;   // about a second of polling
 
-// Grouped GEMM tile: 256 x 256 output, K step 64 bf16 (or 128 e4m3) = 128 B
-// per row.
-constexpr int kBM = 256;
-constexpr int kBN = 256;
 // bf16 large tiles: 32-row blocks of each half of a tile.
 constexpr int kHalfBlocks = 5;
 constexpr int kTileBlocks = 2 * kHalfBlocks;
+constexpr int kBandBf16 = 4;          // row tiles of a raster band
+// fp8 tiles: up to 128 rows.
+constexpr int kTileBlocksFp8 = 4;
+constexpr int kMinBlocksFp8 = 1;
+constexpr int kBandFp8 = 8;
 
 // Cache-policy operand of the raw buffer loads: non-temporal (streaming)
 // data, read once, evicted first and kept out of the last-level cache.

@@ -101,7 +101,7 @@ __device__ __forceinline__ int wave_sum(int v)
 // expert's token count (tot), or T for the shared expert.
 //
 // A large group is split evenly into as few row tiles of at most h 32-row
-// blocks as hold its rows.  h is kTileBlocks, the size that does the most
+// blocks as hold its rows.  h is the largest height, which does the most
 // work per weight read, unless the gate/up product then leaves workgroups
 // without an item: the pass would last as long as its largest tile, so h is
 // the smallest for which the items still fit in one round (a small item
@@ -128,28 +128,28 @@ __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedP
     bool any_large = false;
     for (int c0 = 0; c0 < G; c0 += 64) {
         const int rows = rows_of(c0 + lane);
-        n_small += __popcll(__ballot(rows > 0 && rows <= kSmallRows));
-        any_large |= __ballot(rows > kSmallRows) != 0;
-        n10 += rows > kSmallRows ? (((rows + 31) >> 5) + kTileBlocks - 1) / kTileBlocks : 0;
+        n_small += __popcll(__ballot(rows > 0 && rows <= plan.small_rows));
+        any_large |= __ballot(rows > plan.small_rows) != 0;
+        n10 += rows > plan.small_rows ? (((rows + 31) >> 5) + plan.max_blocks - 1) / plan.max_blocks : 0;
     }
     const int room = plan.grid - n_small * plan.nt_small / 3;
-    int h = kTileBlocks;
+    int h = plan.max_blocks;
     if (any_large && wave_sum(n10) * plan.nt_large <= room) {
         // lane h: the items with tiles of h blocks (few groups: each makes one
         // row tile at least)
-        const int hl = min(max(lane, 2), kTileBlocks);
+        const int hl = min(max(lane, plan.min_blocks), plan.max_blocks);
         int n = 0;
         for (int i = 0; i < G; ++i) {
             const int rows = rows_of(i);
-            n += rows > kSmallRows ? (((rows + 31) >> 5) + hl - 1) / hl : 0;
+            n += rows > plan.small_rows ? (((rows + 31) >> 5) + hl - 1) / hl : 0;
         }
-        const uint64_t fits = __ballot(lane >= 2 && lane <= kTileBlocks && n * plan.nt_large <= room);
+        const uint64_t fits = __ballot(lane >= plan.min_blocks && lane <= plan.max_blocks && n * plan.nt_large <= room);
         h = __ffsll((unsigned long long)fits) - 1;
     }
-    // row tiles of each class (large, small above kSmallRowsDown rows, small),
+    // row tiles of each class (large, small above plan.small_rows_down rows, small),
     // then every group's first row and first row tile
-    auto tiles_of = [&](int rows) { return rows > kSmallRows ? (((rows + 31) >> 5) + h - 1) / h : rows > 0 ? 1 : 0; };
-    auto class_of = [](int rows) { return rows > kSmallRows ? 0 : rows > kSmallRowsDown ? 1 : 2; };
+    auto tiles_of = [&](int rows) { return rows > plan.small_rows ? (((rows + 31) >> 5) + h - 1) / h : rows > 0 ? 1 : 0; };
+    auto class_of = [&](int rows) { return rows > plan.small_rows ? 0 : rows > plan.small_rows_down ? 1 : 2; };
     int n_large = 0, n_mid = 0, n_all = 0;
     for (int c0 = 0; c0 < G; c0 += 64) {
         const int rows = rows_of(c0 + lane), m = tiles_of(rows);

@@ -705,19 +705,6 @@ __device__ __forceinline__ void run_tall(const SmallTile &t, const Lds &l, const
 
 }  // namespace
 
-// The kernel's arguments, read where they are used: kept in registers over a
-// tile's loop they would be spilled.
-typedef const __attribute__((address_space(4))) FfnArgs *KernArgs;
-__device__ __forceinline__ KernArgs kernel_args()
-{
-    return (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
-}
-__device__ __forceinline__ KernArgs reload(KernArgs p)
-{
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
 template <bool LARGE>
 __global__ __launch_bounds__(kThreads, 1)
 void k_ffn_bf16(FfnArgs)

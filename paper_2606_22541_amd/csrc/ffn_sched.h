@@ -6,7 +6,7 @@
 // has m row tiles from `first` on): the large groups' tiles, group by group,
 // then the small groups'.
 // An item of a product is (row tile, column tile); items are numbered group
-// by group, within a large group in bands of kBandM row tiles (row tiles
+// by group, within a large group in bands of a few row tiles (row tiles
 // fastest, so that one band's weight panels and token rows are shared in an
 // L2).
 //
@@ -33,7 +33,6 @@
 namespace moe {
 
 constexpr int kMaxSchedCus = 512;     // workgroups of one launch
-constexpr int kBandM = 4;             // row tiles per raster band
 constexpr int kTickStride = 32;       // ints between ticket counters (128 bytes)
 constexpr int kListsLog2 = 3;
 constexpr int kLists = 1 << kListsLog2;
@@ -57,7 +56,7 @@ constexpr int kSchedTicks = 2 * kLists * kTickStride;
 // Row tiles that G groups with `rows` rows in all can make.
 __host__ __device__ inline int64_t sched_max_tiles(int64_t rows, int64_t G)
 {
-    return rows / kBM + G + kMaxSchedCus;
+    return rows / 128 + G + kMaxSchedCus;
 }
 // Ints of a schedule, and its arrays in one allocation.
 inline int64_t sched_ints(int64_t max_tiles)
@@ -88,7 +87,7 @@ struct SchedLds {
     int32_t hdr[4];
     int32_t item, wait;
     int32_t stage;     // thread 0: list being drained (0 gate/up, 1 down, 2 the others')
-    uint64_t w[2];     // weights of the two products
+    uint64_t w[2], ws[2];   // weights of the two products, and their scales
 };
 
 __device__ __forceinline__ int agent_load(const int32_t *p)
@@ -108,6 +107,7 @@ __device__ __forceinline__ int agent_swap(int32_t *p, int v)
 struct FfnTiles {
     int32_t ntl[2];    // of a large row tile (256 columns)
     int32_t nts[2];    // of a small row tile (128 columns)
+    int32_t band;      // row tiles of a raster band
 };
 
 typedef const __attribute__((address_space(4))) FfnTiles ArgTiles;
@@ -117,11 +117,11 @@ struct Items {
     int lg, C, x;              // log2 of the lists, workgroups per list, this workgroup's list
     int C1;                    // run length of the down product's items
     int nrt, nl0, nl1;         // row tiles, large ones of gate/up and of down
-    int ntl0, ntl1, nts0, nts1;
+    int ntl0, ntl1, nts0, nts1, band;
     int total0, total1;
 
     template <bool LARGE>
-    __device__ __forceinline__ void load(const SchedLds &l, int phases, int a0, int a1, int b0, int b1)
+    __device__ __forceinline__ void load(const SchedLds &l, int phases, ArgTiles &ct)
     {
         const int P = gridDim.x;
         lg = (P & (kLists - 1)) ? 0 : kListsLog2;
@@ -130,10 +130,11 @@ struct Items {
         nrt = __builtin_amdgcn_readfirstlane(l.hdr[0]);
         nl0 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[1]) : 0;
         nl1 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[2]) : 0;
-        ntl0 = a0;
-        ntl1 = a1;
-        nts0 = b0;
-        nts1 = b1;
+        ntl0 = ct.ntl[0];
+        ntl1 = ct.ntl[1];
+        nts0 = ct.nts[0];
+        nts1 = ct.nts[1];
+        band = ct.band;
         const int g = nl0 * ntl0 + (nrt - nl0) * nts0, d = nl1 * ntl1 + (nrt - nl1) * nts1;
         total0 = (phases & 1) ? g : 0;
         total1 = (phases & 2) ? d : 0;
@@ -180,7 +181,7 @@ struct Worker {
         else if (tid == 128) l.item = (phases & 1) ? agent_swap(&s.claim[b], 1) : 1;
         __syncthreads();
         Items q;
-        q.load<LARGE>(l, phases, ct.ntl[0], ct.ntl[1], ct.nts[0], ct.nts[1]);
+        q.load<LARGE>(l, phases, ct);
         all_done = false;
         pending = -1;
         pre = -1;
@@ -323,14 +324,14 @@ struct Worker {
             const int4 e = entry(s, l, r0);
             const int rt0 = e.w, m = e.z >> 9;
             const int i = it - rt0 * wl;
-            if (m <= kBandM) {
+            if (m <= q.band) {
                 nt = i / m;
                 rt = rt0 + i - nt * m;
             } else {
-                const int band = i / (kBandM * wl), r = i - band * kBandM * wl;
-                const int bm = min(kBandM, m - band * kBandM);
+                const int b = i / (q.band * wl), r = i - b * q.band * wl;
+                const int bm = min(q.band, m - b * q.band);
                 nt = r / bm;
-                rt = rt0 + band * kBandM + r - nt * bm;
+                rt = rt0 + b * q.band + r - nt * bm;
             }
         } else {
             const int i = it - nl * wl;
@@ -352,7 +353,7 @@ struct Worker {
     __device__ __forceinline__ bool next(ArgSched &s, SchedLds &l, int phases, ArgTiles &ct, int32_t *err)
     {
         Items q;
-        q.load<LARGE>(l, phases, ct.ntl[0], ct.ntl[1], ct.nts[0], ct.nts[1]);
+        q.load<LARGE>(l, phases, ct);
         int it = pending;
         if (first >= 0) {
             it = first;

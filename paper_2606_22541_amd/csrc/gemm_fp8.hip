@@ -58,6 +58,7 @@
 //    the quotient is taken as a product with the scale's reciprocal), four
 //    codes per lane and store.  The down product writes bf16, four
 //    consecutive features per lane.
+#include "ffn_sched.h"
 #include "kernels.h"
 
 namespace moe {
@@ -72,9 +73,15 @@ constexpr int kXBytes = kTokT * kGrpB;       // token rows of one stage: 16 KB
 constexpr int kXSBytes = kXBytes + kTokT * 4; // ... followed by the step's 128 token scales
 constexpr int kWaves8 = 8;
 constexpr int kThreads8 = 64 * kWaves8;
-constexpr int kBand8 = 8;                    // token tiles per raster band
+constexpr int kHStride8 = 128 + 16;          // staged h codes: a row of 128, padded
+constexpr int kAgentScope8 = 16;             // sc1: past this XCD's L2
+static_assert(kTokT == 32 * kTileBlocksFp8, "row tiles of the schedule");
+static_assert(kTokT * kHStride8 <= kWBytes, "the staged codes fit one stage's weights");
 constexpr int kFillLoads = 7;                // loads per wave per group fill
 typedef __attribute__((address_space(3))) void lds_void;
+
+// 16-byte chunks of LDS token row r are XOR-swizzled by this.
+__device__ __forceinline__ int x_swizzle(int r) { return (r >> 1) & 5; }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc8(const void *base, int64_t bytes)
 {
@@ -125,7 +132,8 @@ __device__ __forceinline__ void fill8_one(const Tile8 &t, const Ring8 &st, int w
                                                  16, t.vx[i - 4], ks * kGrpB, 0, 0);
     } else {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(t.rs, (lds_void *)(st.s + (wave & 1) * 64), 4,
-                                                 (ks * t.s_ld + (wave & 1) * 64 + lane) * 4, 0, 0, 0);
+                                                 (ks * t.s_ld + (wave & 1) * 64 + lane) * 4, 0, 0,
+                                                 kAgentScope8);
     }
 }
 
@@ -334,12 +342,10 @@ __device__ __forceinline__ void kloop8(const Tile8 &t, const Wave8 &w, const Rin
 
 }  // namespace
 
-// One launch covers every group: tile L is (group, 128-token tile, 256-feature
-// tile) in the band order above.
-template <bool SWIGLU>
 __global__ __launch_bounds__(kThreads8, 1)
-void k_gemm_fp8(GemmArgs a, int32_t lds_rows_routed, int32_t lds_rows_shared)
+void k_ffn_fp8(FfnArgs)
 {
+    KernArgs args = kernel_args();
     __shared__ __attribute__((aligned(1024))) uint8_t lds_w0[kWBytes];
     __shared__ __attribute__((aligned(1024))) uint8_t lds_w1[kWBytes];
     __shared__ __attribute__((aligned(1024))) uint8_t lds_w2[kWBytes];
@@ -349,118 +355,107 @@ void k_gemm_fp8(GemmArgs a, int32_t lds_rows_routed, int32_t lds_rows_shared)
     __shared__ __attribute__((aligned(1024))) uint8_t lds_x0[kXSBytes];
     __shared__ __attribute__((aligned(1024))) uint8_t lds_x1[kXSBytes];
     __shared__ __attribute__((aligned(1024))) uint8_t lds_x2[kXSBytes];
-    __shared__ int32_t ttab[kMaxLocalExperts + 2];    // prefix of 128-token tiles per group
     __shared__ float hmax[4][kTokT];                   // SwiGLU: |h| maximum per wave and token
+    __shared__ SchedLds sl;
     const Ring8 ring[3] = {{lds_w0, lds_x0, (float *)(lds_x0 + kXBytes)},
                            {lds_w1, lds_x1, (float *)(lds_x1 + kXBytes)},
                            {lds_w2, lds_x2, (float *)(lds_x2 + kXBytes)}};
 
-    const int tid = threadIdx.x;
-    Wave8 w;
-    w.lane = tid & 63;
-    w.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    w.wf = w.wave & 3;
-    w.wt = w.wave >> 2;
-    const int lane = w.lane;
-    const int N = a.N, K = a.K;
-    const int NT = (N + kFeatT - 1) / kFeatT;
-    const int G = a.G;
-
-    // 128-token tiles per group, prefix over the groups (one wave)
-    if (w.wave == 0) {
-        int carry = 0;
-        for (int c0 = 0; c0 < G; c0 += 64) {
-            const int i = c0 + lane;
-            const int m = i < G ? (a.groups.rows[i] + kTokT - 1) / kTokT : 0;
-            int x = m;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int y = __shfl_up(x, o);
-                if (lane >= o) x += y;
+    int tid = threadIdx.x;
+    Worker<true> wk;
+    if (tid == 192) {                     // the layer's weights, while begin() loads
+        const void *W1 = args->p1.W, *W2 = args->p2.W;
+        const float *S1 = args->p1.Ws, *S2 = args->p2.Ws;
+        if (args->layer_id) {
+            int ly = *args->layer_id;
+            if (ly < 0 || ly >= args->n_layers) {
+                if (blockIdx.x == 0 && args->sched.hdr[0] > 0) atomicOr(args->err, kErrBadLayer);
+                ly = ly < 0 ? 0 : args->n_layers - 1;
             }
-            if (i < G) ttab[i] = carry + x - m;
-            carry += __shfl(x, 63);
+            W1 = args->layers[ly].w1;
+            W2 = args->layers[ly].w2;
+            S1 = args->layers[ly].s1;
+            S2 = args->layers[ly].s2;
         }
-        if (lane == 0) ttab[G] = carry;
+        sl.w[0] = (uint64_t)W1;
+        sl.w[1] = (uint64_t)W2;
+        sl.ws[0] = (uint64_t)S1;
+        sl.ws[1] = (uint64_t)S2;
     }
-    __syncthreads();
-    const int total = __builtin_amdgcn_readfirstlane(ttab[G] * NT);
-    const int P = gridDim.x;
-    const int first = (P & 7) ? (int)blockIdx.x : (int)((blockIdx.x & 7) * (P >> 3) + (blockIdx.x >> 3));
-    if (first >= total) return;      // no tile: leave before resolving the weights
-    const void *Bw;
-    const float *Bsw;
-    resolve_weights(a, Bw, Bsw);
+    if (!wk.begin(args->sched, sl, args->phases, args->tiles)) return;
 
-    // MFMA operand reads.  Weight fragment rb of this wave: feature block
-    // 4 wf + rb, lane-contiguous halves.  Token block cb: lane l takes token
-    // 64 wt + 16 cb + l % 16 and the 32 bytes [32 (l / 16), + 32) of its row.
-    {
-        const int r = w.wt * 64 + (lane & 15), swz = (r >> 1) & 7, c0 = 2 * (lane >> 4);
-        w.w_rd = w.wf * 4 * 2048 + lane * 16;
-        w.x_rd0 = r * kGrpB + ((c0 ^ swz) << 4);
-        w.x_rd1 = r * kGrpB + (((c0 + 1) ^ swz) << 4);
-        w.s_rd = r;
-    }
-    // token fills: lane l covers row 16 w + 8 i + l / 8, physical chunk l % 8;
-    // ((row / 2) % 8) = (4 i + l / 16) % 8 since 16 w / 2 is a multiple of 8
-    const int frow = w.wave * 16 + (lane >> 3);
-    const int fch[2] = {((lane & 7) ^ ((lane >> 4) & 7)) << 4,
-                        ((lane & 7) ^ ((4 + (lane >> 4)) & 7)) << 4};
-
-    for (int L = first; L < total; L += P) {
-        // decode: group g (largest with ttab[g] * NT <= L), then bands of up
-        // to kBand8 token tiles, token tiles fastest
-        int lo = 0, hi = G;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (ttab[mid] * NT <= L) lo = mid; else hi = mid;
+    for (;;) {
+        args = reload(args);
+        if (!wk.next(args->sched, sl, args->phases, args->tiles, args->err)) break;
+        args = reload(args);
+        // nothing that a lane derives from its number is kept over the items
+        asm volatile("" : "+v"(tid));
+        Wave8 w;
+        w.lane = tid & 63;
+        w.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        w.wf = w.wave & 3;
+        w.wt = w.wave >> 2;
+        const int lane = w.lane;
+        // MFMA operand reads.  Weight fragment rb of this wave: feature block
+        // 4 wf + rb, lane-contiguous halves.  Token block cb: lane l takes token
+        // 64 wt + 16 cb + l % 16 and the 32 bytes [32 (l / 16), + 32) of its row.
+        {
+            const int r = w.wt * 64 + (lane & 15), swz = x_swizzle(r), c0 = 2 * (lane >> 4);
+            w.w_rd = w.wf * 4 * 2048 + lane * 16;
+            w.x_rd0 = r * kGrpB + ((c0 ^ swz) << 4);
+            w.x_rd1 = r * kGrpB + (((c0 + 1) ^ swz) << 4);
+            w.s_rd = r;
         }
-        const int g = __builtin_amdgcn_readfirstlane(lo);
-        const int Lg = L - ttab[g] * NT;
-        const int Mt = ttab[g + 1] - ttab[g];
-        const int band = Lg / (kBand8 * NT);
-        const int rr = Lg - band * kBand8 * NT;
-        const int bm = min(kBand8, Mt - band * kBand8);
-        const int mt = __builtin_amdgcn_readfirstlane(band * kBand8 + rr % bm);
-        const int nt = __builtin_amdgcn_readfirstlane(rr / bm);
-        const int grows = __builtin_amdgcn_readfirstlane(a.groups.rows[g]);
-        const int row0 = __builtin_amdgcn_readfirstlane(a.groups.row0[g]) + mt * kTokT;
-        const int rows_valid = min(kTokT, grows - mt * kTokT);
+        const bool down = wk.down;
+        const RowTile rt = wk.row_tile(args->sched, sl);
+        const bool sh = rt.group == args->shared_group;
+        const int N = down ? args->p2.N : args->p1.N, K = down ? args->p2.K : args->p1.K;
+        const void *Ar = down ? args->p2.A_routed : args->p1.A_routed;
+        const void *Ash = down ? args->p2.A_shared : args->p1.A_shared;
+        const float *Sr = down ? args->p2.As_routed : args->p1.As_routed;
+        const float *Ssh = down ? args->p2.As_shared : args->p1.As_shared;
+        const int rows_valid = rt.rows, row0 = rt.row0, nt = wk.nt;
         const int n0 = nt * kFeatT;
-        const bool sh = (g == a.shared_group);
         // routed rows of an indexed A are gathered in the token fills: tile
         // row r is row A_index[row0 + r] / A_index_div of the whole A (its
         // scales are already gathered, indexed by the routed row)
-        const bool indexed = a.A_index != nullptr && !sh;
-        const uint8_t *A = indexed ? (const uint8_t *)a.A_routed
-                                   : (const uint8_t *)(sh ? a.A_shared : a.A_routed) + (int64_t)row0 * K;
-        const float *As = (sh ? a.As_shared : a.As_routed) + row0;      // [K/128][ld]
-        const uint8_t *B = (const uint8_t *)Bw + ((int64_t)g * N + n0) * K;
+        const int32_t *index = (!down && !sh) ? args->A_index : nullptr;
+        const uint8_t *A = index ? (const uint8_t *)Ar : (const uint8_t *)(sh ? Ash : Ar) + (int64_t)row0 * K;
+        const float *As = (sh ? Ssh : Sr) + row0;      // [K/128][ld]
+        const uint8_t *B = uniform_ptr((const uint8_t *)sl.w[down ? 1 : 0]) + ((int64_t)rt.group * N + n0) * K;
+        const float *Bsw = uniform_ptr((const float *)sl.ws[down ? 1 : 0]);
         Tile8 t;
         t.KT = K / kGrpB;
-        t.s_ld = sh ? lds_rows_shared : lds_rows_routed;
+        t.s_ld = sh ? args->lds_shared : args->lds_routed;
         t.ncb = min(kFeatT, N - n0) / 16;
         t.cbstride = t.KT * 2048;
         t.rw = rsrc8(B, (int64_t)t.ncb * t.cbstride);
-        t.rx = rsrc8(A, (indexed ? a.A_routed_rows : (int64_t)rows_valid) * K);
+        t.rx = rsrc8(A, (index ? args->A_routed_rows : (int64_t)rows_valid) * K);
         t.rs = rsrc8(As, ((int64_t)(t.KT - 1) * t.s_ld + rows_valid) * 4);
+        {
+            // token fills: lane l covers row 16 w + 8 i + l / 8, physical chunk l % 8
+            int src[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = frow + 8 * i;
-            t.vx[i] = r < rows_valid ? (indexed ? a.A_index[row0 + r] / a.A_index_div : r) * K + fch[i]
-                                     : (int)0x80000000u;
+            for (int i = 0; i < 2; ++i) {
+                const int r = min(w.wave * 16 + 8 * i + (lane >> 3), rows_valid - 1);
+                src[i] = index ? index[row0 + r] / args->A_index_div : r;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = w.wave * 16 + 8 * i + (lane >> 3);
+                t.vx[i] = r < rows_valid ? src[i] * K + (((lane & 7) ^ x_swizzle(r)) << 4) : (int)0x80000000u;
+            }
         }
         const float *sbp0, *sbp1;
-        if constexpr (SWIGLU) {
+        if (!down) {
             // [G][f/128][gate, up][K/128]: tile nt covers gate/up scale block nt
             const int f = N / 2;
-            sbp0 = Bsw + ((int64_t)g * (f / 128) + nt) * 2 * t.KT;
+            sbp0 = Bsw + ((int64_t)rt.group * (f / 128) + nt) * 2 * t.KT;
             sbp1 = sbp0 + t.KT;
         } else {
             // [G][N/128][K/128]: wave features n0 + 64 wf .. + 63
             const int nb = min(2 * nt + (w.wf >> 1), N / 128 - 1);
-            sbp0 = sbp1 = Bsw + ((int64_t)g * (N / 128) + nb) * t.KT;
+            sbp0 = sbp1 = Bsw + ((int64_t)rt.group * (N / 128) + nb) * t.KT;
         }
         t.sbp0 = (const cfloat *)(uintptr_t)sbp0;
         t.sbp1 = (const cfloat *)(uintptr_t)sbp1;
@@ -493,18 +488,21 @@ void k_gemm_fp8(GemmArgs a, int32_t lds_rows_routed, int32_t lds_rows_shared)
         }
         __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0): the clamped look-ahead fills
         __syncthreads();                                     // ring idle in every wave
+        wk.request();
 
         // Accumulator register i of block (rb, cb) holds feature
         // 16 rb + 4 (lane / 16) + i of the wave and token 16 cb + lane % 16.
         const int tok = w.wt * 64 + (lane & 15);        // + 16 cb
         const int fq = 4 * (lane >> 4);                 // + 16 rb + i
-        if constexpr (SWIGLU) {
+        if (!down) {
             // Gate and up rows interleave by 16: blocks rb = 2 p and 2 p + 1 are
             // gate and up of h channels 32 wf + 16 p + 4 (lane / 16) + i of the
             // tile's 128, so every wave forms its own h.  A token's scale needs
             // |h| over all 128 channels: each wave reduces its 32 (lanes
             // l, l ^ 16, l ^ 32, l ^ 48 hold the same token), and the four
-            // waves of the same tokens meet in LDS.
+            // waves of the same tokens meet in LDS.  The codes are staged in the
+            // ring and leave as whole 128-byte lines, past this XCD's L2 (the
+            // down items that read them run on other XCDs in the same launch).
             const int f = N / 2;
             f32x4 h[2][4];
             float am[4];
@@ -524,26 +522,32 @@ void k_gemm_fp8(GemmArgs a, int32_t lds_rows_routed, int32_t lds_rows_shared)
                 if (lane < 16) hmax[w.wf][tok + 16 * cb] = am[cb];
             }
             __syncthreads();
-            uint8_t *H = (uint8_t *)(sh ? a.C_shared : a.C_routed);
-            float *Hs = (sh ? a.Cs_shared : a.Cs_routed) + (int64_t)nt * t.s_ld + row0;
+            float *Hs = (sh ? args->p1.Cs_shared : args->p1.Cs_routed) + (int64_t)nt * t.s_ld + row0;
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
                 const int tk = tok + 16 * cb;
                 const float amax = fmaxf(fmaxf(hmax[0][tk], hmax[1][tk]), fmaxf(hmax[2][tk], hmax[3][tk]));
                 const float sc = amax > 0.0f ? amax / 448.0f : 1.0f;   // the activation quantiser's scale
                 const float inv = __builtin_amdgcn_rcpf(sc);
-                if (tk < rows_valid) {
-                    uint8_t *dst = H + (int64_t)(row0 + tk) * f + nt * 128 + w.wf * 32 + fq;
+                uint8_t *dst = lds_w0 + tk * kHStride8 + w.wf * 32 + fq;
 #pragma unroll
-                    for (int pq = 0; pq < 2; ++pq)
-                        *(uint32_t *)(dst + 16 * pq) =
-                            e4m3_pack4(h[pq][cb][0] * inv, h[pq][cb][1] * inv,
-                                       h[pq][cb][2] * inv, h[pq][cb][3] * inv);
-                    if (w.wf == 0 && lane < 16) Hs[tk] = sc;
-                }
+                for (int pq = 0; pq < 2; ++pq)
+                    *(uint32_t *)(dst + 16 * pq) = e4m3_pack4(h[pq][cb][0] * inv, h[pq][cb][1] * inv,
+                                                              h[pq][cb][2] * inv, h[pq][cb][3] * inv);
+                if (w.wf == 0 && lane < 16 && tk < rows_valid)
+                    __hip_atomic_store(&Hs[tk], sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+            const auto rh = rsrc8((uint8_t *)(sh ? args->p1.C_shared : args->p1.C_routed) + (int64_t)row0 * f,
+                                  (int64_t)rows_valid * f);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = i * 64 + (tid >> 3), c = tid & 7;       // 16 bytes of a row's 128
+                const u32x4 v = *(const u32x4 *)(lds_w0 + r * kHStride8 + c * 16);
+                __builtin_amdgcn_raw_buffer_store_b128(v, rh, r * f + nt * 128 + c * 16, 0, kAgentScope8);
             }
         } else {
-            bf16 *C = (bf16 *)(sh ? a.C_shared : a.C_routed);
+            bf16 *C = (bf16 *)(sh ? args->p2.C_shared : args->p2.C_routed);
             const int fb = n0 + w.wf * 64 + fq;
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
@@ -562,26 +566,13 @@ void k_gemm_fp8(GemmArgs a, int32_t lds_rows_routed, int32_t lds_rows_shared)
                 }
             }
         }
+        wk.done(args->sched);
     }
 }
 
-hipError_t launch_gemm_fp8(const GemmArgs &a, bool swiglu, int mt_max, int g_max, int num_cus,
-                           int32_t lds_rows_routed, int32_t lds_rows_shared, hipStream_t s)
+hipError_t launch_ffn_fp8(const FfnArgs &a, int grid, hipStream_t s)
 {
-    (void)g_max;
-    if (mt_max <= 0) return hipSuccess;
-    if (a.K % 128 || a.N % 128 || (swiglu && a.N % 256)) return hipErrorNotSupported;
-    if (a.G < 1 || a.G > kMaxLocalExperts + 1) return hipErrorNotSupported;
-    // 128-token tiles: at most two per 256-row tile of the bound
-    const int64_t tiles = (int64_t)2 * mt_max * ((a.N + kFeatT - 1) / kFeatT);
-    int grid = num_cus < tiles ? num_cus : (int)tiles;
-    if (grid >= 8) grid &= ~7;
-    if (swiglu)
-        hipLaunchKernelGGL(k_gemm_fp8<true>, dim3(grid), dim3(kThreads8), 0, s, a,
-                           lds_rows_routed, lds_rows_shared);
-    else
-        hipLaunchKernelGGL(k_gemm_fp8<false>, dim3(grid), dim3(kThreads8), 0, s, a,
-                           lds_rows_routed, lds_rows_shared);
+    hipLaunchKernelGGL(k_ffn_fp8, dim3(grid), dim3(kThreads8), 0, s, a);
     return hipGetLastError();
 }
 

@@ -10,10 +10,14 @@
 namespace moe {
 
 // What the row-tile build knows of the launch that will run them: its
-// workgroups, and the column tiles of the gate/up product (of 256 and of 128
-// columns).
+// workgroups, the column tiles of the gate/up product (of 256 and of 128
+// columns), the row limits of small groups (in the gate/up and the down
+// product; 0: every group is large), and the smallest and largest height of a
+// large row tile in 32-row blocks.
 struct SchedPlan {
     int32_t grid, nt_large, nt_small;
+    int32_t small_rows, small_rows_down;
+    int32_t min_blocks, max_blocks;
 };
 
 struct DispatchArgs {
@@ -67,39 +71,6 @@ struct LayerWeights {
     const float *s1, *s2;     // fp8 block scales (null in bf16)
 };
 
-struct GemmArgs {
-    const void *A_routed;    // [rows][K] (rows of H, or pre-grouped rows), or x itself when A_index is set
-    const void *A_shared;    // [T][K] (x or H_shared) for group E_loc, if shared
-    const float *As_routed;  // fp8: [rows][K/128] scales of A
-    const float *As_shared;
-    const void *B;           // [G][N][K] weights (K contiguous)
-    const float *Bs;         // fp8: block scales
-    void *C_routed;          // [rows][ldc]
-    void *C_shared;
-    float *Cs_routed;        // fp8 SwiGLU epilogue: [rows][f/128] scales of H
-    float *Cs_shared;
-    int32_t N, K;
-    int32_t shared_group;    // index of the shared group, -1 if none
-    GroupTable groups;
-    int32_t G;
-    // When A_index is set, routed row r (r < the routed rows) is row
-    // A_index[r] / A_index_div of A_routed, which has A_routed_rows rows (the
-    // row gather happens in the GEMM's token-row loads; A_index = slot_of_row).
-    // In fp8 the A scales stay indexed by the routed row (As_routed holds the
-    // gathered scales, launch_gather_scales).
-    const int32_t *A_index;
-    int32_t A_index_div;
-    int64_t A_routed_rows;
-    // Layer-oblivious weights: with layer_id set, B and Bs are taken on the
-    // device from layers[*layer_id] (w1/s1, or w2/s2 when `down`); an id
-    // outside [0, n_layers) is clamped and flagged in err.
-    const int32_t *layer_id;
-    const LayerWeights *layers;
-    int32_t n_layers;
-    int32_t down;
-    int32_t *err;
-};
-
 // A pointer loaded from memory, made provably wave-uniform (the value is the
 // same in every lane), so that buffer descriptors built from it stay in
 // scalar registers instead of being re-established lane by lane at each load.
@@ -112,31 +83,14 @@ __device__ __forceinline__ T *uniform_ptr(T *p)
     return (T *)(((uint64_t)hi << 32) | lo);
 }
 
-// The weights a GEMM launch uses: a.B / a.Bs, or the ones of the layer named
-// in device memory (read once per workgroup; every wave gets the same value).
-// Workgroup 0 reports an id out of range; it calls this whenever the launch
-// has any tile (a launch without tiles reads no weights and checks nothing).
-__device__ __forceinline__ void resolve_weights(const GemmArgs &a, const void *&B, const float *&Bs)
-{
-    B = a.B;
-    Bs = a.Bs;
-    if (a.layer_id) {
-        int l = __builtin_amdgcn_readfirstlane(*a.layer_id);
-        if (l < 0 || l >= a.n_layers) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(a.err, kErrBadLayer);
-            l = l < 0 ? 0 : a.n_layers - 1;
-        }
-        const LayerWeights &lw = a.layers[l];
-        B = uniform_ptr(a.down ? lw.w2 : lw.w1);
-        Bs = uniform_ptr(a.down ? lw.s2 : lw.s1);
-    }
-}
-
 // One product of an FFN pass, as a work item sees it.
 struct FfnProduct {
     const void *A_routed, *A_shared;   // token rows (x or pre-grouped rows), or H; [rows][K]
     void *C_routed, *C_shared;         // H, or Y
     const void *W;                     // packed weights of layer 0, [G][N][K]
+    const float *Ws;                   // fp8: their block scales
+    const float *As_routed, *As_shared;   // fp8: scales of A, transposed, [K/128][lds_routed or lds_shared]
+    float *Cs_routed, *Cs_shared;      // fp8, gate/up: scales of H, transposed likewise
     int32_t N, K;
     int32_t ldc;                       // elements of an output row
 };
@@ -149,6 +103,7 @@ struct FfnArgs {
     const int32_t *A_index;
     int32_t A_index_div;
     int64_t A_routed_rows;
+    int32_t lds_routed, lds_shared;    // fp8: leading dimensions of the scales
     int32_t shared_group;              // index of the shared group, -1 if none
     int32_t phases;                    // 1: gate/up items, 2: down items, 3: both
     Sched sched;
@@ -162,6 +117,19 @@ struct FfnArgs {
     int32_t *err;
 };
 
+// An FFN kernel's arguments, read where they are used: kept in registers over a
+// tile's loop they would be spilled.
+typedef const __attribute__((address_space(4))) FfnArgs *KernArgs;
+__device__ __forceinline__ KernArgs kernel_args()
+{
+    return (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+}
+__device__ __forceinline__ KernArgs reload(KernArgs p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // bf16 expert FFN over the row tiles of a.sched (ffn_bf16.h).  rt_max bounds
 // the row tiles, grid is the workgroups the row tiles were planned for (at
 // most one per CU).  launch_ffn_bf16_small is for passes all of whose groups
@@ -169,14 +137,11 @@ struct FfnArgs {
 hipError_t launch_ffn_bf16(const FfnArgs &a, int grid, hipStream_t s);
 hipError_t launch_ffn_bf16_small(const FfnArgs &a, int grid, hipStream_t s);
 
-// e4m3 grouped GEMM with 128-block scales (same conventions; the A scales
-// are transposed, [K/128][ld] with ld = lds_rows_routed / lds_rows_shared).
-// swiglu = true writes e4m3 h with one scale per row and 128 channels
-// (C and Cs, the scales transposed like the A scales).  Every group runs
-// as 128-row tiles (mt_max bounds the 256-row tiles of all groups together;
-// g_max is unused).
-hipError_t launch_gemm_fp8(const GemmArgs &a, bool swiglu, int mt_max, int g_max, int num_cus,
-                           int32_t lds_rows_routed, int32_t lds_rows_shared, hipStream_t s);
+// e4m3 expert FFN with 128-block scales (gemm_fp8.hip).  The scales of A are
+// indexed by the routed row (As_routed holds the gathered scales,
+// launch_gather_scales); H is written as e4m3 codes with one scale per row
+// and 128 channels.
+hipError_t launch_ffn_fp8(const FfnArgs &a, int grid, hipStream_t s);
 
 struct CombineArgs {
     const void *y_perm;        // [rows][d] bf16

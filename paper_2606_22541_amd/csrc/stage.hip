@@ -450,7 +450,13 @@ static int ffn_grid(int cus)
 static SchedPlan sched_plan(const moe_stage *st, int cus)
 {
     const int n1 = 2 * st->desc.d_ff;
-    return SchedPlan{ffn_grid(cus), (n1 + 255) / 256, (n1 + 127) / 128};
+    SchedPlan p{ffn_grid(cus), (n1 + 255) / 256, (n1 + 127) / 128, kSmallRows, kSmallRowsDown, 2, kTileBlocks};
+    if (st->desc.dtype == MOE_DTYPE_FP8_E4M3_B128) {   // every group in the fp8 kernel's tiles
+        p.small_rows = p.small_rows_down = 0;
+        p.min_blocks = kMinBlocksFp8;
+        p.max_blocks = kTileBlocksFp8;
+    }
+    return p;
 }
 
 // The three phases.  `rec` records the slot's event at the end; a submit
@@ -517,8 +523,6 @@ struct FfnPass {
     void *y;                          // Y_perm, or the caller's y
     const int32_t *layer_id;
     int64_t max_group;                // no group has more rows than this
-    int64_t mt_max;                   // bound on the 256-row tiles of all groups
-    int32_t G;
 };
 
 // The two grouped GEMMs of one FFN pass on `s`: gate/up with the fused
@@ -530,106 +534,54 @@ static moe_status launch_ffn(moe_stage *st, SlotWs &sl, const FfnPass &f, bool a
 {
     const moe_stage_desc &d = st->desc;
     const bool fp8 = d.dtype == MOE_DTYPE_FP8_E4M3_B128;
-    const int mt = f.mt_max > 0x7fffffff ? 0x7fffffff : (int)f.mt_max;
     const int cus = stream_cus(st, s);
-    const int32_t shared_group = f.rows_shared ? d.n_local_experts : -1;
     hipError_t e = hipSuccess;
-    if (!fp8) {
-        if (!after_dispatch) {
-            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(s, &cs) != hipSuccess) (void)hipGetLastError();
-            sl.captured |= cs != hipStreamCaptureStatusNone;
-            if ((!sl.sched_fresh || sl.captured) && launch_reset_schedule(sl.sched, s) != hipSuccess)
-                return MOE_EHIP;
+    if (!after_dispatch) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cs) != hipSuccess) (void)hipGetLastError();
+        sl.captured |= cs != hipStreamCaptureStatusNone;
+        if ((!sl.sched_fresh || sl.captured) && launch_reset_schedule(sl.sched, s) != hipSuccess)
+            return MOE_EHIP;
+    }
+    sl.sched_fresh = false;
+    FfnArgs a{};
+    a.p1 = FfnProduct{f.rows, f.rows_shared, sl.h, sl.h_sh, st->w1, st->s1, sl.x_perm_s, sl.xsh_s,
+                      sl.h_s, sl.h_sh_s, 2 * d.d_ff, d.d_model, d.d_ff};
+    a.p2 = FfnProduct{sl.h, sl.h_sh, f.y, sl.y_sh, st->w2, st->s2, sl.h_s, sl.h_sh_s,
+                      nullptr, nullptr, d.d_model, d.d_ff, d.d_model};
+    a.A_index = f.index;
+    a.A_index_div = d.top_k;
+    a.A_routed_rows = f.n_rows;
+    a.lds_routed = (int32_t)st->sz.cap;
+    a.lds_shared = d.max_tokens;
+    a.shared_group = f.rows_shared ? d.n_local_experts : -1;
+    a.sched = sl.sched;
+    a.tiles = FfnTiles{{(2 * d.d_ff + 255) / 256, (d.d_model + 255) / 256},
+                       {(2 * d.d_ff + 127) / 128, (d.d_model + 127) / 128},
+                       fp8 ? kBandFp8 : kBandBf16};
+    a.layer_id = f.layer_id;           // weights named on the device (null: layer 0)
+    a.layers = st->layers;
+    a.n_layers = d.n_layers;
+    a.err = st->err;
+    const bool small = f.max_group <= kSmallRows;
+    const int grid = ffn_grid(cus);
+    auto run = [&](int phases) {
+        a.phases = phases;
+        return fp8 ? launch_ffn_fp8(a, grid, s)
+               : small ? launch_ffn_bf16_small(a, grid, s) : launch_ffn_bf16(a, grid, s);
+    };
+    if (st->prof_on) {                 // timed by product: one launch each
+        {
+            ProfScope ps(st, 2, s);
+            e = run(1);
         }
-        sl.sched_fresh = false;
-        FfnArgs a{};
-        a.p1 = FfnProduct{f.rows, f.rows_shared, sl.h, sl.h_sh, st->w1, 2 * d.d_ff, d.d_model, d.d_ff};
-        a.p2 = FfnProduct{sl.h, sl.h_sh, f.y, sl.y_sh, st->w2, d.d_model, d.d_ff, d.d_model};
-        a.A_index = f.index;
-        a.A_index_div = d.top_k;
-        a.A_routed_rows = f.n_rows;
-        a.shared_group = shared_group;
-        a.sched = sl.sched;
-        a.tiles = FfnTiles{{(2 * d.d_ff + 255) / 256, (d.d_model + 255) / 256},
-                           {(2 * d.d_ff + 127) / 128, (d.d_model + 127) / 128}};
-        a.layer_id = f.layer_id;       // weights named on the device (null: layer 0)
-        a.layers = st->layers;
-        a.n_layers = d.n_layers;
-        a.err = st->err;
-        const bool small = f.max_group <= kSmallRows;
-        const int grid = ffn_grid(cus);
-        auto run = [&](int phases) {
-            a.phases = phases;
-            return small ? launch_ffn_bf16_small(a, grid, s) : launch_ffn_bf16(a, grid, s);
-        };
-        if (st->prof_on) {             // timed by product: one launch each
-            {
-                ProfScope ps(st, 2, s);
-                e = run(1);
-            }
-            if (e == hipSuccess) {
-                ProfScope ps(st, 3, s);
-                e = run(2);
-            }
-        } else {
-            e = run(3);
+        if (e == hipSuccess) {
+            ProfScope ps(st, 3, s);
+            e = run(2);
         }
-        return e == hipSuccess ? MOE_OK : MOE_EHIP;
+    } else {
+        e = run(3);
     }
-
-    const int32_t cap = (int32_t)st->sz.cap, tmax = d.max_tokens;
-    GemmArgs g1{};
-    g1.A_routed = f.rows;
-    g1.A_shared = f.rows_shared;
-    g1.A_index = f.index;              // routed row r = token slot_of_row[r] / k of x
-    g1.A_index_div = d.top_k;
-    g1.A_routed_rows = f.n_rows;
-    g1.As_routed = sl.x_perm_s;
-    g1.As_shared = sl.xsh_s;
-    g1.B = st->w1;
-    g1.Bs = st->s1;
-    g1.C_routed = sl.h;                // e4m3 codes, with their scales in Cs
-    g1.C_shared = sl.h_sh;
-    g1.Cs_routed = sl.h_s;
-    g1.Cs_shared = sl.h_sh_s;
-    g1.N = 2 * d.d_ff;
-    g1.K = d.d_model;
-    g1.shared_group = shared_group;
-    g1.groups = sl.tables();
-    g1.G = f.G;
-    g1.layer_id = f.layer_id;
-    g1.layers = st->layers;
-    g1.n_layers = d.n_layers;
-    g1.down = 0;
-    g1.err = st->err;
-
-    GemmArgs g2 = g1;
-    g2.A_index = nullptr;              // H rows are already grouped by expert
-    g2.A_index_div = 0;
-    g2.A_routed_rows = 0;
-    g2.Cs_routed = nullptr;            // the down product writes bf16 Y
-    g2.Cs_shared = nullptr;
-    g2.A_routed = sl.h;
-    g2.A_shared = sl.h_sh;
-    g2.As_routed = sl.h_s;
-    g2.As_shared = sl.h_sh_s;
-    g2.B = st->w2;
-    g2.Bs = st->s2;
-    g2.down = 1;
-    g2.C_routed = f.y;
-    g2.C_shared = sl.y_sh;
-    g2.N = d.d_model;
-    g2.K = d.d_ff;
-    {
-        ProfScope ps(st, 2, s);
-        e = launch_gemm_fp8(g1, true, mt, f.G, cus, cap, tmax, s);
-    }
-    if (e == hipSuccess) {
-        ProfScope ps(st, 3, s);
-        e = launch_gemm_fp8(g2, false, mt, f.G, cus, cap, tmax, s);
-    }
-    if (e == hipErrorNotSupported) return MOE_EUNSUPPORTED;
     return e == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 
@@ -650,9 +602,6 @@ static moe_status ffn_impl(moe_stage *st, int32_t slot, void *stream, bool rec)
     f.y = sl.y_perm;
     f.layer_id = sl.mb.layer_id;
     f.max_group = (int64_t)T * d.top_k;       // a token may repeat an id
-    f.mt_max = (f.max_group + kBM - 1) / kBM + d.n_local_experts;
-    if (d.has_shared_expert) f.mt_max += (T + kBM - 1) / kBM;
-    f.G = (int32_t)st->sz.G;
     const moe_status r = launch_ffn(st, sl, f, !rec, s);
     if (r != MOE_OK) return r;
     return rec ? record(sl, s) : MOE_OK;
@@ -693,8 +642,6 @@ static moe_status ffn_grouped_impl(moe_stage *st, int32_t slot, const moe_groupe
     f.y = gb->y;
     f.layer_id = gb->layer_id;
     f.max_group = n;
-    f.mt_max = ((int64_t)n + kBM - 1) / kBM + d.n_local_experts;
-    f.G = d.n_local_experts;
     const moe_status r = launch_ffn(st, sl, f, true, s);
     if (r != MOE_OK) return r;
     return record(sl, s);
