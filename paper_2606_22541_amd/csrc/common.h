@@ -29,7 +29,6 @@ constexpr int kTileBlocks = 2 * kHalfBlocks;
 constexpr int kBandBf16 = 4;          // row tiles of a raster band
 // fp8 tiles: up to 128 rows.
 constexpr int kTileBlocksFp8 = 4;
-constexpr int kMinBlocksFp8 = 1;
 constexpr int kBandFp8 = 8;
 
 // Cache-policy operand of the raw buffer loads: non-temporal (streaming)

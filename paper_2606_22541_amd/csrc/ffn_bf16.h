@@ -138,6 +138,7 @@ __device__ __forceinline__ void h_store(u32x4 v, const Out &o, int off)
 // the panel-ordered weights per step) and read back lane-contiguous.
 // ---------------------------------------------------------------------------
 constexpr int kBK = 32;                       // bf16 elements per K step (2 MFMA sub-steps)
+constexpr int kAhead = 2;                     // steps that the fills run ahead
 
 struct Tile {
     __amdgpu_buffer_rsrc_t ra, rb;
@@ -268,19 +269,19 @@ __device__ __forceinline__ void pp_step(const Tile &t, const WaveConst &w, const
                                         f32x16 (&acc)[NMB > 0 ? NMB : 1][2], bf16x8 (&a0)[kHalfBlocks],
                                         bf16x8 (&a1)[kHalfBlocks], bf16x8 (&b0)[2], bf16x8 (&b1)[2], int j)
 {
-    // the fills of steps j+1 and j+2 are the loads issued after step j's
-    constexpr int kAfter = 2 * (row_loads(NMB) + 2);
+    // the fills of the kAhead - 1 steps after j are the loads issued after step j's
+    constexpr int kAfter = (kAhead - 1) * (row_loads(NMB) + 2);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt((kAfter & 15) | ((kAfter >> 4) << 14) | (7 << 4) | (15 << 8));
     phase_barrier();                                        // E_j
-    bf16 *fa = l.a((S + 3) & 3), *fb = l.b((S + 3) & 3);
+    bf16 *fa = l.a((S + kAhead) & 3), *fb = l.b((S + kAhead) & 3);
     if constexpr (LEAD) {
         read_step<S, NMB>(w, l, a0, a1, b0, b1);
         phase_barrier();                                    // O_j
-        mma_step<NMB, STREAM, true>(t, w, fa, fb, j + 3, acc, a0, a1, b0, b1);
+        mma_step<NMB, STREAM, true>(t, w, fa, fb, j + kAhead, acc, a0, a1, b0, b1);
     } else {
-        if constexpr (PREV) mma_step<NMB, STREAM, true>(t, w, fa, fb, j + 3, acc, a0, a1, b0, b1);
-        else fill<NMB, STREAM>(t, w, fa, fb, j + 3);
+        if constexpr (PREV) mma_step<NMB, STREAM, true>(t, w, fa, fb, j + kAhead, acc, a0, a1, b0, b1);
+        else fill<NMB, STREAM>(t, w, fa, fb, j + kAhead);
         phase_barrier();                                    // O_j
         read_step<S, NMB>(w, l, a0, a1, b0, b1);
         // the reads of stage S complete before E_{j+1}, where it is refilled
@@ -304,7 +305,7 @@ __device__ __forceinline__ void run_large(const Tile &t, const WaveConst &w, con
     bf16x8 a0[kHalfBlocks], a1[kHalfBlocks], b0[2], b1[2];
     fill<NMB, STREAM>(t, w, l.a(0), l.b(0), 0);
     fill<NMB, STREAM>(t, w, l.a(1), l.b(1), 1);
-    fill<NMB, STREAM>(t, w, l.a(2), l.b(2), 2);
+    if constexpr (kAhead > 2) fill<NMB, STREAM>(t, w, l.a(2), l.b(2), 2);
     // K is a multiple of 128, so KT is a multiple of 4; the first step (the
     // trailing half has nothing to multiply yet), then branch-free bodies of
     // four steps (stage = step % 4)
@@ -316,7 +317,7 @@ __device__ __forceinline__ void run_large(const Tile &t, const WaveConst &w, con
         pp_step<0, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j);
         pp_step<1, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + 1);
         pp_step<2, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + 2);
-        pp_step<3, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + 3);
+        pp_step<3, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + kAhead);
     }
     // E_KT: the trailing half multiplies the last step
     phase_barrier();
@@ -840,10 +841,7 @@ void k_ffn_bf16(FfnArgs)
             if (nb == kTallBlocks) {
                 t.vb = (wave >> 2) * ncb * 2048 + (4 * half + (wave & 3)) * 2048 + lane * 16;
                 run_tall(t, l, sw, o, n0 + (wave & 3) * 32, request);
-                wk.done(args->sched);
-                continue;
-            }
-            switch (nb) {
+            } else switch (nb) {
             case 1: run_small<1>(t, l, sw, o, n0, lds_h, request); break;
             case 2: run_small<2>(t, l, sw, o, n0, lds_h, request); break;
             case 3: run_small<3>(t, l, sw, o, n0, lds_h, request); break;
@@ -851,7 +849,8 @@ void k_ffn_bf16(FfnArgs)
             default: run_small<5>(t, l, sw, o, n0, lds_h, request); break;
             }
         }
-        wk.done(args->sched);
+        args = reload(args);
+        wk.done(args->sched, sl, args->phases, args->tiles);
     }
 }
 

@@ -85,10 +85,20 @@ constexpr int kSchedLdsTiles = 64;
 struct SchedLds {
     int4 rt[kSchedLdsTiles];
     int32_t hdr[4];
-    int32_t item, wait;
+    int32_t claimed, wait;     // begin(): the fixed item was taken; next(): what the wait found
+    int32_t item, rti, nt;     // the next item and its tile (bit 30 of rti: a large one)
     int32_t stage;     // thread 0: list being drained (0 gate/up, 1 down, 2 the others')
     uint64_t w[2], ws[2];   // weights of the two products, and their scales
 };
+
+// The thread's number, as a value that the compiler does not keep (nor what
+// it derives from it) in registers from one item to the next.
+__device__ __forceinline__ int fresh_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 
 __device__ __forceinline__ int agent_load(const int32_t *p)
 {
@@ -166,6 +176,7 @@ template <bool LARGE>
 struct Worker {
     int pending;                 // a down item put off for a gate/up item, or -1
     int first;                   // the fixed first item, or -1
+    bool have;                   // done() has taken the next item
     bool all_done;               // every row tile's gate/up tiles are written
     // current item
     bool down, large;
@@ -178,7 +189,7 @@ struct Worker {
         const int tid = threadIdx.x, b = blockIdx.x;
         if (tid < kSchedLdsTiles) l.rt[tid] = ((const int4 *)s.rt)[tid];
         else if (tid < kSchedLdsTiles + 3) l.hdr[tid - kSchedLdsTiles] = s.hdr[tid - kSchedLdsTiles];
-        else if (tid == 128) l.item = (phases & 1) ? agent_swap(&s.claim[b], 1) : 1;
+        else if (tid == 128) l.claimed = (phases & 1) ? agent_swap(&s.claim[b], 1) : 1;
         __syncthreads();
         Items q;
         q.load<LARGE>(l, phases, ct);
@@ -187,7 +198,8 @@ struct Worker {
         pre = -1;
         const int run = q.C << q.lg;
         first = q.x * q.C + (b >> q.lg);
-        if (__builtin_amdgcn_readfirstlane(l.item) != 0 || first >= q.total0) first = -1;
+        if (__builtin_amdgcn_readfirstlane(l.claimed) != 0 || first >= q.total0) first = -1;
+        have = false;
         if (tid == 0) l.stage = run + q.x * q.C < q.total0 ? 0 : 1;   // a second run of this list
         return q.total0 + q.total1 > 0;
     }
@@ -209,7 +221,7 @@ struct Worker {
     static __device__ __forceinline__ int ticket(ArgSched &s, int p, int y)
     {
         int j = 0;
-        if ((threadIdx.x & 63) == 0) j = agent_add(tick_of(s, p, y), 1);
+        if ((fresh_tid() & 63) == 0) j = agent_add(tick_of(s, p, y), 1);
         return __builtin_amdgcn_readfirstlane(j);
     }
     // An item of another list, product in bit 30, or -1 (wave 0): lane
@@ -217,7 +229,7 @@ struct Worker {
     // (gate/up items, and down items whose rows are ready) come first.
     static __device__ __forceinline__ int steal(ArgSched &s, const SchedLds &l, const Items &q)
     {
-        const int lane = threadIdx.x & 63, p = lane >> kListsLog2 & 1, y = lane & (kLists - 1);
+        const int lane = fresh_tid() & 63, p = lane >> kListsLog2 & 1, y = lane & (kLists - 1);
         const int first = p ? 0 : q.C;
         const int n = lane < 2 * kLists && y < 1 << q.lg ? q.len(p, y) : 0;
         for (;;) {
@@ -261,11 +273,24 @@ struct Worker {
         return steal(s, l, q);
     }
 
+    // Wave 0: takes the next item and looks up its tile.
+    __device__ __forceinline__ void take_next(ArgSched &s, SchedLds &l, const Items &q)
+    {
+        const int it = take(s, l, q);
+        if (it >= 0) {
+            int rt, n;
+            const bool lg = find(s, l, q, it & ~(1 << 30), it >> 30, rt, n);
+            l.rti = rt | (lg ? 1 << 30 : 0);
+            l.nt = n;
+        }
+        l.item = it;
+    }
+
     // Wave 0: waits until the rows of row tile rt are ready.  -1: they are,
     // -2: the rows of every row tile are, >= 0: a gate/up item to run first.
     static __device__ __forceinline__ int wait_or_help(ArgSched &s, const Items &q, int rt, int32_t *err)
     {
-        const int lane = threadIdx.x & 63, nx = 1 << q.lg;
+        const int lane = fresh_tid() & 63, nx = 1 << q.lg;
         for (int polls = 0;; ++polls) {
             const int v = agent_load(&s.dep[rt]);
             bool mine = q.nrt <= 256;
@@ -354,26 +379,34 @@ struct Worker {
     {
         Items q;
         q.load<LARGE>(l, phases, ct);
-        int it = pending;
-        if (first >= 0) {
-            it = first;
+        int it = pending, p;
+        if (first >= 0 || it >= 0) {
+            if (first >= 0) it = first;
             first = -1;
-        } else if (it < 0) {
-            __syncthreads();             // every thread has read the last item
-            if (threadIdx.x < 64) l.item = take(s, l, q);
-            __syncthreads();
+            pending = -1;
+            p = it >> 30;
+            it &= ~(1 << 30);
+            decode(s, l, q, it, p);
+        } else {
+            if (!have) {
+                if (fresh_tid() < 64) take_next(s, l, q);
+                __syncthreads();
+            }
             it = __builtin_amdgcn_readfirstlane(l.item);
             if (it < 0) return false;
+            p = it >> 30;
+            it &= ~(1 << 30);
+            const int r = __builtin_amdgcn_readfirstlane(l.rti);
+            rti = r & ~(1 << 30);
+            large = r >> 30;
+            nt = __builtin_amdgcn_readfirstlane(l.nt);
         }
-        pending = -1;
-        const int p = it >> 30;
-        it &= ~(1 << 30);
+        have = false;
         down = p != 0;
-        decode(s, l, q, it, p);
         if (p && phases == 3 && !all_done) {
-            if (threadIdx.x < 64) {
+            if (fresh_tid() < 64) {
                 const int r = wait_or_help(s, q, rti, err);
-                if (threadIdx.x == 0) l.wait = r;
+                if (fresh_tid() == 0) l.wait = r;
             }
             __syncthreads();
             const int r = __builtin_amdgcn_readfirstlane(l.wait);
@@ -396,7 +429,7 @@ struct Worker {
     // run keeps the workgroups that wait for it waiting.
     __device__ __forceinline__ void request()
     {
-        if (next_tick && threadIdx.x == 0 && pre < 0) pre = agent_add(next_tick, 1);
+        if (next_tick && fresh_tid() == 0 && pre < 0) pre = agent_add(next_tick, 1);
     }
 
     __device__ __forceinline__ RowTile row_tile(ArgSched &s, const SchedLds &l) const
@@ -412,13 +445,20 @@ struct Worker {
     }
 
     // The item's output is stored: a gate/up tile is counted once every
-    // wave's stores have reached memory.  Past it every LDS read of the item
-    // is done.
-    __device__ __forceinline__ void done(ArgSched &s)
+    // wave's stores have reached memory.  Wave 0 takes the next item before
+    // the barrier, while the other waves still store.  Past it every LDS read
+    // of the item is done.
+    __device__ __forceinline__ void done(ArgSched &s, SchedLds &l, int phases, ArgTiles &ct)
     {
+        have = pending < 0;
+        if (have && fresh_tid() < 64) {
+            Items q;
+            q.load<LARGE>(l, phases, ct);
+            take_next(s, l, q);
+        }
         if (!down) __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
         __syncthreads();
-        if (!down && threadIdx.x == 0) agent_add(&s.dep[rti], 1);
+        if (!down && fresh_tid() == 0) agent_add(&s.dep[rti], 1);
     }
 };
 

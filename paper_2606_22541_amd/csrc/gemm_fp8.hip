@@ -117,6 +117,7 @@ struct Ring8 {
 //    same ones: identical data to identical addresses).
 // Load i (0..6) of the fills: 0..3 the weight fragment halves, 4..5 the
 // token rows, 6 the token scales.
+template <bool DOWN>
 __device__ __forceinline__ void fill8_one(const Tile8 &t, const Ring8 &st, int wave, int lane, int kg,
                                           int i)
 {
@@ -133,14 +134,15 @@ __device__ __forceinline__ void fill8_one(const Tile8 &t, const Ring8 &st, int w
     } else {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(t.rs, (lds_void *)(st.s + (wave & 1) * 64), 4,
                                                  (ks * t.s_ld + (wave & 1) * 64 + lane) * 4, 0, 0,
-                                                 kAgentScope8);
+                                                 DOWN ? kAgentScope8 : 0);
     }
 }
 
+template <bool DOWN>
 __device__ __forceinline__ void fill8(const Tile8 &t, const Ring8 &st, int wave, int lane, int kg)
 {
 #pragma unroll
-    for (int i = 0; i < kFillLoads; ++i) fill8_one(t, st, wave, lane, kg, i);
+    for (int i = 0; i < kFillLoads; ++i) fill8_one<DOWN>(t, st, wave, lane, kg, i);
 }
 
 struct Wave8 {
@@ -206,7 +208,7 @@ __device__ __forceinline__ void read8(const Wave8 &w, const Ring8 (&ring)[3], i3
 // accepts about one 1 KB load every 19 clocks, and fills issued as one burst
 // by every wave hold each wave's later instructions until the load path has
 // taken them.
-template <int NCB, bool FILL = true>
+template <int NCB, bool DOWN, bool FILL = true>
 __device__ __forceinline__ void mfma8(const i32x8 (&wfr)[4], const i32x8 (&xf)[4],
                                       const float (&st)[4], float sb0, float sb1,
                                       f32x4 (&acc)[4][4], f32x4 (&pend)[4], float (&ps)[2],
@@ -227,7 +229,7 @@ __device__ __forceinline__ void mfma8(const i32x8 (&wfr)[4], const i32x8 (&xf)[4
                     wfr[rb], xf[cb], (f32x4){}, 0, 0, 0, 127, 0, 127);
                 if (cb == NCB - 1) pend[rb] = p; else tq[cb & 1][rb] = p;
                 const int j = 2 * cb + (rb >> 1);
-                if ((rb & 1) && j < kInter) fill8_one(t, fst, wave, lane, kgf, j);
+                if ((rb & 1) && j < kInter) fill8_one<DOWN>(t, fst, wave, lane, kgf, j);
             }
             if (cb > 0) {
                 const float s0 = st[cb - 1] * sb0, s1 = st[cb - 1] * sb1;
@@ -248,7 +250,7 @@ __device__ __forceinline__ void mfma8(const i32x8 (&wfr)[4], const i32x8 (&xf)[4
         ps[1] = st[NCB - 1] * sb1;
     }
 #pragma unroll
-    for (int i = kInter; i < (FILL ? kFillLoads : 0); ++i) fill8_one(t, fst, wave, lane, kgf, i);
+    for (int i = kInter; i < (FILL ? kFillLoads : 0); ++i) fill8_one<DOWN>(t, fst, wave, lane, kgf, i);
 }
 
 // s_waitcnt operands (gfx9 encoding: vmcnt [3:0] and [15:14], expcnt [6:4],
@@ -270,7 +272,7 @@ __device__ __forceinline__ void slot_barrier()
 
 // Group g (stage S) for a wave of either half.  LEAD: waves 0..3.  MFMA_PREV:
 // the trailing half has a group g-1 to multiply (g > 0).
-template <int S, int NCB, bool LEAD, bool MFMA_PREV>
+template <int S, int NCB, bool LEAD, bool DOWN, bool MFMA_PREV>
 __device__ __forceinline__ void group8(const Tile8 &t, const Wave8 &w, const Ring8 (&ring)[3],
                                        f32x4 (&acc)[4][4], i32x8 (&wfr)[4], i32x8 (&xf)[4],
                                        float (&st)[4], float (&sb)[2], float (&sb_next)[2],
@@ -285,12 +287,12 @@ __device__ __forceinline__ void group8(const Tile8 &t, const Wave8 &w, const Rin
         sb_next[1] = t.sbp1[min(kg + 1, t.KT - 1)];
         read8<S, NCB>(w, ring, wfr, xf, st, acc, pend, ps);
         slot_barrier<-1>();                       // O_kg
-        mfma8<NCB>(wfr, xf, st, sb[0], sb[1], acc, pend, ps, t, fst, w.wave, w.lane, kg + 2);
+        mfma8<NCB, DOWN>(wfr, xf, st, sb[0], sb[1], acc, pend, ps, t, fst, w.wave, w.lane, kg + 2);
     } else {
         if constexpr (MFMA_PREV)
-            mfma8<NCB>(wfr, xf, st, sb[0], sb[1], acc, pend, ps, t, fst, w.wave, w.lane, kg + 2);
+            mfma8<NCB, DOWN>(wfr, xf, st, sb[0], sb[1], acc, pend, ps, t, fst, w.wave, w.lane, kg + 2);
         else
-            fill8(t, fst, w.wave, w.lane, kg + 2);
+            fill8<DOWN>(t, fst, w.wave, w.lane, kg + 2);
         slot_barrier<-1>();                       // O_kg
         sb[0] = sb_next[0];
         sb[1] = sb_next[1];
@@ -305,7 +307,7 @@ __device__ __forceinline__ void group8(const Tile8 &t, const Wave8 &w, const Rin
 
 // The K loop of one tile for a wave of one half with NCB token blocks
 // holding tokens.  Both halves pass 2 KT + 1 barriers.
-template <bool LEAD, int NCB>
+template <bool LEAD, int NCB, bool DOWN>
 __device__ __forceinline__ void kloop8(const Tile8 &t, const Wave8 &w, const Ring8 (&ring)[3],
                                        f32x4 (&acc)[4][4])
 {
@@ -316,23 +318,23 @@ __device__ __forceinline__ void kloop8(const Tile8 &t, const Wave8 &w, const Rin
     i32x8 wfr[4], xf[4];
     float st[4];
     __builtin_amdgcn_sched_barrier(0);
-    fill8(t, ring[0], w.wave, w.lane, 0);
-    fill8(t, ring[1], w.wave, w.lane, 1);
+    fill8<DOWN>(t, ring[0], w.wave, w.lane, 0);
+    fill8<DOWN>(t, ring[1], w.wave, w.lane, 1);
     // the first group (the trailing half has nothing to multiply yet), a
     // branch-free body of three groups (stage = group % 3), then the rest
-    group8<0, NCB, LEAD, false>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, 0);
+    group8<0, NCB, LEAD, DOWN, false>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, 0);
     int kg = 1;
     for (; kg + 3 <= t.KT; kg += 3) {
-        group8<1, NCB, LEAD, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg);
-        group8<2, NCB, LEAD, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg + 1);
-        group8<0, NCB, LEAD, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg + 2);
+        group8<1, NCB, LEAD, DOWN, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg);
+        group8<2, NCB, LEAD, DOWN, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg + 1);
+        group8<0, NCB, LEAD, DOWN, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg + 2);
     }
-    if (kg < t.KT) group8<1, NCB, LEAD, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg);
-    if (kg + 1 < t.KT) group8<2, NCB, LEAD, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg + 1);
+    if (kg < t.KT) group8<1, NCB, LEAD, DOWN, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg);
+    if (kg + 1 < t.KT) group8<2, NCB, LEAD, DOWN, true>(t, w, ring, acc, wfr, xf, st, sb, sb_next, pend, ps, kg + 1);
     // E_KT: the trailing half multiplies the last group
     slot_barrier<-1>();
     if constexpr (!LEAD)
-        mfma8<NCB, false>(wfr, xf, st, sb[0], sb[1], acc, pend, ps, t, ring[0], w.wave, w.lane, 0);
+        mfma8<NCB, DOWN, false>(wfr, xf, st, sb[0], sb[1], acc, pend, ps, t, ring[0], w.wave, w.lane, 0);
     if constexpr (NCB > 0) {
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
@@ -341,6 +343,29 @@ __device__ __forceinline__ void kloop8(const Tile8 &t, const Wave8 &w, const Rin
 }
 
 }  // namespace
+
+template <bool DOWN>
+__device__ __forceinline__ void kloop8_any(const Tile8 &t, const Wave8 &w, const Ring8 (&ring)[3],
+                                           f32x4 (&acc)[4][4], int ncbw)
+{
+    if (w.wt == 0) {
+        switch (ncbw) {
+        case 0: kloop8<true, 0, DOWN>(t, w, ring, acc); break;
+        case 1: kloop8<true, 1, DOWN>(t, w, ring, acc); break;
+        case 2: kloop8<true, 2, DOWN>(t, w, ring, acc); break;
+        case 3: kloop8<true, 3, DOWN>(t, w, ring, acc); break;
+        default: kloop8<true, 4, DOWN>(t, w, ring, acc); break;
+        }
+    } else {
+        switch (ncbw) {
+        case 0: kloop8<false, 0, DOWN>(t, w, ring, acc); break;
+        case 1: kloop8<false, 1, DOWN>(t, w, ring, acc); break;
+        case 2: kloop8<false, 2, DOWN>(t, w, ring, acc); break;
+        case 3: kloop8<false, 3, DOWN>(t, w, ring, acc); break;
+        default: kloop8<false, 4, DOWN>(t, w, ring, acc); break;
+        }
+    }
+}
 
 __global__ __launch_bounds__(kThreads8, 1)
 void k_ffn_fp8(FfnArgs)
@@ -469,23 +494,8 @@ void k_ffn_fp8(FfnArgs)
         // 16-token blocks of this wave's 64 tokens that hold tokens of the group
         const int ncbw = __builtin_amdgcn_readfirstlane(
             min(4, max(0, rows_valid - w.wt * 64 + 15) / 16));
-        if (w.wt == 0) {
-            switch (ncbw) {
-            case 0: kloop8<true, 0>(t, w, ring, acc); break;
-            case 1: kloop8<true, 1>(t, w, ring, acc); break;
-            case 2: kloop8<true, 2>(t, w, ring, acc); break;
-            case 3: kloop8<true, 3>(t, w, ring, acc); break;
-            default: kloop8<true, 4>(t, w, ring, acc); break;
-            }
-        } else {
-            switch (ncbw) {
-            case 0: kloop8<false, 0>(t, w, ring, acc); break;
-            case 1: kloop8<false, 1>(t, w, ring, acc); break;
-            case 2: kloop8<false, 2>(t, w, ring, acc); break;
-            case 3: kloop8<false, 3>(t, w, ring, acc); break;
-            default: kloop8<false, 4>(t, w, ring, acc); break;
-            }
-        }
+        if (down) kloop8_any<true>(t, w, ring, acc, ncbw);
+        else kloop8_any<false>(t, w, ring, acc, ncbw);
         __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0): the clamped look-ahead fills
         __syncthreads();                                     // ring idle in every wave
         wk.request();
@@ -566,7 +576,8 @@ void k_ffn_fp8(FfnArgs)
                 }
             }
         }
-        wk.done(args->sched);
+        args = reload(args);
+        wk.done(args->sched, sl, args->phases, args->tiles);
     }
 }
 

@@ -453,8 +453,7 @@ static SchedPlan sched_plan(const moe_stage *st, int cus)
     SchedPlan p{ffn_grid(cus), (n1 + 255) / 256, (n1 + 127) / 128, kSmallRows, kSmallRowsDown, 2, kTileBlocks};
     if (st->desc.dtype == MOE_DTYPE_FP8_E4M3_B128) {   // every group in the fp8 kernel's tiles
         p.small_rows = p.small_rows_down = 0;
-        p.min_blocks = kMinBlocksFp8;
-        p.max_blocks = kTileBlocksFp8;
+        p.min_blocks = p.max_blocks = kTileBlocksFp8;
     }
     return p;
 }
