@@ -203,7 +203,7 @@ __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedP
         c_mid += __popcll(mid);
         c_small += __popcll(small);
     }
-    for (int i = lane; i < n_all; i += 64) s.dep[i] = 0;
+    for (int i = lane; i < n_all; i += 64) s.dep[i * kDepStride] = 0;
     if (lane == 0) {
         s.hdr[0] = n_all;
         s.hdr[1] = n_large;
@@ -219,7 +219,7 @@ void k_reset_schedule(Sched s)
     for (int i = threadIdx.x; i < kSchedTicks; i += kDispatchThreads) s.tick[i] = 0;
     for (int i = threadIdx.x; i < kMaxSchedCus; i += kDispatchThreads) s.claim[i] = 0;
     const int n = s.hdr[0];
-    for (int i = threadIdx.x; i < n; i += kDispatchThreads) s.dep[i] = 0;
+    for (int i = threadIdx.x; i < n; i += kDispatchThreads) s.dep[i * kDepStride] = 0;
 }
 
 hipError_t launch_reset_schedule(const Sched &s, hipStream_t st)

@@ -34,6 +34,7 @@ namespace moe {
 
 constexpr int kMaxSchedCus = 512;     // workgroups of one launch
 constexpr int kTickStride = 32;       // ints between ticket counters (128 bytes)
+constexpr int kDepStride = 32;        // ints between row tiles' counts of written tiles
 constexpr int kListsLog2 = 3;
 constexpr int kLists = 1 << kListsLog2;
 // Polls of one wait before it gives up (seconds; a wait takes microseconds).
@@ -42,7 +43,7 @@ constexpr int kMaxPolls = 1 << 22;
 struct Sched {
     int32_t *rt;       // [n] int4 row tiles
     int32_t *hdr;      // row tiles, large ones of gate/up, large ones of down
-    int32_t *dep;      // [n] gate/up tiles written, per row tile
+    int32_t *dep;      // [n] gate/up tiles written, per row tile, kDepStride apart
     int32_t *claim;    // [kMaxSchedCus] fixed first item taken, per workgroup
     int32_t *tick;     // [2][kLists] tickets, kTickStride apart
 };
@@ -61,7 +62,7 @@ __host__ __device__ inline int64_t sched_max_tiles(int64_t rows, int64_t G)
 // Ints of a schedule, and its arrays in one allocation.
 inline int64_t sched_ints(int64_t max_tiles)
 {
-    return kSchedHdr + kSchedTicks + kMaxSchedCus + ((5 * max_tiles + 63) & ~(int64_t)63);
+    return kSchedHdr + kSchedTicks + kMaxSchedCus + (4 + kDepStride) * max_tiles;
 }
 inline Sched sched_at(int32_t *base, int64_t max_tiles)
 {
@@ -241,7 +242,7 @@ struct Worker {
             if (open && p) {
                 int rt, nt;
                 find(s, l, q, q.item(j, y, 1), 1, rt, nt);
-                ready = agent_load(&s.dep[rt]) >= q.need(rt);
+                ready = agent_load(&s.dep[rt * kDepStride]) >= q.need(rt);
             }
             const uint64_t now = __ballot(ready);
             const int v = __ffsll((unsigned long long)(now ? now : any)) - 1;
@@ -292,17 +293,14 @@ struct Worker {
     {
         const int lane = fresh_tid() & 63, nx = 1 << q.lg;
         for (int polls = 0;; ++polls) {
-            const int v = agent_load(&s.dep[rt]);
-            bool mine = q.nrt <= 256;
-            if (mine) {
-                int d[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) d[i] = agent_load(&s.dep[min(lane + 64 * i, q.nrt - 1)]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) mine &= d[i] >= q.need(min(lane + 64 * i, q.nrt - 1));
+            // one load of one line a poll: many workgroups may be waiting, and
+            // their polls share HBM channels with the others' streams
+            if (__builtin_amdgcn_readfirstlane(agent_load(&s.dep[rt * kDepStride])) >= q.need(rt)) {
+                bool mine = true;
+                for (int i = lane; i < q.nrt && i < 256; i += 64)
+                    mine &= agent_load(&s.dep[i * kDepStride]) >= q.need(i);
+                return __all(mine) && q.nrt <= 256 ? -2 : -1;
             }
-            if (__all(mine)) return -2;
-            if (__builtin_amdgcn_readfirstlane(v) >= q.need(rt)) return -1;
             if (polls > 2) {
                 // gate/up items that no workgroup has taken: tickets ...
                 const int y = lane & (kLists - 1);
@@ -458,7 +456,7 @@ struct Worker {
         }
         if (!down) __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
         __syncthreads();
-        if (!down && fresh_tid() == 0) agent_add(&s.dep[rti], 1);
+        if (!down && fresh_tid() == 0) agent_add(&s.dep[rti * kDepStride], 1);
     }
 };
 
