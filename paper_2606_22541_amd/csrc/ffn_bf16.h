@@ -317,7 +317,7 @@ __device__ __forceinline__ void run_large(const Tile &t, const WaveConst &w, con
         pp_step<0, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j);
         pp_step<1, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + 1);
         pp_step<2, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + 2);
-        pp_step<3, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + kAhead);
+        pp_step<3, NMB, STREAM, LEAD, true>(t, w, l, acc, a0, a1, b0, b1, j + 3);
     }
     // E_KT: the trailing half multiplies the last step
     phase_barrier();
