@@ -27,13 +27,18 @@ import os
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
+_FFN_BF16 = ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/ffn_bf16.h", "csrc/ffn_sched.h",
+             "csrc/common.h", "csrc/kernels.h"]
+_FFN_FP8 = ["csrc/gemm_fp8.hip", "csrc/ffn_sched.h", "csrc/common.h", "csrc/kernels.h"]
+# "ffn": the launch of both products; the gemm groups: its two halves, which
+# run as launches of their own while a stage's profiling is on
 KERNEL_SOURCES = {
-    "gemm_gate_up_swiglu": ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/common.h",
-                            "csrc/kernels.h"],
-    "gemm_down": ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/common.h",
-                  "csrc/kernels.h"],
-    "gemm_gate_up_swiglu_fp8": ["csrc/gemm_fp8.hip", "csrc/common.h", "csrc/kernels.h"],
-    "gemm_down_fp8": ["csrc/gemm_fp8.hip", "csrc/common.h", "csrc/kernels.h"],
+    "ffn": _FFN_BF16,
+    "ffn_fp8": _FFN_FP8,
+    "gemm_gate_up_swiglu": _FFN_BF16,
+    "gemm_down": _FFN_BF16,
+    "gemm_gate_up_swiglu_fp8": _FFN_FP8,
+    "gemm_down_fp8": _FFN_FP8,
     "combine": ["csrc/combine.hip", "csrc/common.h", "csrc/kernels.h"],
     "gather": ["csrc/dispatch.hip", "csrc/common.h", "csrc/kernels.h"],
     "dispatch_index": ["csrc/dispatch.hip", "csrc/common.h", "csrc/kernels.h"],
@@ -42,12 +47,9 @@ KERNEL_SOURCES = {
 # bench.py times (a group's kernels each run once per micro-batch, so a
 # group's per-step figure is the sum over its kernels)
 NAME_MAP = (
-    ("void moe::k_gemm_bf16_small<true>", "gemm_gate_up_swiglu"),
-    ("void moe::k_gemm_bf16<true>", "gemm_gate_up_swiglu"),
-    ("void moe::k_gemm_bf16<false>", "gemm_down"),
-    ("void moe::k_gemm_bf16_small<false>", "gemm_down"),
-    ("void moe::k_gemm_fp8<true>", "gemm_gate_up_swiglu_fp8"),
-    ("void moe::k_gemm_fp8<false>", "gemm_down_fp8"),
+    ("void moe::k_ffn_bf16<true>", "ffn"),
+    ("void moe::k_ffn_bf16<false>", "ffn"),
+    ("moe::k_ffn_fp8", "ffn_fp8"),
     ("moe::k_combine", "combine"),
     ("moe::k_gather_scales", "gather"),
     ("moe::k_transpose_scales", "gather"),
@@ -221,7 +223,7 @@ PEAK_CLOCK_GHZ = 2.4
 
 
 def flop_per_mfma(kernel: str) -> int:
-    return 65536 if "k_gemm_fp8" in kernel else 32768
+    return 65536 if "_fp8" in kernel else 32768
 
 
 def mfma_util(path: str):
@@ -233,7 +235,7 @@ def mfma_util(path: str):
     per = collections.defaultdict(dict)
     for r in rows:
         n = r["Kernel_Name"]
-        if not n.startswith("void moe::k_gemm"):
+        if "moe::k_gemm" not in n and "moe::k_ffn" not in n:
             continue
         d = per[(n.split("(")[0], r["Dispatch_Id"])]
         d[r["Counter_Name"]] = float(r["Counter_Value"])
