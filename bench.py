@@ -735,7 +735,7 @@ def run_grouped(name="c1", steps=40, warmup=20, repeats=3):
     """The pre-grouped input path (moe_expert_ffn_grouped): the micro-batch's
     local (token, expert) rows laid out grouped by expert before the timed
     region (torch ops), the per-expert counts in device memory; each step is
-    one moe_expert_ffn_grouped call (tile tables from the counts, then the two
+    one moe_expert_ffn_grouped call (row tiles from the counts, then the two
     grouped GEMMs).  Returns ms per call (median of `repeats` regions)."""
     import torch
     from paper_2606_22541_amd import inputs

@@ -216,11 +216,12 @@ MOE_API moe_status moe_dispatch(moe_stage *stage, int32_t slot, const moe_microb
                         void *stream);
 
 /* Step 2: grouped GEMM gate/up with fused SiLU*up epilogue, then grouped GEMM
- * down, for every local expert with rows (and the shared expert, if any).
- * The tile schedule is built on the device by moe_dispatch. */
+ * down, for every local expert with rows (and the shared expert, if any), in
+ * one launch.  The schedule of its tiles is built on the device by
+ * moe_dispatch. */
 MOE_API moe_status moe_expert_ffn(moe_stage *stage, int32_t slot, void *stream);
 
-/* Step 2 for pre-grouped rows (moe_grouped_batch): builds the tile tables
+/* Step 2 for pre-grouped rows (moe_grouped_batch): builds the schedule of tiles
  * on the device from gb->counts, then runs the same grouped GEMMs as
  * moe_expert_ffn on gb->rows into gb->y, on `slot`'s workspace (H; fp8 also
  * the transposed row scales).  The stage's shared expert, if any, is not
@@ -285,8 +286,8 @@ MOE_API moe_status moe_stage_poll(moe_stage *stage, int32_t slot);
  * stable counting-sort permutation; bf16 moe_dispatch minus the stage) for
  * callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Allocates nothing:
- * its only scratch (one histogram row of n_experts counts per 1024 slots,
- * and the grouped-GEMM tile tables) is a fixed 4 MiB array that the library
+ * its only scratch (one histogram row of n_experts counts per 1024 slots)
+ * is a fixed 4 MiB array that the library
  * holds on every device it runs on until the process ends.
  * Inputs:  topk_ids [n_tokens][top_k] int32 (-1 = masked), device memory.
  * Outputs (device memory, written as moe_dispatch writes them into a slot):
@@ -329,13 +330,15 @@ MOE_API moe_status moe_stage_query(moe_stage *stage, int32_t slot, moe_dispatch_
  * clears) the sticky device errors: MOE_EBADID if a kernel saw an invalid
  * expert id since the last sync, else MOE_EBADLAYER if one saw an invalid
  * layer id, else MOE_EBADCOUNT if one saw invalid pre-grouped counts, else
- * MOE_ETIMEOUT if an ingest wait gave up, else MOE_OK (or MOE_EHIP). */
+ * MOE_ETIMEOUT if an ingest wait gave up, else MOE_OK (or MOE_EHIP: a HIP
+ * call failed, or an FFN pass gave up waiting for its own rows). */
 MOE_API moe_status moe_stage_sync(moe_stage *stage);
 
 /* Per-kernel timing with HIP events, for measurement (off by default).
  * While enabled, every enqueue call records an event pair around each of its
  * kernel groups on the launch stream (this creates events, i.e. allocates
- * host-side runtime objects).  Kinds, in order: 0 dispatch index
+ * host-side runtime objects), and the two grouped GEMMs run as a launch each
+ * (otherwise one launch runs both, and takes less than their sum).  Kinds, in order: 0 dispatch index
  * (histogram, scan, scatter), 1 gather of the token scales (fp8 only; the
  * rows themselves are gathered inside kind 2), 2 grouped GEMM gate/up with the SiLU*up epilogue (fp8: and the
  * quantisation of h), 3 grouped GEMM down, 4 combine, 5 reserved (no

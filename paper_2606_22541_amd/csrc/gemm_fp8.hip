@@ -11,12 +11,13 @@
 // these fp32 scales and are left at 1.
 //
 // Design for gfx950:
-//  * one persistent workgroup per CU walks the tiles of every group
-//    (128-token x 256-feature tiles; the per-group tile counts are a prefix
-//    the workgroup builds in LDS from the device row counts), XCD-aware:
-//    consecutive tile numbers go to the 32 workgroups of one XCD, rastered
-//    in bands of up to 8 token tiles so that each weight panel is read by
-//    one XCD;
+//  * one persistent workgroup per CU runs items (128-token x 256-feature
+//    tiles) of both products in one launch, from the lists of ffn_sched.h: a
+//    down item starts once the gate/up tiles of its rows are written, so no
+//    idle last round and no launch gap lies between the products (T = 32768,
+//    d = 7168, f = 2048, 8 experts, with dispatch and combine: 514 -> 491 us;
+//    T = 2049: 133 -> 129).  Row tiles are rastered in bands of up to 8 so that each weight
+//    panel is read by one XCD;
 //  * the product is formed transposed, D[feature][token] = W X^T: the
 //    weights are the MFMA's row operand and the tokens its column operand,
 //    so each lane holds four consecutive features of ONE token and the
@@ -42,7 +43,9 @@
 //    block) and a 256-feature gate/up tile covers exactly one 128-channel
 //    group of h;
 //  * token rows are 128-byte rows whose 16-byte chunks are XOR-swizzled by
-//    (row / 2) % 8; rows past a group's end have an offset past every buffer
+//    (row / 2) & 5: a lane reads two chunks 4 apart, and with this mask neither
+//    read has a bank conflict ((row / 2) % 8 has: 1% of the time at T = 32768
+//    and above); rows past a group's end have an offset past every buffer
 //    range and read as zero; the scalar offset, which the range check does
 //    not cover, only moves along K (clamped to the last group) and between
 //    weight fragments that exist;
@@ -55,8 +58,12 @@
 //    channels, the per-token |h| maximum over the tile's 128 channels meets
 //    in a 2 KB LDS table, and each token's channels are quantised to e4m3
 //    with one fp32 scale amax / 448 (the activation quantiser's scale;
-//    the quotient is taken as a product with the scale's reciprocal), four
-//    codes per lane and store.  The down product writes bf16, four
+//    the quotient is taken as a product with the scale's reciprocal).  The
+//    codes are staged in LDS and leave as whole 128-byte rows, past this XCD's
+//    L2 to memory (the down items that read them run on other XCDs in the same
+//    launch).  The down product reads the rows' scales the same way (the gate/up
+//    product's scales are inputs and keep ordinary loads: 0.7% of the time) and
+//    writes bf16, four
 //    consecutive features per lane.
 #include "ffn_sched.h"
 #include "kernels.h"

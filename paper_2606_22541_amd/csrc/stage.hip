@@ -606,7 +606,7 @@ static moe_status ffn_impl(moe_stage *st, int32_t slot, void *stream, bool rec)
     return rec ? record(sl, s) : MOE_OK;
 }
 
-// Pre-grouped rows: the tile tables come from the caller's device counts
+// Pre-grouped rows: the row tiles come from the caller's device counts
 // instead of the dispatch, the gate/up product reads the rows as they are,
 // and the down product writes the caller's y.  No combine follows.
 static moe_status ffn_grouped_impl(moe_stage *st, int32_t slot, const moe_grouped_batch *gb,
