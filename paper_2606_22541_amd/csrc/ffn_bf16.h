@@ -23,9 +23,9 @@
 //
 // Measured, against one launch per product and size class with whole rounds of
 // equal tiles (us a micro-batch with its dispatch and combine, d = 7168, f =
-// 2048, 8 of 256 experts here, top 8): T = 32768 805 -> 707, T = 8191 319 -> 269,
+// 2048, 8 of 256 experts here, top 8): T = 32768 810 -> 705, T = 8191 340 -> 258,
 // T = 4096, where the weights' stream bounds both products, 168 -> 167; 32
-// experts here and a shared one, T = 1000: 702 -> 538.
+// experts here and a shared one, T = 1000: 701 -> 537.
 #pragma once
 
 #include "ffn_sched.h"

@@ -4,7 +4,11 @@
 //
 // Row tiles (int4 {group | only << 30, row0, rows | m << 9, first}: the group
 // has m row tiles from `first` on): the large groups' tiles, group by group,
-// then the small groups'.
+// then the small groups'.  Where the down product does not split the groups that
+// the gate/up product splits, its row tiles, one a group and all of them large,
+// follow as a table of their own ({group | m of gate/up << 16 | 1 << 30, row0,
+// rows | 1 << 9 | first of gate/up << 19, first}), and the written gate/up tiles
+// are counted per group (at the group's first row tile) instead of per row tile.
 // An item of a product is (row tile, column tile); items are numbered group
 // by group, within a large group in bands of a few row tiles (row tiles
 // fastest, so that one band's weight panels and token rows are shared in an
@@ -45,7 +49,9 @@ constexpr int kMaxReadyScan = 1024;   // row tiles that one wait looks over for 
 
 struct Sched {
     int32_t *rt;       // [n] int4 row tiles
-    int32_t *hdr;      // row tiles, large ones of gate/up, large ones of down
+    // row tiles, large ones of gate/up, large ones of down; row tiles of the
+    // down product, where its table begins (0: the same table)
+    int32_t *hdr;
     int32_t *dep;      // [n] gate/up tiles written, per row tile, kDepStride apart
     int32_t *claim;    // [kMaxSchedCus] fixed first item taken, per workgroup
     int32_t *tick;     // [2][kLists] tickets, kTickStride apart
@@ -55,12 +61,13 @@ struct Sched {
 typedef const __attribute__((address_space(4))) Sched ArgSched;
 
 constexpr int kSchedHdr = 64;
+constexpr int kSchedHdrInts = 5;
 constexpr int kSchedTicks = 2 * kLists * kTickStride;
 
 // Row tiles that G groups with `rows` rows in all can make.
 __host__ __device__ inline int64_t sched_max_tiles(int64_t rows, int64_t G)
 {
-    return rows / 128 + G + kMaxSchedCus;
+    return rows / 128 + 2 * (G + kMaxSchedCus);
 }
 // Ints of a schedule, and its arrays in one allocation.
 inline int64_t sched_ints(int64_t max_tiles)
@@ -88,7 +95,7 @@ struct RowTile {
 constexpr int kSchedLdsTiles = 64;
 struct SchedLds {
     int4 rt[kSchedLdsTiles];
-    int32_t hdr[4];
+    int32_t hdr[kSchedHdrInts];
     int32_t claimed, wait;     // begin(): the fixed item was taken; next(): what the wait found
     int32_t item, rti, nt;     // the next item and its tile (bit 30 of rti: a large one)
     int32_t stage;     // thread 0: list being drained (0 gate/up, 1 down, 2 the others')
@@ -131,10 +138,11 @@ struct Items {
     int lg, C, x;              // log2 of the lists, workgroups per list, this workgroup's list
     int C1;                    // run length of the down product's items
     int nrt, nl0, nl1;         // row tiles, large ones of gate/up and of down
+    int nrtd, sd;              // row tiles of down, the start of their table
     int ntl0, ntl1, nts0, nts1, band;
     int total0, total1;
 
-    template <bool LARGE>
+    template <bool LARGE, bool OWN>
     __device__ __forceinline__ void load(const SchedLds &l, int phases, ArgTiles &ct)
     {
         const int P = gridDim.x;
@@ -144,12 +152,14 @@ struct Items {
         nrt = __builtin_amdgcn_readfirstlane(l.hdr[0]);
         nl0 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[1]) : 0;
         nl1 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[2]) : 0;
+        nrtd = OWN ? __builtin_amdgcn_readfirstlane(l.hdr[3]) : nrt;
+        sd = OWN ? __builtin_amdgcn_readfirstlane(l.hdr[4]) : 0;
         ntl0 = ct.ntl[0];
         ntl1 = ct.ntl[1];
         nts0 = ct.nts[0];
         nts1 = ct.nts[1];
         band = ct.band;
-        const int g = nl0 * ntl0 + (nrt - nl0) * nts0, d = nl1 * ntl1 + (nrt - nl1) * nts1;
+        const int g = nl0 * ntl0 + (nrt - nl0) * nts0, d = nl1 * ntl1 + (nrtd - nl1) * nts1;
         total0 = (phases & 1) ? g : 0;
         total1 = (phases & 2) ? d : 0;
         // a list's down items are those of the row tiles that it did the
@@ -171,12 +181,13 @@ struct Items {
         const int R = p ? C1 : C, r = j / R;
         return r * (R << lg) + y * R + (j - r * R);
     }
-    // gate/up tiles of a row tile
+    // gate/up tiles that the count of gate/up row tile rt comes to
     __device__ __forceinline__ int need(int rt) const { return rt < nl0 ? ntl0 : nts0; }
 };
 
 // One workgroup's place in the lists.
-template <bool LARGE>
+// LARGE: large tiles occur.  OWN: the down product may have row tiles of its own.
+template <bool LARGE, bool OWN = LARGE>
 struct Worker {
     int pending;                 // a down item put off for a gate/up item, or -1
     int first;                   // the fixed first item, or -1
@@ -192,11 +203,11 @@ struct Worker {
     {
         const int tid = threadIdx.x, b = blockIdx.x;
         if (tid < kSchedLdsTiles) l.rt[tid] = ((const int4 *)s.rt)[tid];
-        else if (tid < kSchedLdsTiles + 3) l.hdr[tid - kSchedLdsTiles] = s.hdr[tid - kSchedLdsTiles];
+        else if (tid < kSchedLdsTiles + kSchedHdrInts) l.hdr[tid - kSchedLdsTiles] = s.hdr[tid - kSchedLdsTiles];
         else if (tid == 128) l.claimed = (phases & 1) ? agent_swap(&s.claim[b], 1) : 1;
         __syncthreads();
         Items q;
-        q.load<LARGE>(l, phases, ct);
+        q.load<LARGE, OWN>(l, phases, ct);
         all_done = false;
         pending = -1;
         pre = -1;
@@ -221,6 +232,22 @@ struct Worker {
         return v;
     }
 
+    // The count that the down items of row tile rt (its place in the table)
+    // wait for, and what it comes to.
+    static __device__ __forceinline__ const int32_t *dep_of(ArgSched &s, const SchedLds &l, const Items &q, int rt,
+                                                            int &need)
+    {
+        int c = rt;
+        need = 1;
+        if (OWN && q.sd) {
+            const int4 e = entry(s, l, rt);
+            c = e.z >> 19;
+            need = e.x >> 16 & 0x3fff;
+        }
+        need *= q.need(c);
+        return &s.dep[c * kDepStride];
+    }
+
     // A ticket of product p, list y (wave 0; every lane gets it).
     static __device__ __forceinline__ int ticket(ArgSched &s, int p, int y)
     {
@@ -243,9 +270,10 @@ struct Worker {
             if (!any) return -1;
             bool ready = open;
             if (open && p) {
-                int rt, nt;
+                int rt, nt, need;
                 find(s, l, q, q.item(j, y, 1), 1, rt, nt);
-                ready = agent_load(&s.dep[rt * kDepStride]) >= q.need(rt);
+                const int32_t *dep = dep_of(s, l, q, rt, need);
+                ready = agent_load(dep) >= need;
             }
             const uint64_t now = __ballot(ready);
             const int v = __ffsll((unsigned long long)(now ? now : any)) - 1;
@@ -292,18 +320,24 @@ struct Worker {
 
     // Wave 0: waits until the rows of row tile rt are ready.  -1: they are,
     // -2: the rows of every row tile are, >= 0: a gate/up item to run first.
-    static __device__ __forceinline__ int wait_or_help(ArgSched &s, const Items &q, int rt, int32_t *err)
+    static __device__ __forceinline__ int wait_or_help(ArgSched &s, const SchedLds &l, const Items &q, int rt,
+                                                       int32_t *err)
     {
         const int lane = fresh_tid() & 63, nx = 1 << q.lg;
+        int need;
+        const int32_t *dep = dep_of(s, l, q, rt, need);
         for (int polls = 0;; ++polls) {
             // one load of one line a poll: many workgroups may be waiting, and
             // their polls share HBM channels with the others' streams
-            if (__builtin_amdgcn_readfirstlane(agent_load(&s.dep[rt * kDepStride])) >= q.need(rt)) {
+            if (__builtin_amdgcn_readfirstlane(agent_load(dep)) >= __builtin_amdgcn_readfirstlane(need)) {
                 // with every row tile ready the workgroup's later items need
                 // no poll (fp8, 270 row tiles: 1721 -> 1698 us a pass)
-                bool mine = q.nrt <= kMaxReadyScan;
-                for (int i = lane; i < q.nrt && i < kMaxReadyScan; i += 64)
-                    mine &= agent_load(&s.dep[i * kDepStride]) >= q.need(i);
+                bool mine = q.nrtd <= kMaxReadyScan;
+                for (int i = lane; i < q.nrtd && i < kMaxReadyScan; i += 64) {
+                    int n;
+                    const int32_t *di = dep_of(s, l, q, q.sd + i, n);
+                    mine &= agent_load(di) >= n;
+                }
                 return __all(mine) ? -2 : -1;
             }
             if (polls > 2) {
@@ -346,11 +380,12 @@ struct Worker {
     {
         const int nl = p ? q.nl1 : q.nl0, wl = p ? q.ntl1 : q.ntl0, ws = p ? q.nts1 : q.nts0;
         const bool large = it < nl * wl;
+        const int base = OWN && p ? q.sd : 0;
         if (large) {
             // the items of a group's m row tiles from the first on, in bands
             const int r0 = it / wl;
-            const int4 e = entry(s, l, r0);
-            const int rt0 = e.w, m = e.z >> 9;
+            const int4 e = entry(s, l, base + r0);
+            const int rt0 = e.w, m = e.z >> 9 & (base ? 0x3ff : -1);
             const int i = it - rt0 * wl;
             if (m <= q.band) {
                 nt = i / m;
@@ -367,6 +402,7 @@ struct Worker {
             rt = nl + j;
             nt = i - j * ws;
         }
+        rt += base;
         return large;
     }
     __device__ __forceinline__ void decode(ArgSched &s, const SchedLds &l, const Items &q, int it, int p)
@@ -381,7 +417,7 @@ struct Worker {
     __device__ __forceinline__ bool next(ArgSched &s, SchedLds &l, int phases, ArgTiles &ct, int32_t *err)
     {
         Items q;
-        q.load<LARGE>(l, phases, ct);
+        q.load<LARGE, OWN>(l, phases, ct);
         int it = pending, p;
         if (first >= 0 || it >= 0) {
             if (first >= 0) it = first;
@@ -408,7 +444,7 @@ struct Worker {
         down = p != 0;
         if (p && phases == 3 && !all_done) {
             if (fresh_tid() < 64) {
-                const int r = wait_or_help(s, q, rti, err);
+                const int r = wait_or_help(s, l, q, rti, err);
                 if (fresh_tid() == 0) l.wait = r;
             }
             __syncthreads();
@@ -456,12 +492,16 @@ struct Worker {
         have = pending < 0;
         if (have && fresh_tid() < 64) {
             Items q;
-            q.load<LARGE>(l, phases, ct);
+            q.load<LARGE, OWN>(l, phases, ct);
             take_next(s, l, q);
         }
         if (!down) __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
         __syncthreads();
-        if (!down && fresh_tid() == 0) agent_add(&s.dep[rti * kDepStride], 1);
+        if (!down && fresh_tid() == 0) {
+            int c = rti;
+            if (OWN && l.hdr[4] != 0) c = l.rt[c].w;   // (at most kSchedLdsTiles row tiles then)
+            agent_add(&s.dep[c * kDepStride], 1);
+        }
     }
 };
 

@@ -15,8 +15,8 @@
 //    tiles) of both products in one launch, from the lists of ffn_sched.h: a
 //    down item starts once the gate/up tiles of its rows are written, so no
 //    idle last round and no launch gap lies between the products (T = 32768,
-//    d = 7168, f = 2048, 8 experts, with dispatch and combine: 514 -> 491 us;
-//    T = 2049: 133 -> 129).  Row tiles are rastered in bands of up to 8 so that each weight
+//    d = 7168, f = 2048, 8 experts, with dispatch and combine: 539 -> 497 us;
+//    T = 2049: 132 -> 128).  Row tiles are rastered in bands of up to 8 so that each weight
 //    panel is read by one XCD;
 //  * the product is formed transposed, D[feature][token] = W X^T: the
 //    weights are the MFMA's row operand and the tokens its column operand,
@@ -394,7 +394,7 @@ void k_ffn_fp8(FfnArgs)
                            {lds_w2, lds_x2, (float *)(lds_x2 + kXBytes)}};
 
     int tid = threadIdx.x;
-    Worker<true> wk;
+    Worker<true, false> wk;
     if (tid == 192) {                     // the layer's weights, while begin() loads
         const void *W1 = args->p1.W, *W2 = args->p2.W;
         const float *S1 = args->p1.Ws, *S2 = args->p2.Ws;

@@ -15,7 +15,8 @@ namespace moe {
 // product; 0: every group is large), and the smallest and largest height of a
 // large row tile in 32-row blocks.
 struct SchedPlan {
-    int32_t grid, nt_large, nt_small;
+    int32_t grid, nt_large, nt_small;   // workgroups; column tiles of gate/up
+    int32_t nt_down;                    // column tiles of down (large)
     int32_t small_rows, small_rows_down;
     int32_t min_blocks, max_blocks;
 };

@@ -450,7 +450,8 @@ static int ffn_grid(int cus)
 static SchedPlan sched_plan(const moe_stage *st, int cus)
 {
     const int n1 = 2 * st->desc.d_ff;
-    SchedPlan p{ffn_grid(cus), (n1 + 255) / 256, (n1 + 127) / 128, kSmallRows, kSmallRowsDown, 2, kTileBlocks};
+    SchedPlan p{ffn_grid(cus), (n1 + 255) / 256, (n1 + 127) / 128, (st->desc.d_model + 255) / 256,
+                kSmallRows, kSmallRowsDown, 2, kTileBlocks};
     if (st->desc.dtype == MOE_DTYPE_FP8_E4M3_B128) {   // every group in the fp8 kernel's tiles
         p.small_rows = p.small_rows_down = 0;
         p.min_blocks = p.max_blocks = kTileBlocksFp8;

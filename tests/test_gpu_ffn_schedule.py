@@ -66,6 +66,40 @@ def test_group_sizes_at_the_tiles_edges(name, dtype):
     assert err.max() <= (FP8_TOL if dtype == "fp8" else BF16_TOL), (int(err.argmax()), err.max())
 
 
+@pytest.mark.parametrize("counts", [(193, 255, 256, 257, 288, 289, 319, 320), (200, 0, 260, 320, 193, 224, 225, 0, 310),
+                                    (257, 256, 321, 255, 260, 250, 240, 230), (257, 256, 192, 255, 260, 250, 240, 230),
+                                    (320,) * 8, (193,) * 8])
+def test_down_product_with_row_tiles_of_its_own(counts):
+    """Groups that the gate/up product splits to fill one round (f: 16 column
+    tiles) and the down product (28 column tiles) takes whole; and the same
+    with one group too tall, or one small, where it does not.  Run twice, bits
+    compared: the second pass uses the counters that the first left."""
+    counts = np.asarray(counts, np.int32)
+    n = int(counts.sum())
+    cfg = inputs.MoEConfig("own", d=7168, f=2048, E=16, e0=0, E_loc=len(counts), k=1, lengths=(n,), dtype="bf16", seed=95)
+    log("counts %s" % (counts.tolist(),))
+    wts = inputs.make_weights(cfg, "cuda")
+    x = inputs.make_microbatches(cfg, "cuda")[0].x
+    ys = [torch.full((n, cfg.d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    with ExpertStage(cfg, wts, max_tokens=n) as st:
+        for y in ys:
+            st.expert_ffn_grouped(0, x, torch.from_numpy(counts).to("cuda"), y)
+            st.sync()
+    assert torch.equal(ys[0], ys[1])
+    # every 5th row of each group (and its last) against fp32 products of the same
+    # bf16 values: h and y are each rounded to bf16, as in the other bounds
+    r0 = 0
+    for g, c in enumerate(counts.tolist()):
+        if c:
+            pick = torch.tensor(sorted(set(range(0, c, 5)) | {c - 1}), device="cuda") + r0
+            xr = x[pick].float()
+            h = torch.nn.functional.silu(xr @ wts.w_gate[g].float().T) * (xr @ wts.w_up[g].float().T)
+            ref = (h.to(torch.bfloat16).float() @ wts.w_down[g].float().T).double().cpu().numpy()
+            err = row_rel_l2(ys[0][pick].double().cpu().numpy(), ref)
+            assert np.all(err <= BF16_TOL), (g, c, err.max())
+        r0 += c
+
+
 @pytest.mark.parametrize("E,e0,E_loc,k,T", [(5, 2, 1, 3, 700), (9, 0, 3, 4, 1100), (70, 5, 33, 8, 900),
                                             (300, 40, 200, 8, 1500), (2, 0, 2, 2, 65)])
 def test_placement_with_any_number_of_local_experts(E, e0, E_loc, k, T):
