@@ -25,9 +25,10 @@ struct SlotWs {
     Sched sched{};
     // The schedule's counters are as the dispatch left them: an FFN pass takes
     // the work they count out, and a second one on the same dispatch has to
-    // clear them first.  Once a pass of this slot was captured in a graph the
-    // host no longer knows, and every pass that no dispatch precedes in its
-    // own call clears them.
+    // clear them first.  Once any call on this slot was captured in a graph the
+    // host no longer knows (a captured call has not run, and a replay runs it
+    // unseen), and every pass that no dispatch precedes in its own call clears
+    // them.
     bool sched_fresh = false, captured = false;
     GroupTable tables() const { return GroupTable{g_row0, g_rows}; }
     int32_t *slot_of_row = nullptr, *row_of_slot = nullptr;
@@ -459,6 +460,16 @@ static SchedPlan sched_plan(const moe_stage *st, int cus)
     return p;
 }
 
+// Whether calls on `s` are being captured, marked in the slot.
+static bool note_capture(SlotWs &sl, hipStream_t s)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess) (void)hipGetLastError();
+    if (cs == hipStreamCaptureStatusNone) return false;
+    sl.captured = true;
+    return true;
+}
+
 // The three phases.  `rec` records the slot's event at the end; a submit
 // records it once, after the combine, since every record is a release that
 // stalls the stream for several microseconds.
@@ -489,7 +500,7 @@ static moe_status dispatch_impl(moe_stage *st, int32_t slot, const moe_microbatc
     a.groups = sl.tables();
     a.sched = sl.sched;
     a.plan = sched_plan(st, stream_cus(st, s));
-    sl.sched_fresh = true;
+    const bool captured = note_capture(sl, s);
     a.slot_of_row = sl.slot_of_row;
     a.row_of_slot = sl.row_of_slot;
     a.err = st->err;
@@ -497,6 +508,7 @@ static moe_status dispatch_impl(moe_stage *st, int32_t slot, const moe_microbatc
         ProfScope ps(st, 0, s);
         if (launch_dispatch_index(a, s) != hipSuccess) return MOE_EHIP;
     }
+    if (!captured) sl.sched_fresh = true;
     // The gate/up GEMM reads the token rows of x through slot_of_row; fp8
     // gathers the rows' scales (transposed) for it.
     const int64_t max_rows = (int64_t)T * d.top_k;
@@ -537,9 +549,7 @@ static moe_status launch_ffn(moe_stage *st, SlotWs &sl, const FfnPass &f, bool a
     const int cus = stream_cus(st, s);
     hipError_t e = hipSuccess;
     if (!after_dispatch) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &cs) != hipSuccess) (void)hipGetLastError();
-        sl.captured |= cs != hipStreamCaptureStatusNone;
+        note_capture(sl, s);
         if ((!sl.sched_fresh || sl.captured) && launch_reset_schedule(sl.sched, s) != hipSuccess)
             return MOE_EHIP;
     }
@@ -623,6 +633,7 @@ static moe_status ffn_grouped_impl(moe_stage *st, int32_t slot, const moe_groupe
     SlotWs &sl = st->slots[slot];
     sl.has_mb = false;               // nothing in this slot to combine
     if (n == 0) return record(sl, s);
+    note_capture(sl, s);
     const GroupTable gt = sl.tables();
     {
         ProfScope ps(st, 0, s);

@@ -216,6 +216,47 @@ def test_captured_pass_replays(dtype, whole):
         st.sync()
 
 
+@pytest.mark.parametrize("captured", ["dispatch", "submit"])
+def test_second_pass_after_a_capture_on_its_slot(captured):
+    """moe_expert_ffn on a dispatch whose counters are used up although the
+    calls before it look as if they were not: a dispatch that was captured but
+    not replayed came after the pass that used them, or a replayed submit of
+    the slot did.  The token rows change in between: it computes them again."""
+    cfg, wts, ow, mb, ids, w, out, x, xs = _setup("bf16", 85)
+    with ExpertStage(cfg, wts) as st:
+        m = st.microbatch(x, ids, w, out, xs)
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        g = torch.cuda.CUDAGraph()
+        if captured == "submit":
+            with torch.cuda.graph(g, stream=s):
+                st.submit(m)
+        with torch.cuda.stream(s):
+            st.dispatch(0, m)
+            if captured == "dispatch":
+                st.expert_ffn(0)
+                st.combine(0)
+        s.synchronize()
+        if captured == "dispatch":
+            with torch.cuda.graph(g, stream=s):
+                st.dispatch(0, m)
+        else:
+            with torch.cuda.stream(s):
+                g.replay()
+            s.synchronize()
+        _check(cfg, ow, mb, out, "first pass")
+        x.copy_(x.flip(0))
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            st.expert_ffn(0)
+            st.combine(0)
+        s.synchronize()
+        st.sync()
+    mb.x = x
+    _check(cfg, ow, mb, out, "second pass")
+
+
 def test_grids_of_a_few_workgroups():
     """Streams of 16 and of 32 compute units: lists of two and of four
     workgroups, so nearly every item comes from a ticket.  In a child process:
