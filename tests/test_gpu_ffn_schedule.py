@@ -73,7 +73,7 @@ def test_down_product_with_row_tiles_of_its_own(counts):
     """Groups that the gate/up product splits to fill one round (f: 16 column
     tiles) and the down product (28 column tiles) takes whole; and the same
     with one group too tall, or one small, where it does not.  Run twice, bits
-    compared: the second pass uses the counters that the first left."""
+    compared (each call builds its row tiles and counters anew)."""
     counts = np.asarray(counts, np.int32)
     n = int(counts.sum())
     cfg = inputs.MoEConfig("own", d=7168, f=2048, E=16, e0=0, E_loc=len(counts), k=1, lengths=(n,), dtype="bf16", seed=95)
@@ -255,6 +255,47 @@ def test_second_pass_after_a_capture_on_its_slot(captured):
         st.sync()
     mb.x = x
     _check(cfg, ow, mb, out, "second pass")
+
+
+def test_second_pass_with_row_tiles_of_the_down_product():
+    """moe_expert_ffn twice after one moe_dispatch of groups that the down
+    product takes whole and the gate/up product splits: the second pass finds
+    the counters cleared, those kept per group included."""
+    T = 2100                                             # about 262 rows an expert
+    cfg = inputs.MoEConfig("own2", d=7168, f=2048, E=8, e0=0, E_loc=8, k=1, lengths=(T,), dtype="bf16", seed=97)
+    wts = inputs.make_weights(cfg, "cuda")
+    mb = inputs.make_microbatches(cfg, "cuda")[0]
+    ids, w = to_device_routing(mb.ids, mb.w)
+    outs = [torch.full((T, cfg.d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    x = mb.x.clone()
+    with ExpertStage(cfg, wts) as st:
+        st.dispatch(0, st.microbatch(x, ids, w, outs[0]))
+        view = st.view(0, rows=False)
+        rows = np.diff(view["offsets"])
+        assert rows.min() > 192 and rows.max() <= 320, rows
+        st.expert_ffn(0)
+        st.combine(0)
+        torch.cuda.synchronize()
+        outs[1].copy_(outs[0])
+        x.copy_(x.flip(0))
+        outs[0].fill_(float("nan"))
+        st.expert_ffn(0)
+        st.combine(0)
+        torch.cuda.synchronize()
+        outs[2].copy_(outs[0])
+        st.sync()
+    # every 7th token against fp32 products of the same bf16 values
+    pick = torch.arange(0, T, 7, device="cuda")
+    for rows_in, out in ((mb.x, outs[1]), (x, outs[2])):
+        xr = rows_in[pick].float()
+        ref = torch.zeros((len(pick), cfg.d), device="cuda")
+        for e in range(cfg.E_loc):
+            at = (ids[pick, 0] == e).nonzero()[:, 0]
+            h = torch.nn.functional.silu(xr[at] @ wts.w_gate[e].float().T) * (xr[at] @ wts.w_up[e].float().T)
+            y = (h.to(torch.bfloat16).float() @ wts.w_down[e].float().T).to(torch.bfloat16).float()
+            ref[at] = y * w[pick][at]
+        err = row_rel_l2(out[pick].double().cpu().numpy(), ref.double().cpu().numpy())
+        assert np.all(err <= BF16_TOL), err.max()
 
 
 def test_grids_of_a_few_workgroups():
