@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bounds.h"
+
 namespace moe {
 
 typedef __bf16 bf16;

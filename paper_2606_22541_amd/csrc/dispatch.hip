@@ -430,16 +430,21 @@ void k_group_tables_from_counts(const int32_t *__restrict__ counts, int32_t E_lo
         int carry = 0, bad = 0;
         for (int c0 = 0; c0 < E_loc; c0 += 64) {
             const int i = c0 + lane;
-            int c = i < E_loc ? counts[i] : 0;
-            bad |= c < 0;
-            c = c < 0 ? 0 : c;
-            int t;
-            const int before = carry + wave_excl_scan(c, lane, t);
+            const int c = i < E_loc ? counts[i] : 0, asked = rows_asked(c, n_rows_max);
+            // sums capped at n_rows_max, so that no counts can wrap them
+            int x = asked;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(x, o);
+                if (lane >= o) x = add_capped(x, y, n_rows_max);
+            }
+            const int y = __shfl_up(x, 1);
+            const int before = add_capped(carry, lane ? y : 0, n_rows_max);
             // rows past n_rows_max are dropped: the group keeps what fits
-            const int keep = min(c, max(0, n_rows_max - before));
+            const int keep = rows_kept(asked, before, n_rows_max);
             bad |= keep != c;
             if (i < E_loc) tot[i] = keep;
-            carry += t;
+            carry = add_capped(carry, __shfl(x, 63), n_rows_max);
         }
         if (__any(bad) && lane == 0) atomicOr(err, kErrBadCount);
     }

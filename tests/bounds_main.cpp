@@ -1,0 +1,49 @@
+/*
+ * Test driver: the arithmetic of csrc/bounds.h on the host, built by
+ * tests/test_bounds_cpu.py with the undefined-behaviour sanitizer.  CPU-only
+ * test infrastructure.
+ *
+ * "counts": stdin n_rows_max, E_loc, E_loc counts; stdout the rows that each
+ * group keeps and whether any count was changed.  The lanes of a wave take the
+ * steps of the device's scan one after the other.
+ */
+#include <cstdio>
+#include <cstring>
+
+#include "bounds.h"
+
+using namespace moe;
+
+static int counts()
+{
+    int cap, n;
+    if (std::scanf("%d %d", &cap, &n) != 2 || n < 0 || n > 256) return 2;
+    int32_t carry = 0;
+    bool bad = false;
+    for (int c0 = 0; c0 < n; c0 += 64) {
+        int32_t c[64] = {}, asked[64], x[64], y[64];
+        for (int l = 0; l < 64; ++l) {
+            if (c0 + l < n && std::scanf("%d", &c[l]) != 1) return 2;
+            x[l] = asked[l] = rows_asked(c[l], cap);
+        }
+        for (int o = 1; o < 64; o <<= 1) {
+            std::memcpy(y, x, sizeof x);
+            for (int l = o; l < 64; ++l) x[l] = add_capped(x[l], y[l - o], cap);
+        }
+        for (int l = 0; l < 64 && c0 + l < n; ++l) {
+            const int32_t keep = rows_kept(asked[l], add_capped(carry, l ? x[l - 1] : 0, cap), cap);
+            bad |= keep != c[l];
+            std::printf("%d ", keep);
+        }
+        carry = add_capped(carry, x[63], cap);
+    }
+    std::printf("%d\n", (int)bad);
+    return 0;
+}
+
+int main(int argc, char **argv)
+{
+    if (argc < 2) return 2;
+    if (!std::strcmp(argv[1], "counts")) return counts();
+    return 2;
+}

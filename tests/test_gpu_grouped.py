@@ -136,6 +136,30 @@ def test_bad_counts_are_clamped_and_reported():
     _check_rows(bf16_bits(y), ref["y"], kept, BF16_TOL, "clamped")
 
 
+@pytest.mark.parametrize("counts", [(2**31 - 1,) * 6, (40, 2**31 - 1, 2**31 - 1, 2**31 - 1, 5, 2**31 - 1),
+                                    (0, 100, -2**31, 2**31 - 1, 2**31 - 1, 2**31 - 1)])
+def test_counts_whose_sum_passes_32_bits(counts):
+    """Running totals past 2^31 leave every group inside the buffer: the rows
+    past it stay as they were."""
+    cfg = _cfg("bf16", 55)
+    wts = inputs.make_weights(cfg, "cuda")
+    ow = oracle.OracleWeights(wts, "bf16")
+    n = 300
+    x = np.random.default_rng(55).standard_normal((n, cfg.d)).astype(np.float32)
+    rows = torch.from_numpy(x).to("cuda").to(torch.bfloat16)
+    kept = oracle.grouped_counts(counts, n)
+    ref = oracle.run_grouped(cfg, ow, bits_to_f64(bf16_bits(rows)), np.asarray(counts, np.int64))
+    y = _y_buffer(cfg, n + SPARE)
+    log("grouped: counts %s" % (counts,))
+    with ExpertStage(cfg, wts, n_slots=1, max_tokens=cfg.lengths[0]) as st:
+        st.expert_ffn_grouped(0, rows, torch.tensor(counts, dtype=torch.int32, device="cuda"), y[:n])
+        with pytest.raises(C.MoEStageError) as e:
+            st.sync()
+        assert e.value.status == C.MOE_EBADCOUNT
+        torch.cuda.synchronize()
+    _check_rows(bf16_bits(y), ref["y"], kept, BF16_TOL, "counts near 2^31")
+
+
 def test_grouped_layer_and_empty_and_host_errors():
     cfg = _cfg("bf16", 53, E_loc=4)
     layers = [inputs.make_weights(inputs.scaled(cfg, seed=200 + l), "cuda") for l in range(2)]
