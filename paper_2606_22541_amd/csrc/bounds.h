@@ -22,4 +22,16 @@ constexpr int32_t rows_kept(int32_t asked, int32_t before, int32_t cap)
     return asked < cap - before ? asked : cap - before;
 }
 
+// A tile addresses its rows of activations and of outputs, `cols` elements
+// each, with 32-bit byte offsets: the 32-row blocks that a bf16 tile of up to
+// `most` may have, and whether the kernels take rows of that length at all
+// (in tiles of kLeastBlocks blocks).
+constexpr int kLeastBlocks = 8;
+constexpr bool tile_fits(int blocks, int64_t cols) { return 32 * blocks * cols * 2 < (int64_t)1 << 31; }
+constexpr int tile_blocks(int most, int64_t cols)
+{
+    while (most > kLeastBlocks && !tile_fits(most, cols)) --most;
+    return most;
+}
+
 }  // namespace moe

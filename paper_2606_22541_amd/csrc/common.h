@@ -60,6 +60,7 @@ constexpr int kSmallRows = 192;
 // with small down tiles up to 128 rows the pass at T = 4096 took 187 us instead
 // of 180, up to 192 rows 213.
 constexpr int kSmallRowsDown = 64;
+static_assert(kSmallRows <= 32 * kLeastBlocks && kTileBlocksFp8 <= kLeastBlocks, "every tile's offsets fit");
 
 // Device-side tables of the groups, written by the dispatch, read by the GEMMs.
 struct GroupTable {

@@ -82,8 +82,7 @@ bool desc_ok(const moe_stage_desc *d)
     if (d->n_layers < 1 || d->n_layers > kMaxLayers) return false;
     // 32-bit slot and row indices; 32-bit byte offsets inside one GEMM tile
     if ((int64_t)d->max_tokens * d->top_k >= (int64_t)1 << 31) return false;
-    if ((int64_t)256 * d->d_model * 2 >= (int64_t)1 << 31) return false;
-    if ((int64_t)256 * d->d_ff * 2 >= (int64_t)1 << 31) return false;
+    if (!tile_fits(kLeastBlocks, d->d_model) || !tile_fits(kLeastBlocks, d->d_ff)) return false;
     // the bf16 gate/up GEMM addresses token rows of x with 32-bit byte offsets
     if ((int64_t)d->max_tokens * d->d_model * 2 >= (int64_t)1 << 31) return false;
     return true;
@@ -452,7 +451,8 @@ static SchedPlan sched_plan(const moe_stage *st, int cus)
 {
     const int n1 = 2 * st->desc.d_ff;
     SchedPlan p{ffn_grid(cus), (n1 + 255) / 256, (n1 + 127) / 128, (st->desc.d_model + 255) / 256,
-                kSmallRows, kSmallRowsDown, 2, kTileBlocks};
+                kSmallRows, kSmallRowsDown, 2,
+                tile_blocks(kTileBlocks, st->desc.d_model > st->desc.d_ff ? st->desc.d_model : st->desc.d_ff)};
     if (st->desc.dtype == MOE_DTYPE_FP8_E4M3_B128) {   // every group in the fp8 kernel's tiles
         p.small_rows = p.small_rows_down = 0;
         p.min_blocks = p.max_blocks = kTileBlocksFp8;

@@ -41,9 +41,26 @@ static int counts()
     return 0;
 }
 
+/* "blocks": stdin n, then n pairs of blocks and columns; stdout per pair the
+ * blocks that a tile may have, and whether such rows are taken at all. */
+static int blocks()
+{
+    int n;
+    if (std::scanf("%d", &n) != 1) return 2;
+    for (; n > 0; --n) {
+        int most;
+        long long cols;
+        if (std::scanf("%d %lld", &most, &cols) != 2) return 2;
+        std::printf("%d %d ", tile_blocks(most, cols), (int)tile_fits(kLeastBlocks, cols));
+    }
+    std::printf("\n");
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc < 2) return 2;
     if (!std::strcmp(argv[1], "counts")) return counts();
+    if (!std::strcmp(argv[1], "blocks")) return blocks();
     return 2;
 }

@@ -61,3 +61,32 @@ def test_grouped_counts_of_any_value(driver):
         counts = [c if rng.random() < 0.5 else 0 for c in counts]
         got = _run(driver, "counts", n, len(counts), *counts)
         assert got[:-1] == oracle.grouped_counts(counts, n).tolist()
+
+
+def test_tile_offsets_fit_32_bits(driver):
+    """Every row length that the stage takes (256 rows of it fit) gets tiles
+    whose rows' byte offsets fit, and the largest such up to the tiles' own
+    limit of 10 blocks."""
+    edge = [(2**31 - 1) // (64 * b) for b in (8, 9, 10)]
+    cols = sorted({128, 7168, 2**21} | {e // 128 * 128 + 128 * j for e in edge for j in (-1, 0, 1)})
+    got = _run(driver, "blocks", len(cols), *[v for c in cols for v in (10, c)])
+    for c, blocks, taken in zip(cols, got[::2], got[1::2]):
+        assert taken == int(256 * c * 2 < 2**31), c
+        if taken:
+            assert 32 * blocks * c * 2 < 2**31, (c, blocks)
+            assert blocks == 10 or 32 * (blocks + 1) * c * 2 >= 2**31, (c, blocks)
+
+
+def test_descriptors_are_taken_up_to_the_least_tile():
+    """Row lengths on both sides of what the least tile can address are
+    accepted and refused by the library (host only)."""
+    from paper_2606_22541_amd import moe_stage as C
+    for cols, ok in ((4194176, True), (4194304, False), (3355392, True), (3355520, True)):
+        for d, f in ((cols, 128), (128, cols)):
+            desc = C.make_desc(d, f, 8, 0, 1, 2, 160, n_slots=1)
+            if ok:
+                assert C.moe_stage_workspace_bytes(desc) > 0
+            else:
+                with pytest.raises(C.MoEStageError) as e:
+                    C.moe_stage_workspace_bytes(desc)
+                assert e.value.status == C.MOE_EINVAL

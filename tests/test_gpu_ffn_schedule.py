@@ -100,6 +100,32 @@ def test_down_product_with_row_tiles_of_its_own(counts):
         r0 += c
 
 
+@pytest.mark.parametrize("d,f", [(4000000, 128), (128, 4000000)])
+def test_rows_so_long_that_tiles_are_lower(d, f):
+    """320 rows of 4,000,000 elements pass 2^31 bytes, so the tiles of such
+    rows have 256 at most: every row and column is written."""
+    n = 320
+    cfg = inputs.MoEConfig("long", d=d, f=f, E=2, e0=0, E_loc=1, k=2, lengths=(n // 2,), dtype="bf16", seed=99)
+    log("d %d f %d" % (d, f))
+    wts = inputs.make_weights(cfg, "cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(99)
+    x = torch.randn((n, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    y = torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    with ExpertStage(cfg, wts, max_tokens=n // 2) as st:
+        st.expert_ffn_grouped(0, x, torch.tensor([n], dtype=torch.int32, device="cuda"), y)
+        st.sync()
+    # fp32 products of the same bf16 values, rows from every block
+    pick = torch.tensor([0, 31, 32, 159, 160, 255, 256, 267, 268, 300, 319], device="cuda")
+    xr = x[pick].float()
+    h = torch.nn.functional.silu(xr @ wts.w_gate[0].float().T) * (xr @ wts.w_up[0].float().T)
+    ref = h.to(torch.bfloat16).float() @ wts.w_down[0].float().T
+    got = y[pick].float()
+    assert torch.isfinite(y).all()
+    err = (torch.linalg.vector_norm(got - ref, dim=1) / torch.linalg.vector_norm(ref, dim=1)).cpu().numpy()
+    assert np.all(err <= BF16_TOL), err
+
+
 @pytest.mark.parametrize("E,e0,E_loc,k,T", [(5, 2, 1, 3, 700), (9, 0, 3, 4, 1100), (70, 5, 33, 8, 900),
                                             (300, 40, 200, 8, 1500), (2, 0, 2, 2, 65)])
 def test_placement_with_any_number_of_local_experts(E, e0, E_loc, k, T):
