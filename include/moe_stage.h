@@ -327,11 +327,11 @@ MOE_API moe_status moe_stream_destroy(void *stream);
 MOE_API moe_status moe_stage_query(moe_stage *stage, int32_t slot, moe_dispatch_view *out);
 
 /* Waits until every slot's enqueued work has completed and returns (then
- * clears) the sticky device errors: MOE_EBADID if a kernel saw an invalid
- * expert id since the last sync, else MOE_EBADLAYER if one saw an invalid
- * layer id, else MOE_EBADCOUNT if one saw invalid pre-grouped counts, else
- * MOE_ETIMEOUT if an ingest wait gave up, else MOE_OK (or MOE_EHIP: a HIP
- * call failed, or an FFN pass gave up waiting for its own rows). */
+ * clears) the sticky device errors: MOE_EHIP if an FFN pass since the last
+ * sync gave up waiting for its own rows, else MOE_EBADID if a kernel saw an
+ * invalid expert id, else MOE_EBADLAYER if one saw an invalid layer id, else
+ * MOE_EBADCOUNT if one saw invalid pre-grouped counts, else MOE_ETIMEOUT if an
+ * ingest wait gave up, else MOE_OK.  MOE_EHIP also if a HIP call failed. */
 MOE_API moe_status moe_stage_sync(moe_stage *stage);
 
 /* Per-kernel timing with HIP events, for measurement (off by default).

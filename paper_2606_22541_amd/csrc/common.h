@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "bounds.h"
+#include "errors.h"
 
 namespace moe {
 
@@ -39,13 +40,6 @@ constexpr int kBandFp8 = 8;
 // Cache-policy operand of the raw buffer loads: non-temporal (streaming)
 // data, read once, evicted first and kept out of the last-level cache.
 constexpr int kNonTemporal = 2;
-
-// Sticky error bits.
-constexpr int kErrBadId = 1;
-constexpr int kErrBadLayer = 2;
-constexpr int kErrIngestTimeout = 4;
-constexpr int kErrBadCount = 8;       // pre-grouped counts negative or past the rows buffer
-constexpr int kErrStalled = 16;       // a work item's inputs never became ready (ffn_sched.h)
 
 // Groups with at most this many rows ("small": an EP32 share at T = 4096 has
 // ~128 rows per expert) take one tile of all their rows and 128 columns in the

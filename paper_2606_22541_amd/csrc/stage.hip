@@ -857,11 +857,7 @@ moe_status moe_stage_sync(moe_stage *st)
         if (hipMemsetAsync(st->err, 0, 4, st->own) != hipSuccess ||
             hipStreamSynchronize(st->own) != hipSuccess)
             return MOE_EHIP;
-        return (err & kErrBadId)      ? MOE_EBADID
-               : (err & kErrBadLayer) ? MOE_EBADLAYER
-               : (err & kErrBadCount) ? MOE_EBADCOUNT
-               : (err & kErrStalled)  ? MOE_EHIP
-                                      : MOE_ETIMEOUT;
+        return sticky_status(err);
     }
     return MOE_OK;
 }

@@ -28,8 +28,8 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 _FFN_BF16 = ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/ffn_bf16.h", "csrc/ffn_sched.h",
-             "csrc/common.h", "csrc/bounds.h", "csrc/kernels.h"]
-_FFN_FP8 = ["csrc/gemm_fp8.hip", "csrc/ffn_sched.h", "csrc/common.h", "csrc/bounds.h", "csrc/kernels.h"]
+             "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
+_FFN_FP8 = ["csrc/gemm_fp8.hip", "csrc/ffn_sched.h", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
 # "ffn": the launch of both products; the gemm groups: its two halves, which
 # run as launches of their own while a stage's profiling is on
 KERNEL_SOURCES = {
@@ -39,9 +39,9 @@ KERNEL_SOURCES = {
     "gemm_down": _FFN_BF16,
     "gemm_gate_up_swiglu_fp8": _FFN_FP8,
     "gemm_down_fp8": _FFN_FP8,
-    "combine": ["csrc/combine.hip", "csrc/common.h", "csrc/bounds.h", "csrc/kernels.h"],
-    "gather": ["csrc/dispatch.hip", "csrc/common.h", "csrc/bounds.h", "csrc/kernels.h"],
-    "dispatch_index": ["csrc/dispatch.hip", "csrc/common.h", "csrc/bounds.h", "csrc/kernels.h"],
+    "combine": ["csrc/combine.hip", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"],
+    "gather": ["csrc/dispatch.hip", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"],
+    "dispatch_index": ["csrc/dispatch.hip", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"],
 }
 # rocprof kernel-name prefixes of the stage's kernels -> the kernel groups
 # bench.py times (a group's kernels each run once per micro-batch, so a

@@ -1,5 +1,5 @@
 /*
- * Test driver: the arithmetic of csrc/bounds.h on the host, built by
+ * Test driver: the arithmetic of csrc/bounds.h and csrc/errors.h on the host, built by
  * tests/test_bounds_cpu.py with the undefined-behaviour sanitizer.  CPU-only
  * test infrastructure.
  *
@@ -11,6 +11,7 @@
 #include <cstring>
 
 #include "bounds.h"
+#include "errors.h"
 
 using namespace moe;
 
@@ -57,10 +58,21 @@ static int blocks()
     return 0;
 }
 
+/* "status": stdin n, then n values of the error word; stdout their statuses. */
+static int status()
+{
+    int n, err;
+    if (std::scanf("%d", &n) != 1) return 2;
+    for (; n > 0 && std::scanf("%d", &err) == 1; --n) std::printf("%d ", (int)sticky_status(err));
+    std::printf("\n");
+    return n;
+}
+
 int main(int argc, char **argv)
 {
     if (argc < 2) return 2;
     if (!std::strcmp(argv[1], "counts")) return counts();
     if (!std::strcmp(argv[1], "blocks")) return blocks();
+    if (!std::strcmp(argv[1], "status")) return status();
     return 2;
 }

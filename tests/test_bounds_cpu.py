@@ -1,5 +1,6 @@
 """The plain arithmetic of ``csrc/bounds.h``, which keeps row and tile indices
-inside their buffers, compiled with g++ and run on the host."""
+inside their buffers, and of ``csrc/errors.h``, compiled with g++ and run on the
+host."""
 import os
 import shutil
 import subprocess
@@ -9,6 +10,7 @@ import pytest
 
 import oracle
 from paper_2606_22541_amd import build
+from paper_2606_22541_amd import moe_stage as C
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 BIG = 2**31 - 1
@@ -20,7 +22,7 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not ava
 def driver(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("bounds") / "bounds")
     cmd = ["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all",
-           "-I", build.CSRC, os.path.join(HERE, "bounds_main.cpp"), "-o", exe]
+           "-I", build.CSRC, "-I", build.INCLUDE, os.path.join(HERE, "bounds_main.cpp"), "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0 and "sanitize" in r.stderr:
         pytest.skip("sanitizer runtime not available: " + r.stderr[-300:])
@@ -80,7 +82,6 @@ def test_tile_offsets_fit_32_bits(driver):
 def test_descriptors_are_taken_up_to_the_least_tile():
     """Row lengths on both sides of what the least tile can address are
     accepted and refused by the library (host only)."""
-    from paper_2606_22541_amd import moe_stage as C
     for cols, ok in ((4194176, True), (4194304, False), (3355392, True), (3355520, True)):
         for d, f in ((cols, 128), (128, cols)):
             desc = C.make_desc(d, f, 8, 0, 1, 2, 160, n_slots=1)
@@ -90,3 +91,12 @@ def test_descriptors_are_taken_up_to_the_least_tile():
                 with pytest.raises(C.MoEStageError) as e:
                     C.moe_stage_workspace_bytes(desc)
                 assert e.value.status == C.MOE_EINVAL
+
+
+def test_a_stalled_pass_is_reported_before_any_other_error(driver):
+    """All bits of the error word are cleared together, so the one that says
+    that rows are wrong through no fault of the caller must not be hidden."""
+    words = list(range(32))
+    order = ((16, C.MOE_EHIP), (1, C.MOE_EBADID), (2, C.MOE_EBADLAYER), (8, C.MOE_EBADCOUNT), (4, C.MOE_ETIMEOUT))
+    want = [next((s for bit, s in order if w & bit), C.MOE_OK) for w in words]
+    assert _run(driver, "status", len(words), *words) == want
