@@ -16,11 +16,12 @@
 //
 // Lists.  Workgroups are placed round-robin on the 8 XCDs, so the items of a
 // product are dealt to 8 lists in runs of P / 8 consecutive items (P = the
-// grid), one list per XCD: the workgroups of an XCD take them in order.  The
-// first P / 8 gate/up items of a list are fixed, one per workgroup (no ticket
-// has to come back before the first loads); later items are taken with an
-// atomic ticket per list, requested while the previous item runs.  A
-// workgroup whose list is empty takes from the others'.
+// grid), one list per XCD: the workgroups of an XCD take them in order.  Fewer
+// items than workgroups are dealt evenly all the same, so that the weights come
+// through every XCD (deal.h).  The first run of a list's gate/up items is fixed,
+// one per workgroup (no ticket has to come back before the first loads); later
+// items are taken with an atomic ticket per list, requested while the previous
+// item runs.  A workgroup whose list is empty takes from the others'.
 //
 // A down item waits until every gate/up tile of its rows is written (a count
 // per row tile, each on a line of its own: polled on a shared line the waits
@@ -35,14 +36,13 @@
 #pragma once
 
 #include "common.h"
+#include "deal.h"
 
 namespace moe {
 
 constexpr int kMaxSchedCus = 512;     // workgroups of one launch
 constexpr int kTickStride = 32;       // ints between ticket counters (128 bytes)
 constexpr int kDepStride = 32;        // ints between row tiles' counts of written tiles
-constexpr int kListsLog2 = 3;
-constexpr int kLists = 1 << kListsLog2;
 // Polls of one wait before it gives up (seconds; a wait takes microseconds).
 constexpr int kMaxPolls = 1 << 22;
 constexpr int kMaxReadyScan = 1024;   // row tiles that one wait looks over for "all are ready"
@@ -134,21 +134,15 @@ struct FfnTiles {
 typedef const __attribute__((address_space(4))) FfnTiles ArgTiles;
 
 // The items of a launch and how they are dealt to lists.
-struct Items {
-    int lg, C, x;              // log2 of the lists, workgroups per list, this workgroup's list
-    int C1;                    // run length of the down product's items
+struct Items : Deal {
+    int x;                     // this workgroup's list
     int nrt, nl0, nl1;         // row tiles, large ones of gate/up and of down
     int nrtd, sd;              // row tiles of down, the start of their table
     int ntl0, ntl1, nts0, nts1, band;
-    int total0, total1;
 
     template <bool LARGE, bool OWN>
     __device__ __forceinline__ void load(const SchedLds &l, int phases, ArgTiles &ct)
     {
-        const int P = gridDim.x;
-        lg = (P & (kLists - 1)) ? 0 : kListsLog2;
-        C = P >> lg;
-        x = blockIdx.x & ((1 << lg) - 1);
         nrt = __builtin_amdgcn_readfirstlane(l.hdr[0]);
         nl0 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[1]) : 0;
         nl1 = LARGE ? __builtin_amdgcn_readfirstlane(l.hdr[2]) : 0;
@@ -159,27 +153,9 @@ struct Items {
         nts0 = ct.nts[0];
         nts1 = ct.nts[1];
         band = ct.band;
-        const int g = nl0 * ntl0 + (nrt - nl0) * nts0, d = nl1 * ntl1 + (nrtd - nl1) * nts1;
-        total0 = (phases & 1) ? g : 0;
-        total1 = (phases & 2) ? d : 0;
-        // a list's down items are those of the row tiles that it did the
-        // gate/up items of (as far as runs of one length allow): they are ready
-        // when its own gate/up items are
-        C1 = max(1, (int)((float)C * (float)d / (float)max(g, 1) + 0.5f));
+        deal(gridDim.x, nl0 * ntl0 + (nrt - nl0) * nts0, nl1 * ntl1 + (nrtd - nl1) * nts1, phases);
         C1 = __builtin_amdgcn_readfirstlane(C1);
-    }
-    // Length of list y, and its j-th item, of product p: the items are dealt
-    // to the lists in runs of R.
-    __device__ __forceinline__ int len(int p, int y) const
-    {
-        const int R = p ? C1 : C, total = p ? total1 : total0;
-        const int full = total / (R << lg), rem = total - full * (R << lg);
-        return full * R + min(R, max(0, rem - y * R));
-    }
-    __device__ __forceinline__ int item(int j, int y, int p) const
-    {
-        const int R = p ? C1 : C, r = j / R;
-        return r * (R << lg) + y * R + (j - r * R);
+        x = blockIdx.x & ((1 << lg) - 1);
     }
     // gate/up tiles that the count of gate/up row tile rt comes to
     __device__ __forceinline__ int need(int rt) const { return rt < nl0 ? ntl0 : nts0; }
@@ -212,8 +188,8 @@ struct Worker {
         pending = -1;
         pre = -1;
         const int run = q.C << q.lg;
-        first = q.x * q.C + (b >> q.lg);
-        if (__builtin_amdgcn_readfirstlane(l.claimed) != 0 || first >= q.total0) first = -1;
+        first = q.fixed(b);
+        if (__builtin_amdgcn_readfirstlane(l.claimed) != 0) first = -1;
         have = false;
         if (tid == 0) l.stage = run + q.x * q.C < q.total0 ? 0 : 1;   // a second run of this list
         return q.total0 + q.total1 > 0;
@@ -354,7 +330,7 @@ struct Worker {
                 // ... and the fixed ones of workgroups that have not started
                 for (int b0 = 0; b0 < (int)gridDim.x; b0 += 64) {
                     const int b = b0 + lane;
-                    const bool idle = b < (int)gridDim.x && (b & (nx - 1)) * q.C + (b >> q.lg) < q.total0 &&
+                    const bool idle = b < (int)gridDim.x && q.fixed(b) >= 0 &&
                                       agent_load(&s.claim[min(b, (int)gridDim.x - 1)]) == 0;
                     const uint64_t c = __ballot(idle);
                     if (c) {
@@ -362,7 +338,7 @@ struct Worker {
                         int old = 0;
                         if (lane == 0) old = agent_swap(&s.claim[bb], 1);
                         old = __builtin_amdgcn_readfirstlane(old);
-                        if (old == 0) return (bb & (nx - 1)) * q.C + (bb >> q.lg);
+                        if (old == 0) return q.fixed(bb);
                     }
                 }
             }

@@ -27,9 +27,9 @@ import os
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-_FFN_BF16 = ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/ffn_bf16.h", "csrc/ffn_sched.h",
+_FFN_BF16 = ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/ffn_bf16.h", "csrc/ffn_sched.h", "csrc/deal.h",
              "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
-_FFN_FP8 = ["csrc/gemm_fp8.hip", "csrc/ffn_sched.h", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
+_FFN_FP8 = ["csrc/gemm_fp8.hip", "csrc/ffn_sched.h", "csrc/deal.h", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
 # "ffn": the launch of both products; the gemm groups: its two halves, which
 # run as launches of their own while a stage's profiling is on
 KERNEL_SOURCES = {

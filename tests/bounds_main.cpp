@@ -1,5 +1,5 @@
 /*
- * Test driver: the arithmetic of csrc/bounds.h and csrc/errors.h on the host, built by
+ * Test driver: the arithmetic of csrc/bounds.h, deal.h and errors.h on the host, built by
  * tests/test_bounds_cpu.py with the undefined-behaviour sanitizer.  CPU-only
  * test infrastructure.
  *
@@ -11,6 +11,7 @@
 #include <cstring>
 
 #include "bounds.h"
+#include "deal.h"
 #include "errors.h"
 
 using namespace moe;
@@ -68,11 +69,31 @@ static int status()
     return n;
 }
 
+/* "deal": stdin workgroups, gate/up items, down items, phases; stdout the fixed
+ * item of each workgroup, then for each product and list its length and items. */
+static int deal()
+{
+    int P, g, d, phases;
+    if (std::scanf("%d %d %d %d", &P, &g, &d, &phases) != 4) return 2;
+    Deal q;
+    q.deal(P, g, d, phases);
+    std::printf("%d %d ", 1 << q.lg, q.C);
+    for (int b = 0; b < P; ++b) std::printf("%d ", q.fixed(b));
+    for (int p = 0; p < 2; ++p)
+        for (int y = 0; y < 1 << q.lg; ++y) {
+            std::printf("%d ", q.len(p, y));
+            for (int j = 0; j < q.len(p, y); ++j) std::printf("%d ", q.item(j, y, p));
+        }
+    std::printf("\n");
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc < 2) return 2;
     if (!std::strcmp(argv[1], "counts")) return counts();
     if (!std::strcmp(argv[1], "blocks")) return blocks();
     if (!std::strcmp(argv[1], "status")) return status();
+    if (!std::strcmp(argv[1], "deal")) return deal();
     return 2;
 }

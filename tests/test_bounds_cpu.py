@@ -1,6 +1,6 @@
 """The plain arithmetic of ``csrc/bounds.h``, which keeps row and tile indices
-inside their buffers, and of ``csrc/errors.h``, compiled with g++ and run on the
-host."""
+inside their buffers, of ``csrc/deal.h``, which deals work items to lists, and of
+``csrc/errors.h``, compiled with g++ and run on the host."""
 import os
 import shutil
 import subprocess
@@ -100,3 +100,30 @@ def test_a_stalled_pass_is_reported_before_any_other_error(driver):
     order = ((16, C.MOE_EHIP), (1, C.MOE_EBADID), (2, C.MOE_EBADLAYER), (8, C.MOE_EBADCOUNT), (4, C.MOE_ETIMEOUT))
     want = [next((s for bit, s in order if w & bit), C.MOE_OK) for w in words]
     assert _run(driver, "status", len(words), *words) == want
+
+
+@pytest.mark.parametrize("phases", [1, 2, 3])
+@pytest.mark.parametrize("P", [1, 3, 7, 8, 16, 24, 248, 256, 304])
+def test_every_item_is_dealt_once_and_few_are_spread(driver, P, phases):
+    """All items of both products are in the lists exactly once, the fixed ones
+    are the first of each list, and with fewer gate/up items than workgroups no
+    list has more than its even share."""
+    rng = np.random.default_rng(P)
+    sizes = [(0, 0), (1, 1), (8, 8), (9, 1), (32, 56), (128, 448), (255, 1), (256, 224), (257, 3000)]
+    sizes += [tuple(int(v) for v in 2**rng.uniform(0, 12, 2)) for _ in range(12)]
+    for g, d in sizes:
+        out = _run(driver, "deal", P, g, d, phases)
+        lists, run, fixed, rest = out[0], out[1], out[2:2 + P], out[2 + P:]
+        assert lists == (1 if P % 8 else 8)
+        got = {}
+        for p in range(2):
+            for y in range(lists):
+                n = rest.pop(0)
+                got[p, y], rest = rest[:n], rest[n:]
+        assert not rest
+        for p, n in ((0, g if phases & 1 else 0), (1, d if phases & 2 else 0)):
+            assert sorted(i for y in range(lists) for i in got[p, y]) == list(range(n)), (P, g, d, p)
+        for y in range(lists):
+            assert [f for f in fixed[y::lists] if f >= 0] == got[0, y][:run], (P, g, d, y)
+            if phases & 1 and 0 < g <= P:
+                assert len(got[0, y]) <= -(-g // lists), (P, g, d, y)
