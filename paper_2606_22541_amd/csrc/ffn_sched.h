@@ -98,6 +98,7 @@ struct SchedLds {
     int32_t hdr[kSchedHdrInts];
     int32_t claimed, wait;     // begin(): the fixed item was taken; next(): what the wait found
     int32_t item, rti, nt;     // the next item and its tile (bit 30 of rti: a large one)
+    int32_t ahead;             // done(): the next item is known
     int32_t stage;     // thread 0: list being drained (0 gate/up, 1 down, 2 the others')
     uint64_t w[2], ws[2];   // weights of the two products, and their scales
 };
@@ -167,7 +168,7 @@ template <bool LARGE, bool OWN = LARGE>
 struct Worker {
     int pending;                 // a down item put off for a gate/up item, or -1
     int first;                   // the fixed first item, or -1
-    bool have;                   // done() has taken the next item
+    bool have;                   // done() may have taken the next item (l.ahead)
     bool all_done;               // every row tile's gate/up tiles are written
     // current item
     bool down, large;
@@ -258,33 +259,34 @@ struct Worker {
             if (t < q.len(pp, yy)) return q.item(t, yy, pp) | pp << 30;
         }
     }
+    // The item of the requested ticket, or -1: none was requested, or the list
+    // is drained (wave 0).
+    __device__ __forceinline__ int take_requested(SchedLds &l, const Items &q)
+    {
+        const int want = __builtin_amdgcn_readfirstlane(pre), stage = __builtin_amdgcn_readfirstlane(l.stage);
+        pre = -1;
+        if (want < 0 || stage > 1) return -1;
+        const int j = stage ? want : q.C + want;
+        if (j < q.len(stage, q.x)) return q.item(j, q.x, stage) | stage << 30;
+        l.stage = stage + 1;
+        return -1;
+    }
     // Next item (wave 0).
     __device__ __forceinline__ int take(ArgSched &s, SchedLds &l, const Items &q)
     {
-        int stage = __builtin_amdgcn_readfirstlane(l.stage);
-        int want = __builtin_amdgcn_readfirstlane(pre);
-        pre = -1;
-        if (stage == 0) {
-            const int j = q.C + (want >= 0 ? want : ticket(s, 0, q.x));
-            want = -1;
-            if (j < q.len(0, q.x)) return q.item(j, q.x, 0);
-            l.stage = stage = 1;
+        int it = take_requested(l, q);
+        while (it < 0) {
+            const int stage = __builtin_amdgcn_readfirstlane(l.stage);
+            if (stage > 1) return steal(s, l, q);
+            pre = q.len(stage, q.x) > 0 ? ticket(s, stage, q.x) : 0;   // (any ticket is past an empty list)
+            it = take_requested(l, q);
         }
-        if (stage == 1) {
-            const int n = q.len(1, q.x);
-            if (n > 0) {
-                const int j = want >= 0 ? want : ticket(s, 1, q.x);
-                if (j < n) return q.item(j, q.x, 1) | 1 << 30;
-            }
-            l.stage = 2;
-        }
-        return steal(s, l, q);
+        return it;
     }
 
-    // Wave 0: takes the next item and looks up its tile.
-    __device__ __forceinline__ void take_next(ArgSched &s, SchedLds &l, const Items &q)
+    // Wave 0: puts the next item and its tile where every wave finds them.
+    __device__ __forceinline__ void set_next(ArgSched &s, SchedLds &l, const Items &q, int it)
     {
-        const int it = take(s, l, q);
         if (it >= 0) {
             int rt, n;
             const bool lg = find(s, l, q, it & ~(1 << 30), it >> 30, rt, n);
@@ -302,6 +304,9 @@ struct Worker {
         const int lane = fresh_tid() & 63, nx = 1 << q.lg;
         int need;
         const int32_t *dep = dep_of(s, l, q, rt, need);
+        // every gate/up item is taken (and stays so): looking for others costs a
+        // poll five round trips to memory, so it ends once it finds none
+        bool taken = false;
         for (int polls = 0;; ++polls) {
             // one load of one line a poll: many workgroups may be waiting, and
             // their polls share HBM channels with the others' streams
@@ -316,7 +321,7 @@ struct Worker {
                 }
                 return __all(mine) ? -2 : -1;
             }
-            if (polls > 2) {
+            if (polls > 2 && !taken) {
                 // gate/up items that no workgroup has taken: tickets ...
                 const int y = lane & (kLists - 1);
                 const bool open = lane < nx && q.C + agent_load(tick_of(s, 0, y)) < q.len(0, y);
@@ -328,6 +333,7 @@ struct Worker {
                     continue;
                 }
                 // ... and the fixed ones of workgroups that have not started
+                bool none = true;
                 for (int b0 = 0; b0 < (int)gridDim.x; b0 += 64) {
                     const int b = b0 + lane;
                     const bool idle = b < (int)gridDim.x && q.fixed(b) >= 0 &&
@@ -339,8 +345,10 @@ struct Worker {
                         if (lane == 0) old = agent_swap(&s.claim[bb], 1);
                         old = __builtin_amdgcn_readfirstlane(old);
                         if (old == 0) return q.fixed(bb);
+                        none = false;
                     }
                 }
+                taken = none;
             }
             if (polls >= kMaxPolls) {
                 if (lane == 0) atomicOr(err, kErrStalled);
@@ -403,8 +411,8 @@ struct Worker {
             it &= ~(1 << 30);
             decode(s, l, q, it, p);
         } else {
-            if (!have) {
-                if (fresh_tid() < 64) take_next(s, l, q);
+            if (!have || __builtin_amdgcn_readfirstlane(l.ahead) == 0) {
+                if (fresh_tid() < 64) set_next(s, l, q, take(s, l, q));
                 __syncthreads();
             }
             it = __builtin_amdgcn_readfirstlane(l.item);
@@ -460,16 +468,19 @@ struct Worker {
     }
 
     // The item's output is stored: a gate/up tile is counted once every
-    // wave's stores have reached memory.  Wave 0 takes the next item before
-    // the barrier, while the other waves still store.  Past it every LDS read
-    // of the item is done.
+    // wave's stores have reached memory.  Past the barrier every LDS read of the
+    // item is done.  Wave 0 looks the requested ticket's item up before it, while
+    // the other waves still store; where that ticket comes to nothing, the next
+    // item is looked for after the count, since the down items wait for it.
     __device__ __forceinline__ void done(ArgSched &s, SchedLds &l, int phases, ArgTiles &ct)
     {
         have = pending < 0;
         if (have && fresh_tid() < 64) {
             Items q;
             q.load<LARGE, OWN>(l, phases, ct);
-            take_next(s, l, q);
+            const int it = take_requested(l, q);
+            if (it >= 0) set_next(s, l, q, it);
+            l.ahead = it >= 0;
         }
         if (!down) __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
         __syncthreads();
