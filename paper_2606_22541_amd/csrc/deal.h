@@ -9,6 +9,9 @@ namespace moe {
 constexpr int kListsLog2 = 3;
 constexpr int kLists = 1 << kListsLog2;
 
+// Rows shorter than this (bytes) are short, see deal().
+constexpr int kShortRow = 1024;
+
 // Product p (0 gate/up, 1 down) deals its items in runs of consecutive ones to
 // the lists in turn.  Workgroup b belongs to list b % lists.
 struct Deal {
@@ -17,8 +20,8 @@ struct Deal {
     int total0 = 0, total1 = 0;
 
     // P workgroups; g gate/up and d down items, of which the launch runs those
-    // of `phases` (1, 2, or 3 for both).
-    constexpr void deal(int P, int g, int d, int phases)
+    // of `phases` (1, 2, or 3 for both); row_bytes: of an activation row.
+    constexpr void deal(int P, int g, int d, int phases, int64_t row_bytes)
     {
         lg = (P & (kLists - 1)) ? 0 : kListsLog2;
         total0 = (phases & 1) ? g : 0;
@@ -27,9 +30,13 @@ struct Deal {
         // workgroups are shared evenly: in runs of P / lists they fill the first
         // lists only, and their weights come through those XCDs (32 items of one
         // expert, d = 7168, f = 2048, 16 rows, a layer: 79.0 us, shared 69.8; fp8,
-        // two experts 80.4 and 58.8).
+        // two experts 80.4 and 58.8).  Not where rows are so short that the
+        // weights do not count: latencies are lower with h in one L2 then (4
+        // experts, f = d / 2, 64 tokens, shared and in runs: fp8, d = 512 31.8 and
+        // 30.8, bf16, d = 256 25.5 and 24.2; bf16, d = 512, rows of 1 KB, 27.6 and
+        // 28.1).
         const int share = (g + (1 << lg) - 1) >> lg, most = P >> lg;
-        C = share < 1 ? 1 : share < most ? share : most;
+        C = row_bytes < kShortRow ? most : share < 1 ? 1 : share < most ? share : most;
         // A list's down items are those of the row tiles that it did the
         // gate/up items of (as far as runs of one length allow): they are ready
         // when its own gate/up items are.

@@ -130,6 +130,7 @@ struct FfnTiles {
     int32_t ntl[2];    // of a large row tile (256 columns)
     int32_t nts[2];    // of a small row tile (128 columns)
     int32_t band;      // row tiles of a raster band
+    int32_t row_bytes; // of an activation row
 };
 
 typedef const __attribute__((address_space(4))) FfnTiles ArgTiles;
@@ -154,7 +155,7 @@ struct Items : Deal {
         nts0 = ct.nts[0];
         nts1 = ct.nts[1];
         band = ct.band;
-        deal(gridDim.x, nl0 * ntl0 + (nrt - nl0) * nts0, nl1 * ntl1 + (nrtd - nl1) * nts1, phases);
+        deal(gridDim.x, nl0 * ntl0 + (nrt - nl0) * nts0, nl1 * ntl1 + (nrtd - nl1) * nts1, phases, ct.row_bytes);
         C1 = __builtin_amdgcn_readfirstlane(C1);
         x = blockIdx.x & ((1 << lg) - 1);
     }

@@ -568,7 +568,7 @@ static moe_status launch_ffn(moe_stage *st, SlotWs &sl, const FfnPass &f, bool a
     a.sched = sl.sched;
     a.tiles = FfnTiles{{(2 * d.d_ff + 255) / 256, (d.d_model + 255) / 256},
                        {(2 * d.d_ff + 127) / 128, (d.d_model + 127) / 128},
-                       fp8 ? kBandFp8 : kBandBf16};
+                       fp8 ? kBandFp8 : kBandBf16, d.d_model * (int32_t)st->sz.eb};
     a.layer_id = f.layer_id;           // weights named on the device (null: layer 0)
     a.layers = st->layers;
     a.n_layers = d.n_layers;

@@ -69,14 +69,14 @@ static int status()
     return n;
 }
 
-/* "deal": stdin workgroups, gate/up items, down items, phases; stdout the fixed
- * item of each workgroup, then for each product and list its length and items. */
+/* "deal": stdin workgroups, gate/up items, down items, phases, bytes of a row;
+ * stdout the fixed item of each workgroup, then for each product and list its length and items. */
 static int deal()
 {
-    int P, g, d, phases;
-    if (std::scanf("%d %d %d %d", &P, &g, &d, &phases) != 4) return 2;
+    int P, g, d, phases, bytes;
+    if (std::scanf("%d %d %d %d %d", &P, &g, &d, &phases, &bytes) != 5) return 2;
     Deal q;
-    q.deal(P, g, d, phases);
+    q.deal(P, g, d, phases, bytes);
     std::printf("%d %d ", 1 << q.lg, q.C);
     for (int b = 0; b < P; ++b) std::printf("%d ", q.fixed(b));
     for (int p = 0; p < 2; ++p)

@@ -102,17 +102,19 @@ def test_a_stalled_pass_is_reported_before_any_other_error(driver):
     assert _run(driver, "status", len(words), *words) == want
 
 
+@pytest.mark.parametrize("row_bytes", [896, 1024])
 @pytest.mark.parametrize("phases", [1, 2, 3])
 @pytest.mark.parametrize("P", [1, 3, 7, 8, 16, 24, 248, 256, 304])
-def test_every_item_is_dealt_once_and_few_are_spread(driver, P, phases):
+def test_every_item_is_dealt_once_and_few_are_spread(driver, P, phases, row_bytes):
     """All items of both products are in the lists exactly once, the fixed ones
     are the first of each list, and with fewer gate/up items than workgroups no
-    list has more than its even share."""
+    list has more than its even share (rows of 1 KB and more; shorter ones fill
+    the lists one after the other)."""
     rng = np.random.default_rng(P)
     sizes = [(0, 0), (1, 1), (8, 8), (9, 1), (32, 56), (128, 448), (255, 1), (256, 224), (257, 3000)]
     sizes += [tuple(int(v) for v in 2**rng.uniform(0, 12, 2)) for _ in range(12)]
     for g, d in sizes:
-        out = _run(driver, "deal", P, g, d, phases)
+        out = _run(driver, "deal", P, g, d, phases, row_bytes)
         lists, run, fixed, rest = out[0], out[1], out[2:2 + P], out[2 + P:]
         assert lists == (1 if P % 8 else 8)
         got = {}
@@ -125,5 +127,7 @@ def test_every_item_is_dealt_once_and_few_are_spread(driver, P, phases):
             assert sorted(i for y in range(lists) for i in got[p, y]) == list(range(n)), (P, g, d, p)
         for y in range(lists):
             assert [f for f in fixed[y::lists] if f >= 0] == got[0, y][:run], (P, g, d, y)
-            if phases & 1 and 0 < g <= P:
+            if phases & 1 and 0 < g <= P and row_bytes >= 1024:
                 assert len(got[0, y]) <= -(-g // lists), (P, g, d, y)
+            if phases & 1 and g <= P and row_bytes < 1024:
+                assert len(got[0, y]) == min(P // lists, max(0, g - y * (P // lists))), (P, g, d, y)
