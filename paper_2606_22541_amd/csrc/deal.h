@@ -1,5 +1,6 @@
-// How the items of an FFN pass are dealt to the work lists of ffn_sched.h: plain
-// constexpr arithmetic without HIP types, checked on the host.
+// How the items of an FFN pass are dealt to the work lists of ffn_sched.h, and
+// whether one launch runs both products: plain constexpr arithmetic without HIP
+// types, checked on the host.
 #pragma once
 
 #include <stdint.h>
@@ -63,5 +64,32 @@ struct Deal {
         return j < C && it < total0 ? it : -1;
     }
 };
+
+// A pass whose weights take at least about 30 us to stream, see split_products().
+constexpr int64_t kLongStream = (int64_t)160 << 20;
+
+// Whether a pass runs its products in a launch each, when the stage's passes
+// come in on `streams` streams.  groups: its experts; rows: rows that one of them
+// can expect, of tiles of up to `tile` rows and `nt` column tiles in the gate/up
+// product; weight_bytes: of all its experts; grid: workgroups of a launch.
+//
+// One launch runs both faster when it has the GPU to itself, but its workgroups
+// keep their CUs from the first item to the last, those that wait for the down
+// product's rows included.  If the gate/up product is one round at most they wait
+// most, and passes of other streams could have run there (us a micro-batch, d =
+// 7168, f = 2048, 8 of 256 experts, top 8, one launch and two): bf16 on three
+// streams T = 1024 125.3 and 119.0, T = 8192 262.6 and 242.3, on four T = 4096 181.5 and
+// 161.5; fp8 on two streams T = 1024 89.6 and 69.3, on three T = 4096 103.6 and 95.5.
+// Not otherwise:
+//  * of several rounds, one launch fills the first product's last: fp8, two streams, T =
+//    16384 283 and 320; 32 experts and a shared one, T = 1000, 495 and 511;
+//  * bf16 on two streams: T = 4096 176 and 181, T = 1024 125.6 and 127.4;
+//  * short passes are bound by their launches: 8 experts, top 2, three streams,
+//    fp8, d = 2048, f = 1536 (75 MB) 22.7 and 24.0, bf16 (151 MB) 53.1 and 56.0, but
+//    d = 4096, f = 1024 (201 MB) 56.0 and 44.1.
+constexpr bool split_products(int streams, bool fp8, int64_t items, int64_t weight_bytes, int grid)
+{
+    return streams >= (fp8 ? 2 : 3) && weight_bytes >= kLongStream && items <= grid;
+}
 
 }  // namespace moe

@@ -30,6 +30,9 @@ struct SlotWs {
     // unseen), and every pass that no dispatch precedes in its own call clears
     // them.
     bool sched_fresh = false, captured = false;
+    // The stream of the slot's last FFN pass, plus one (0: none yet): only ever
+    // compared.
+    uintptr_t ffn_stream = 0;
     GroupTable tables() const { return GroupTable{g_row0, g_rows}; }
     int32_t *slot_of_row = nullptr, *row_of_slot = nullptr;
     float *x_perm_s = nullptr;     // fp8: the routed rows' x scales, transposed
@@ -535,10 +538,28 @@ struct FfnPass {
     void *y;                          // Y_perm, or the caller's y
     const int32_t *layer_id;
     int64_t max_group;                // no group has more rows than this
+    int64_t mean_group;               // rows that a local expert can expect
 };
 
+// Streams that the stage's slots had their last FFN passes on, `s` among them
+// (counted to three).  Slots may be used by a thread each.
+static int ffn_streams(moe_stage *st, SlotWs &sl, hipStream_t s)
+{
+    uintptr_t seen[2] = {(uintptr_t)s + 1, 0};
+    __atomic_store_n(&sl.ffn_stream, seen[0], __ATOMIC_RELAXED);
+    int n = 1;
+    for (const SlotWs &o : st->slots) {
+        const uintptr_t v = __atomic_load_n(&o.ffn_stream, __ATOMIC_RELAXED);
+        if (v == 0 || v == seen[0] || v == seen[1]) continue;
+        if (n == 2) return 3;
+        seen[n++] = v;
+    }
+    return n;
+}
+
 // The two grouped GEMMs of one FFN pass on `s`: gate/up with the fused
-// SiLU*up epilogue (fp8: and the quantisation of h), then down.
+// SiLU*up epilogue (fp8: and the quantisation of h), then down; in one launch, or
+// in one each (the results are the same bits).
 // `after_dispatch`: the dispatch was enqueued by the same call, so the
 // schedule's counters are as it leaves them.
 static moe_status launch_ffn(moe_stage *st, SlotWs &sl, const FfnPass &f, bool after_dispatch,
@@ -580,7 +601,20 @@ static moe_status launch_ffn(moe_stage *st, SlotWs &sl, const FfnPass &f, bool a
         return fp8 ? launch_ffn_fp8(a, grid, s)
                : small ? launch_ffn_bf16_small(a, grid, s) : launch_ffn_bf16(a, grid, s);
     };
-    if (st->prof_on) {                 // timed by product: one launch each
+    // gate/up items of a group of `rows` rows, as many as one can expect
+    auto items_of = [&](int64_t rows) {
+        if (!fp8 && rows <= kSmallRows) return (int64_t)a.tiles.nts[0];
+        const int tile = 32 * (fp8 ? kTileBlocksFp8 : kTileBlocks);
+        return (rows + tile - 1) / tile * a.tiles.ntl[0];
+    };
+    const int64_t items = d.n_local_experts * items_of(f.mean_group) + (f.rows_shared ? items_of(f.n_rows) : 0);
+    const int64_t groups = d.n_local_experts + (f.rows_shared ? 1 : 0);
+    const bool split = split_products(ffn_streams(st, sl, s), fp8, items,
+                                      groups * 3 * d.d_model * d.d_ff * st->sz.eb, grid);
+    if (!st->prof_on && split) {
+        e = run(1);
+        if (e == hipSuccess) e = run(2);
+    } else if (st->prof_on) {          // timed by product: one launch each
         {
             ProfScope ps(st, 2, s);
             e = run(1);
@@ -612,6 +646,7 @@ static moe_status ffn_impl(moe_stage *st, int32_t slot, void *stream, bool rec)
     f.y = sl.y_perm;
     f.layer_id = sl.mb.layer_id;
     f.max_group = (int64_t)T * d.top_k;       // a token may repeat an id
+    f.mean_group = (f.max_group + d.n_experts - 1) / d.n_experts;
     const moe_status r = launch_ffn(st, sl, f, !rec, s);
     if (r != MOE_OK) return r;
     return rec ? record(sl, s) : MOE_OK;
@@ -653,6 +688,7 @@ static moe_status ffn_grouped_impl(moe_stage *st, int32_t slot, const moe_groupe
     f.y = gb->y;
     f.layer_id = gb->layer_id;
     f.max_group = n;
+    f.mean_group = (n + d.n_local_experts - 1) / d.n_local_experts;
     const moe_status r = launch_ffn(st, sl, f, true, s);
     if (r != MOE_OK) return r;
     return record(sl, s);

@@ -88,6 +88,22 @@ static int deal()
     return 0;
 }
 
+/* "split": stdin n, then n times streams, fp8, items, bytes of weights,
+ * workgroups; stdout whether the products are launched one by one. */
+static int split()
+{
+    int n;
+    if (std::scanf("%d", &n) != 1) return 2;
+    for (; n > 0; --n) {
+        int streams, fp8, grid;
+        long long items, bytes;
+        if (std::scanf("%d %d %lld %lld %d", &streams, &fp8, &items, &bytes, &grid) != 5) return 2;
+        std::printf("%d ", (int)split_products(streams, fp8 != 0, items, bytes, grid));
+    }
+    std::printf("\n");
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc < 2) return 2;
@@ -95,5 +111,6 @@ int main(int argc, char **argv)
     if (!std::strcmp(argv[1], "blocks")) return blocks();
     if (!std::strcmp(argv[1], "status")) return status();
     if (!std::strcmp(argv[1], "deal")) return deal();
+    if (!std::strcmp(argv[1], "split")) return split();
     return 2;
 }

@@ -131,3 +131,18 @@ def test_every_item_is_dealt_once_and_few_are_spread(driver, P, phases, row_byte
                 assert len(got[0, y]) <= -(-g // lists), (P, g, d, y)
             if phases & 1 and g <= P and row_bytes < 1024:
                 assert len(got[0, y]) == min(P // lists, max(0, g - y * (P // lists))), (P, g, d, y)
+
+
+def test_products_are_split_where_other_streams_can_use_the_gpu(driver):
+    """One launch on one stream, for several rounds and for short streams of
+    weights; a launch per product for one round on several streams."""
+    MB = 2**20
+    cases = []                                 # streams, fp8, items, bytes, workgroups, expected
+    for streams in (1, 2, 3):
+        for fp8 in (0, 1):
+            for items in (1, 256, 257, 1056):
+                for size in (159, 160, 704):
+                    want = streams >= (2 if fp8 else 3) and items <= 256 and size >= 160
+                    cases.append((streams, fp8, items, size * MB, 256, want))
+    got = _run(driver, "split", len(cases), *[v for c in cases for v in c[:5]])
+    assert got == [int(c[5]) for c in cases]

@@ -324,6 +324,52 @@ def test_second_pass_with_row_tiles_of_the_down_product():
         assert np.all(err <= BF16_TOL), err.max()
 
 
+@pytest.mark.parametrize("dtype,E_loc", [("bf16", 2), ("fp8", 4)])
+def test_passes_on_several_streams_give_the_same_bits(dtype, E_loc):
+    """Micro-batches of one round of items whose weights are a long stream: on
+    one stream one launch runs both products, on three a launch each.  Same
+    bits, with two micro-batches per slot in flight."""
+    T = 700
+    cfg = inputs.MoEConfig("streams", d=7168, f=2048, E=8, e0=0, E_loc=E_loc, k=2, lengths=(T,) * 6, dtype=dtype,
+                           seed=101)
+    wts = inputs.make_weights(cfg, "cuda")
+    mbs = inputs.make_microbatches(cfg, "cuda")
+    args, outs = [], []
+    for mb in mbs:
+        ids, w = to_device_routing(mb.ids, mb.w)
+        x, xs = quantize_fp8(mb.x) if dtype == "fp8" else (mb.x, None)
+        args.append((x, ids, w, xs))
+    for streams in ([torch.cuda.current_stream()], [torch.cuda.Stream() for _ in range(3)]):
+        log("%s on %d streams" % (dtype, len(streams)))
+        out = [torch.full((T, cfg.d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in mbs]
+        with ExpertStage(cfg, wts, n_slots=3) as st:
+            torch.cuda.synchronize()
+            for r in range(2):                 # the second time every slot's stream is known
+                for i, (x, ids, w, xs) in enumerate(args):
+                    with torch.cuda.stream(streams[i % len(streams)]):
+                        st.submit(st.microbatch(x, ids, w, out[i], xs))
+            st.sync()
+            torch.cuda.synchronize()
+        outs.append(out)
+    for a, b in zip(*outs):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a, b)
+    if dtype == "bf16":                        # tokens of one local expert, against fp32 products
+        x, ids, w, _ = args[0]
+        t = ((ids[:, 0] < E_loc) != (ids[:, 1] < E_loc)).nonzero()[::5, 0]
+        j = (ids[t, 1] < E_loc).long()
+        e = ids[t, j]
+        ref = torch.zeros((len(t), cfg.d), device="cuda")
+        for g in range(E_loc):
+            at = (e == g).nonzero()[:, 0]
+            xr = x[t[at]].float()
+            h = torch.nn.functional.silu(xr @ wts.w_gate[g].float().T) * (xr @ wts.w_up[g].float().T)
+            ref[at] = (h.to(torch.bfloat16).float() @ wts.w_down[g].float().T).to(torch.bfloat16).float()
+        ref *= w[t, j][:, None]
+        err = row_rel_l2(outs[1][0][t].double().cpu().numpy(), ref.double().cpu().numpy())
+        assert np.all(err <= BF16_TOL), err.max()
+
+
 def test_grids_of_a_few_workgroups():
     """Streams of 16 and of 32 compute units: lists of two and of four
     workgroups, so nearly every item comes from a ticket.  In a child process:
