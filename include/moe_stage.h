@@ -217,8 +217,9 @@ MOE_API moe_status moe_dispatch(moe_stage *stage, int32_t slot, const moe_microb
 
 /* Step 2: grouped GEMM gate/up with fused SiLU*up epilogue, then grouped GEMM
  * down, for every local expert with rows (and the shared expert, if any), in
- * one launch.  The schedule of its tiles is built on the device by
- * moe_dispatch. */
+ * one launch, or in a launch each where the stage's slots are in use on several
+ * streams and that is faster (the results are the same bits).  The schedule of
+ * its tiles is built on the device by moe_dispatch. */
 MOE_API moe_status moe_expert_ffn(moe_stage *stage, int32_t slot, void *stream);
 
 /* Step 2 for pre-grouped rows (moe_grouped_batch): builds the schedule of tiles
@@ -338,11 +339,11 @@ MOE_API moe_status moe_stage_sync(moe_stage *stage);
  * While enabled, every enqueue call records an event pair around each of its
  * kernel groups on the launch stream (this creates events, i.e. allocates
  * host-side runtime objects), and the two grouped GEMMs run as a launch each
- * (otherwise one launch runs both, and takes less than their sum).  Kinds, in order: 0 dispatch index
- * (histogram, scan, scatter), 1 gather of the token scales (fp8 only; the
- * rows themselves are gathered inside kind 2), 2 grouped GEMM gate/up with the SiLU*up epilogue (fp8: and the
- * quantisation of h), 3 grouped GEMM down, 4 combine, 5 reserved (no
- * longer recorded). */
+ * (one launch of both takes less than their sum).  Kinds, in order: 0 dispatch
+ * index (histogram, scan, scatter), 1 gather of the token scales (fp8 only; the
+ * rows themselves are gathered inside kind 2), 2 grouped GEMM gate/up with the
+ * SiLU*up epilogue (fp8: and the quantisation of h), 3 grouped GEMM down, 4
+ * combine, 5 reserved (no longer recorded). */
 #define MOE_PROF_KINDS 6
 MOE_API moe_status moe_stage_profile(moe_stage *stage, int32_t enable);
 

@@ -56,12 +56,6 @@ constexpr int kSmallRows = 192;
 constexpr int kSmallRowsDown = 64;
 static_assert(kSmallRows <= 32 * kLeastBlocks && kTileBlocksFp8 <= kLeastBlocks, "every tile's offsets fit");
 
-// Device-side tables of the groups, written by the dispatch, read by the GEMMs.
-struct GroupTable {
-    int32_t *row0;      // [G] first row of the group in its A matrix
-    int32_t *rows;      // [G] rows of the group
-};
-
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 // Round-to-nearest-even fp32 -> bf16 (finite inputs).

@@ -96,8 +96,8 @@ __device__ __forceinline__ int wave_sum(int v)
     return __builtin_amdgcn_readfirstlane(v);
 }
 
-// The groups' rows and the row tiles of the FFN pass (ffn_sched.h) over G =
-// E_loc (+1 shared) groups, built by one workgroup; rows[i] is the local
+// The row tiles of the FFN pass (ffn_sched.h) over G = E_loc (+1 shared)
+// groups, built by one workgroup; a group's rows are the local
 // expert's token count (tot), or T for the shared expert.
 //
 // A large group is split evenly into as few row tiles of at most h 32-row
@@ -112,7 +112,7 @@ __device__ __forceinline__ int wave_sum(int v)
 // The first wave builds (in chunks of 64 groups, with shuffle scans and no
 // workgroup barrier: the other workgroups place their slots meanwhile), the
 // other waves clear the counters of the next pass.
-__device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedPlan &plan, const int32_t *tot,
+__device__ void build_schedule(const Sched &s, const SchedPlan &plan, const int32_t *tot,
                                int E_loc, int has_shared, int T)
 {
     const int G = E_loc + (has_shared ? 1 : 0);
@@ -184,10 +184,6 @@ __device__ void build_schedule(const GroupTable &g, const Sched &s, const SchedP
         const int p_large = wave_excl_scan(c == 0 ? m : 0, lane, t_large);
         const uint64_t mid = __ballot(m > 0 && c == 1), small = __ballot(m > 0 && c == 2);
         const int row0 = i < E_loc ? c_row + p_row : 0;
-        if (i < G) {
-            g.row0[i] = row0;
-            g.rows[i] = rows;
-        }
         if (own) {
             const uint64_t some = __ballot(m > 0);
             const int at = c_group + __popcll(some & below);
@@ -268,7 +264,7 @@ __global__ __launch_bounds__(kDispatchThreads)
 void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, int32_t E,
              int32_t e0, int32_t E_loc, int32_t T, int32_t has_shared,
              const int32_t *__restrict__ blk_counts, int32_t *__restrict__ counts,
-             int32_t *__restrict__ offsets, GroupTable g, Sched sched, SchedPlan plan,
+             int32_t *__restrict__ offsets, Sched sched, SchedPlan plan,
              int32_t *__restrict__ slot_of_row, int32_t *__restrict__ row_of_slot)
 {
     __shared__ int32_t tot[kMaxLocalExperts], pre[kMaxLocalExperts];
@@ -361,7 +357,7 @@ void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, 
     // the last workgroup owns no slots (the launch adds it for this): it
     // builds the FFN's row tiles while the others place their slots
     if (b == (int)gridDim.x - 1 && b > 0) {
-        if (g.rows) build_schedule(g, sched, plan, tot, E_loc, has_shared, T);
+        if (sched.hdr) build_schedule(sched, plan, tot, E_loc, has_shared, T);
         return;
     }
 
@@ -412,7 +408,7 @@ void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, 
         }
     }
     // without slots there is one workgroup only
-    if (gridDim.x == 1 && g.rows) build_schedule(g, sched, plan, tot, E_loc, has_shared, T);
+    if (gridDim.x == 1 && sched.hdr) build_schedule(sched, plan, tot, E_loc, has_shared, T);
 }
 
 // Row tiles for pre-grouped rows (the receive region of section 3.2.1 in
@@ -421,7 +417,7 @@ void k_place(const int32_t *__restrict__ ids, int32_t n_slots, int32_t nb_hist, 
 // build as the dispatch.
 __global__ __launch_bounds__(kDispatchThreads)
 void k_group_tables_from_counts(const int32_t *__restrict__ counts, int32_t E_loc,
-                                int32_t n_rows_max, GroupTable g, Sched sched, SchedPlan plan,
+                                int32_t n_rows_max, Sched sched, SchedPlan plan,
                                 int32_t *__restrict__ err)
 {
     __shared__ int32_t tot[kMaxLocalExperts];
@@ -449,15 +445,15 @@ void k_group_tables_from_counts(const int32_t *__restrict__ counts, int32_t E_lo
         if (__any(bad) && lane == 0) atomicOr(err, kErrBadCount);
     }
     __syncthreads();
-    build_schedule(g, sched, plan, tot, E_loc, 0, 0);
+    build_schedule(sched, plan, tot, E_loc, 0, 0);
 }
 
 hipError_t launch_group_tables_from_counts(const int32_t *counts, int32_t E_loc,
-                                           int32_t n_rows_max, GroupTable g, const Sched &sched,
+                                           int32_t n_rows_max, const Sched &sched,
                                            const SchedPlan &plan, int32_t *err, hipStream_t s)
 {
     hipLaunchKernelGGL(k_group_tables_from_counts, dim3(1), dim3(kDispatchThreads), 0, s, counts, E_loc,
-                       n_rows_max, g, sched, plan, err);
+                       n_rows_max, sched, plan, err);
     return hipGetLastError();
 }
 
@@ -471,7 +467,7 @@ hipError_t launch_dispatch_index(const DispatchArgs &a, hipStream_t s)
     // one workgroup per histogram row, plus one without slots for the row tiles
     hipLaunchKernelGGL(k_place, dim3(nb + 1), dim3(kDispatchThreads), 0, s, a.ids,
                        a.n_slots, nb, a.E, a.e0, a.E_loc, a.T, a.has_shared, a.blk_counts,
-                       a.counts, a.offsets, a.groups, a.sched, a.plan, a.slot_of_row, a.row_of_slot);
+                       a.counts, a.offsets, a.sched, a.plan, a.slot_of_row, a.row_of_slot);
     return hipGetLastError();
 }
 

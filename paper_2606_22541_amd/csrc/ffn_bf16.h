@@ -3,7 +3,8 @@
 //
 //   H[g] = SiLU(A[g] Wg[g]^T) * (A[g] Wu[g]^T),   Y[g] = H[g] Wd[g]^T,
 //
-// in one launch, for every group g (a local expert, or the shared expert).
+// in one launch (or, where passes of several streams share the GPU, in one each:
+// split_products()), for every group g (a local expert, or the shared expert).
 // A[g] is a run of token rows (gathered from x through slot_of_row), all
 // operands are K-contiguous, and the weights are stored in MFMA fragment
 // order (see launch_pack_frag_bf16).

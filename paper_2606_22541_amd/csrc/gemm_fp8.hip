@@ -119,7 +119,7 @@ struct Ring8 {
 //  * weight fragments 2 w and 2 w + 1 of the tile's 16, both 1 KB halves;
 //  * token rows 16 w .. 16 w + 15 as two 8-row instructions; lane l writes
 //    LDS row 16 w + 8 i + l / 8, physical chunk l % 8, with global chunk
-//    (l % 8) ^ ((row / 2) % 8);
+//    (l % 8) ^ ((row / 2) & 5);
 //  * 64 of the 128 token scales (waves w and w + 2, w + 4, w + 6 load the
 //    same ones: identical data to identical addresses).
 // Load i (0..6) of the fills: 0..3 the weight fragment halves, 4..5 the

@@ -29,8 +29,7 @@ struct DispatchArgs {
     int32_t *blk_counts;     // [nb][E]
     int32_t *counts;         // [E]
     int32_t *offsets;        // [E_loc+1]
-    GroupTable groups;       // G = E_loc + has_shared groups (null: not wanted)
-    Sched sched;             // the FFN's row tiles (unused without groups)
+    Sched sched;             // the FFN's row tiles over G = E_loc + has_shared groups (null: not wanted)
     SchedPlan plan;
     int32_t *slot_of_row;    // [cap]
     int32_t *row_of_slot;    // [T*k]
@@ -40,12 +39,12 @@ struct DispatchArgs {
 // Histogram -> scan (+ the FFN's row tiles) -> stable scatter.
 hipError_t launch_dispatch_index(const DispatchArgs &a, hipStream_t s);
 
-// Row tiles (over the E_loc routed groups, no shared group) for rows that arrive already grouped by local expert: counts[i] rows of expert
-// i, consecutive.  Counts are read on the device; a negative count is taken
+// Row tiles (over the E_loc routed groups, no shared group) for rows that arrive
+// already grouped by local expert: counts[i] rows of expert i, consecutive.  Counts are read on the device; a negative count is taken
 // as 0 and the running total is capped at n_rows_max (later groups lose
 // their rows), both reported through kErrBadCount in *err.
 hipError_t launch_group_tables_from_counts(const int32_t *counts, int32_t E_loc,
-                                           int32_t n_rows_max, GroupTable g, const Sched &sched,
+                                           int32_t n_rows_max, const Sched &sched,
                                            const SchedPlan &plan, int32_t *err, hipStream_t s);
 
 // Clears a schedule's counters for another pass over the same row tiles.
@@ -131,9 +130,8 @@ __device__ __forceinline__ KernArgs reload(KernArgs p)
     return p;
 }
 
-// bf16 expert FFN over the row tiles of a.sched (ffn_bf16.h).  rt_max bounds
-// the row tiles, grid is the workgroups the row tiles were planned for (at
-// most one per CU).  launch_ffn_bf16_small is for passes all of whose groups
+// bf16 expert FFN over the row tiles of a.sched (ffn_bf16.h).  grid is the
+// workgroups the row tiles were planned for (at most one per CU).  launch_ffn_bf16_small is for passes all of whose groups
 // have at most kSmallRows rows.
 hipError_t launch_ffn_bf16(const FfnArgs &a, int grid, hipStream_t s);
 hipError_t launch_ffn_bf16_small(const FfnArgs &a, int grid, hipStream_t s);

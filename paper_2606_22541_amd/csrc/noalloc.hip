@@ -5,14 +5,15 @@
 //
 // The kernels are the stage's own (k_hist, k_place; no row tiles are asked
 // for).  What the stage keeps in a slot's workspace -- one histogram row per
-// 1024-slot workgroup -- lives here in one file-scope device array.  Its device address is looked up once per device
-// with hipGetSymbolAddress (in host code the array's name is not a device
-// address) and only that address is ever handed to a kernel.
+// 1024-slot workgroup -- lives here in one file-scope device array.  Its device
+// address is looked up once per device with hipGetSymbolAddress (in host code the
+// array's name is not a device address) and only that address is ever handed to a
+// kernel.
 //
 // Every call on a device shares that device's array: calls that overlap on
 // one device (other streams, other threads) race on it.  Nothing in it needs
 // clearing between calls: k_hist writes every entry of each histogram row it
-// owns, and the table build writes every table entry the placement reads.
+// owns, and the placement reads those only.
 #include <mutex>
 
 #include "kernels.h"

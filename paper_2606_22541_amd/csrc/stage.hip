@@ -21,7 +21,6 @@ namespace {
 
 struct SlotWs {
     int32_t *blk_counts = nullptr, *counts = nullptr, *offsets = nullptr;
-    int32_t *g_row0 = nullptr, *g_rows = nullptr;
     Sched sched{};
     // The schedule's counters are as the dispatch left them: an FFN pass takes
     // the work they count out, and a second one on the same dispatch has to
@@ -33,7 +32,6 @@ struct SlotWs {
     // The stream of the slot's last FFN pass, plus one (0: none yet): only ever
     // compared.
     uintptr_t ffn_stream = 0;
-    GroupTable tables() const { return GroupTable{g_row0, g_rows}; }
     int32_t *slot_of_row = nullptr, *row_of_slot = nullptr;
     float *x_perm_s = nullptr;     // fp8: the routed rows' x scales, transposed
     void *h = nullptr;
@@ -118,7 +116,7 @@ Sizes sizes_of(const moe_stage_desc *d)
     int64_t b = 0;
     b += align256(s.nb_max * E * 4) + align256(E * 4) + align256((El + 1) * 4);
     s.rt_max = sched_max_tiles(cap1 + (d->has_shared_expert ? T1 : 0), s.G);
-    b += 2 * align256(s.G * 4) + align256(sched_ints(s.rt_max) * 4);
+    b += align256(sched_ints(s.rt_max) * 4);
     b += align256(cap1 * 4) + align256((s.n_slots_tok > 0 ? s.n_slots_tok : 1) * 4);
     if (fp8) b += align256(cap1 * (D / 128) * 4);   // gathered token scales (fp8 only)
     b += align256(cap1 * F * s.eb) + (fp8 ? align256(cap1 * (F / 128) * 4) : 0);
@@ -377,7 +375,7 @@ moe_status moe_stage_create(const moe_stage_desc *desc, const moe_weights *w, mo
     for (auto &sl : st->slots) {
         ok = alloc(st, &sl.blk_counts, z.nb_max * E * 4) && alloc(st, &sl.counts, E * 4) &&
              alloc(st, &sl.offsets, (El + 1) * 4) &&
-             alloc(st, &sl.g_row0, z.G * 4) && alloc(st, &sl.g_rows, z.G * 4) && alloc(st, &sl.sched.hdr, sched_ints(z.rt_max) * 4) &&
+             alloc(st, &sl.sched.hdr, sched_ints(z.rt_max) * 4) &&
              alloc(st, &sl.slot_of_row, cap1 * 4) &&
              alloc(st, &sl.row_of_slot, (z.n_slots_tok > 0 ? z.n_slots_tok : 1) * 4) &&
              alloc(st, &sl.h, cap1 * F * z.eb) &&
@@ -500,7 +498,6 @@ static moe_status dispatch_impl(moe_stage *st, int32_t slot, const moe_microbatc
     a.blk_counts = sl.blk_counts;
     a.counts = sl.counts;
     a.offsets = sl.offsets;
-    a.groups = sl.tables();
     a.sched = sl.sched;
     a.plan = sched_plan(st, stream_cus(st, s));
     const bool captured = note_capture(sl, s);
@@ -669,10 +666,9 @@ static moe_status ffn_grouped_impl(moe_stage *st, int32_t slot, const moe_groupe
     sl.has_mb = false;               // nothing in this slot to combine
     if (n == 0) return record(sl, s);
     note_capture(sl, s);
-    const GroupTable gt = sl.tables();
     {
         ProfScope ps(st, 0, s);
-        if (launch_group_tables_from_counts(gb->counts, d.n_local_experts, n, gt, sl.sched,
+        if (launch_group_tables_from_counts(gb->counts, d.n_local_experts, n, sl.sched,
                                             sched_plan(st, stream_cus(st, s)), st->err, s) != hipSuccess)
             return MOE_EHIP;
     }
