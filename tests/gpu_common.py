@@ -198,20 +198,3 @@ class CachedWeights:
         if "sh" not in self._cache:
             self._cache["sh"] = self.ow.shared()
         return self._cache["sh"]
-
-
-def band_order_tiles(rows_per_group, N, small_rows=192, tile=256):
-    """Tiles of the 256-row GEMM over groups of more than `small_rows` rows
-    with N output columns, the persistent grid it runs on (one workgroup per
-    CU, a multiple of 8), and whether it takes the size order: a single round,
-    or a last round at most half full.  Mirrors the launch's documented rule
-    so a test can assert which order a case exercises."""
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    nt = -(-N // tile)
-    total = sum(-(-int(r) // tile) for r in rows_per_group if r > small_rows) * nt
-    P = min(cus, total)
-    if P >= 8:
-        P &= ~7
-    tail = total % P if P else 0
-    by_size = total <= P or (tail != 0 and 2 * tail <= P)
-    return total, P, by_size

@@ -13,7 +13,7 @@ from paper_2606_22541_amd import inputs
 from paper_2606_22541_amd import moe_stage as C
 from paper_2606_22541_amd.stage import ExpertStage, bf16_bits, to_device_routing
 
-from gpu_common import (BF16_TOL, CachedWeights, band_order_tiles, check_dispatch, check_expert_rows,
+from gpu_common import (BF16_TOL, CachedWeights, check_dispatch, check_expert_rows,
                         check_outputs, gpu_run, log, oracle_run, poison_workspace)
 
 pytestmark = pytest.mark.gpu
@@ -320,19 +320,18 @@ def test_c3_ep8_share_with_shared_expert():
     _case(inputs.CONFIGS["c3"])
 
 
-def test_band_order_with_more_tiles_than_cus():
-    """More 256x256 tiles than CUs with a last round more than half full: the
-    256-row GEMMs keep the band order (row tiles rastered in bands of 4 per
-    column block, partial tiles beside their full ones) in both products.
-    d = 1024, f = 512 and about 26k routed rows over 8 experts (13-14 row
-    tiles each); every row is checked."""
+def test_groups_of_several_bands_of_row_tiles():
+    """Groups of three bands of row tiles (tiles of up to 320 rows, bands of 4,
+    the last band a partial one) and more items than workgroups in both
+    products: d = 1024, f = 512 and about 26k routed rows over 8 experts; every
+    row is checked."""
     cfg = inputs.MoEConfig("band", d=1024, f=512, E=16, e0=0, E_loc=8, k=8, lengths=(6500,), seed=21)
     mbs = inputs.make_microbatches(cfg, "cuda")
     disp = oracle.dispatch(mbs[0].ids, cfg.E, cfg.e0, cfg.E_loc)
-    for N, small in ((2 * cfg.f, 192), (cfg.d, 0)):       # gate/up, down (every group)
-        total, cus, by_size = band_order_tiles(disp["counts"][:cfg.E_loc], N, small)
-        log("  N=%d: %d tiles on %d CUs, size order %s" % (N, total, cus, by_size))
-        assert not by_size, "the case no longer exercises the band order"
+    tiles = -(-disp["counts"][:cfg.E_loc] // 320)
+    assert np.all((tiles > 8) & (tiles < 12)), tiles
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert tiles.sum() * min(2 * cfg.f, cfg.d) // 256 > cus
     _case(cfg, mbs)
 
 
@@ -359,13 +358,11 @@ def test_max_local_experts_and_group_size_boundaries():
     _case(cfg, [mb])
 
 
-def test_partial_row_tiles_in_size_order():
-    """The 256-row GEMM runs every group's full row tiles first and then the
-    partial ones by decreasing size.  Group sizes around every tile boundary
-    (0, 1, 31..33, 63..65, 128/129, 192/193, 255..257, 511..513), two groups with the
-    same partial size (300 and 44 rows), a group with several full tiles
-    (700) and a shared expert over all 4579 tokens; outputs start as NaN, so a
-    tile that no workgroup ran fails the comparison."""
+def test_groups_of_every_size_in_one_pass():
+    """Small and large groups beside one another: group sizes around the tiles'
+    boundaries (0, 1, 31..33, 63..65, 128/129, 192/193, 255..257, 300) and with several
+    row tiles (511..513, 700), and a shared expert over all 4579 tokens; outputs
+    start as NaN, so a tile that no workgroup ran fails the comparison."""
     sizes = [0, 1, 31, 32, 33, 63, 64, 65, 128, 129, 192, 193, 255, 256, 257, 300, 511, 512, 513,
              700, 44]
     cfg = inputs.MoEConfig("tile_order", d=256, f=128, E=24, e0=0, E_loc=len(sizes), k=1,
