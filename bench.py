@@ -88,8 +88,8 @@ def run_workload(name, steps, warmup, n_buffers=3, repeats=5):
     all of them released by one start event and joined at the end (a single
     micro-batch runs on one stream with nothing else on it).  Returns the
     timed region of exactly `steps` steps, the step times of `repeats`
-    further regions (spread only), and per-kernel times from the library's
-    events in one more region."""
+    further regions (spread only), and per-kernel times from events in two more
+    regions."""
     import torch
     from paper_2606_22541_amd import inputs
     from paper_2606_22541_amd import moe_stage as C
@@ -177,6 +177,21 @@ def run_workload(name, steps, warmup, n_buffers=3, repeats=5):
     torch.cuda.synchronize()
     prof = C.moe_stage_profile_read(stage.handle)
     C.moe_stage_profile(stage.handle, False)
+    # the launch of both products, which the library's events time as two: events
+    # around moe_expert_ffn (on one stream again)
+    pairs = []
+    for s in range(steps):
+        for m in mbs[s % n_sets]:
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            stage.dispatch(0, m, main)
+            e[0].record(main)
+            stage.expert_ffn(0, main)
+            e[1].record(main)
+            stage.combine(0, main)
+            pairs.append(e)
+    stage.sync()
+    torch.cuda.synchronize()
+    ffn_ms = sum(a.elapsed_time(b) for a, b in pairs) / steps
     stage.close()
 
     acct = None
@@ -192,6 +207,7 @@ def run_workload(name, steps, warmup, n_buffers=3, repeats=5):
         n_local += int(counts_local.sum())
     # per-step totals (a kernel group runs once per micro-batch)
     kern = {k: (v[0] / steps if v[1] else None) for k, v in prof.items()}
+    kern["ffn"] = ffn_ms
     del w, mbs_in, sets
     torch.cuda.empty_cache()
     return dict(cfg=cfg, T=sum(Ts), Ts=Ts, ms=ms, steps=steps, kern=kern, acct=acct,
@@ -203,29 +219,29 @@ def run_workload(name, steps, warmup, n_buffers=3, repeats=5):
 
 
 def measured_traffic(workload, kernel, fp8=False):
-    """HBM bytes per launch from the committed rocprofv3 counter summary, or
+    """HBM bytes per micro-batch from the committed rocprofv3 counter summary, or
     None when it is missing or the kernel's sources changed since."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
-    if fp8 and kernel.startswith("gemm_"):
+    if fp8 and kernel == "ffn":
         kernel += "_fp8"
     try:
         from paper_2606_22541_amd.profiling import sources_digest
         rec = json.load(open(path))["kernels"]["%s:%s" % (workload, kernel)]
         if rec["source_sha256"] != sources_digest(kernel):
             return None
-        return rec["bytes_per_dispatch"]
+        return rec["bytes_per_microbatch"]
     except Exception:
         return None
 
 
-STEP_GROUPS = ("dispatch_index", "gather", "gemm_gate_up_swiglu", "gemm_down", "combine")
+STEP_GROUPS = ("dispatch_index", "gather", "ffn", "combine")
 
 
 def step_roofline(r):
     """Roofline of a whole step of a multi-micro-batch workload, whose
     micro-batches overlap on their own streams: the step's algorithmic FLOPs
     (both grouped GEMMs) and bytes (every kernel group) over the measured
-    step time.  `traffic` sums the counters' bytes per dispatch of each
+    step time.  `traffic` sums the counters' bytes per micro-batch of each
     kernel group times the micro-batches of a step (null unless every group
     has a current record)."""
     a = r["acct"]
@@ -261,13 +277,13 @@ def step_roofline(r):
     return base
 
 
-def roofline_for(r, kernel="gemm_gate_up_swiglu"):
-    """Roofline of one launch of `kernel` (per step when the step has one
-    micro-batch; summed over the step's micro-batches otherwise)."""
+def roofline_for(r):
+    """Roofline of the launch of both grouped products (per step when the step
+    has one micro-batch; summed over the step's micro-batches otherwise)."""
+    kernel = "ffn"
     a = r["acct"]
     t = r["kern"][kernel] / 1e3
-    flop, byts = (a["g1_flop"], a["g1_bytes"]) if kernel == "gemm_gate_up_swiglu" else (
-        a["g2_flop"], a["g2_bytes"])
+    flop, byts = a["g1_flop"] + a["g2_flop"], a["g1_bytes"] + a["g2_bytes"]
     fp8 = r["cfg"].dtype == "fp8"
     peak_tf = PEAK_FP8_TFLOPS if fp8 else PEAK_BF16_TFLOPS
     t_mfma = flop / (peak_tf * 1e12)
@@ -303,12 +319,15 @@ def stream_rooflines(r):
             if k == "gather":
                 # the fp8 token scales only (a few MB): launch and memory latency
                 out[k]["bound"] = "latency"
+    # the two products as launches of their own, as the library times them
     g1, g2 = r["kern"][g1k], r["kern"][g2k]
     out[g1k] = {"avg_ms": round(g1, 4), "tflops": round(a["g1_flop"] / (g1 / 1e3) / 1e12, 1)}
     out[g2k] = {"avg_ms": round(g2, 4), "tflops": round(a["g2_flop"] / (g2 / 1e3) / 1e12, 1)}
-    tot = (a["g1_flop"] + a["g2_flop"]) / ((g1 + g2) / 1e3) / 1e12
-    out["grouped_gemm_total"] = {"tflops": round(tot, 1), "frac_mfma": round(tot / peak_tf, 4),
-                                 "peak_tflops": peak_tf}
+    t = r["kern"]["ffn"]
+    tot = (a["g1_flop"] + a["g2_flop"]) / (t / 1e3) / 1e12
+    gbs = (a["g1_bytes"] + a["g2_bytes"]) / (t / 1e3) / 1e9
+    out["ffn"] = {"avg_ms": round(t, 4), "tflops": round(tot, 1), "frac_mfma": round(tot / peak_tf, 4),
+                  "peak_tflops": peak_tf, "achieved_GBs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 4)}
     if r["kern"].get("quantize_h"):
         out["quantize_h"] = {"avg_ms": round(r["kern"]["quantize_h"], 4)}
     t = r["kern"]["dispatch_index"]

@@ -5,7 +5,7 @@ the stage's kernels (calls, average and total duration).
 
 ``traffic``: turns two ``--pmc FETCH_SIZE`` / ``--pmc WRITE_SIZE`` runs of a
 workload, plus the same two counters read for a plain device copy of known
-size, into HBM bytes per dispatch of each kernel.  Each counter is scaled by
+size, into HBM bytes per micro-batch of each kernel group.  Each counter is scaled by
 (known copy bytes / what the counter reported for the copy), so systematic
 under- or over-counting of the counters cancels.
 
@@ -27,25 +27,20 @@ import os
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-_FFN_BF16 = ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/ffn_bf16.h", "csrc/ffn_sched.h", "csrc/deal.h",
-             "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
-_FFN_FP8 = ["csrc/gemm_fp8.hip", "csrc/ffn_sched.h", "csrc/deal.h", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
-# "ffn": the launch of both products; the gemm groups: its two halves, which
-# run as launches of their own while a stage's profiling is on
+_COMMON = ["csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"]
+_FFN = ["csrc/ffn_sched.h", "csrc/deal.h"] + _COMMON
 KERNEL_SOURCES = {
-    "ffn": _FFN_BF16,
-    "ffn_fp8": _FFN_FP8,
-    "gemm_gate_up_swiglu": _FFN_BF16,
-    "gemm_down": _FFN_BF16,
-    "gemm_gate_up_swiglu_fp8": _FFN_FP8,
-    "gemm_down_fp8": _FFN_FP8,
-    "combine": ["csrc/combine.hip", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"],
-    "gather": ["csrc/dispatch.hip", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"],
-    "dispatch_index": ["csrc/dispatch.hip", "csrc/common.h", "csrc/bounds.h", "csrc/errors.h", "csrc/kernels.h"],
+    "ffn": ["csrc/gemm_bf16.hip", "csrc/gemm_bf16_small.hip", "csrc/ffn_bf16.h"] + _FFN,
+    "ffn_fp8": ["csrc/gemm_fp8.hip"] + _FFN,
+    "combine": ["csrc/combine.hip"] + _COMMON,
+    "gather": ["csrc/dispatch.hip"] + _COMMON,
+    "dispatch_index": ["csrc/dispatch.hip"] + _COMMON,
 }
 # rocprof kernel-name prefixes of the stage's kernels -> the kernel groups
-# bench.py times (a group's kernels each run once per micro-batch, so a
-# group's per-step figure is the sum over its kernels)
+# bench.py times.  Figures are per micro-batch: sums over a group's launches,
+# divided by the number of micro-batches, which is that of PER_MICROBATCH's
+# launches (the FFN is one launch or, while a stage's profiling is on and on
+# several streams, two).
 NAME_MAP = (
     ("void moe::k_ffn_bf16<true>", "ffn"),
     ("void moe::k_ffn_bf16<false>", "ffn"),
@@ -57,6 +52,8 @@ NAME_MAP = (
     ("moe::k_place", "dispatch_index"),
     ("moe::k_quantize_fp8", "quantize_fp8"),
 )
+PER_MICROBATCH = "moe::k_place"
+NOT_PER_MICROBATCH = ("quantize_fp8",)
 COPY_NAMES = ("__amd_rocclr_copyBuffer",)
 
 
@@ -85,29 +82,31 @@ def _find_csv(path: str, suffix: str) -> str:
 
 
 def kernel_stats(path: str):
-    """Per kernel group: calls of its first kernel and the summed average
-    and total durations of its kernels."""
+    """Per kernel group: launches, the total duration of its kernels, and that
+    per micro-batch (quantize_fp8: per launch)."""
     rows = list(csv.DictReader(open(_find_csv(path, "kernel_stats.csv"))))
+    n_mb = sum(int(r["Calls"]) for r in rows if r["Name"].startswith(PER_MICROBATCH))
     out = {}
     for r in rows:
         k = kind_of(r["Name"])
         if not k:
             continue
-        e = out.setdefault(k, {"calls": int(r["Calls"]), "avg_ms": 0.0, "total_ms": 0.0,
-                               "kernels": []})
-        e["avg_ms"] += float(r["AverageNs"]) / 1e6
+        e = out.setdefault(k, {"launches": 0, "total_ms": 0.0, "kernels": []})
+        e["launches"] += int(r["Calls"])
         e["total_ms"] += float(r["TotalDurationNs"]) / 1e6
         e["kernels"].append(r["Name"].split("(")[0])
+    for k, e in out.items():
+        e["avg_ms"] = e["total_ms"] / (e["launches"] if k in NOT_PER_MICROBATCH else n_mb)
     return out
 
 
-def counter_per_dispatch(path: str, counter: str):
-    """Mean counter value per dispatch of each kernel, summed over the
-    kernels of a group (copy kernels are their own group)."""
+def counter_per_microbatch(path: str, counter: str):
+    """Counter value of each kernel group per micro-batch (quantize_fp8 and copy
+    kernels, which are their own group: per launch)."""
     rows = list(csv.DictReader(open(_find_csv(path, "counter_collection.csv"))))
     acc = collections.defaultdict(float)
     disp = collections.defaultdict(set)
-    group = {}
+    mbs = set()
     for r in rows:
         if r["Counter_Name"] != counter:
             continue
@@ -115,21 +114,19 @@ def counter_per_dispatch(path: str, counter: str):
         k = kind_of(name) or (name if name in COPY_NAMES else None)
         if k is None:
             continue
-        key = name.split("(")[0]
-        group[key] = k
-        acc[key] += float(r["Counter_Value"])
-        disp[key].add(r["Dispatch_Id"])
-    out = collections.defaultdict(float)
-    for key, k in group.items():
-        out[k] += acc[key] / len(disp[key])
-    return dict(out)
+        acc[k] += float(r["Counter_Value"])
+        disp[k].add(r["Dispatch_Id"])
+        if name.startswith(PER_MICROBATCH):
+            mbs.add(r["Dispatch_Id"])
+    own = NOT_PER_MICROBATCH + COPY_NAMES
+    return {k: v / (len(disp[k]) if k in own else len(mbs)) for k, v in acc.items()}
 
 
 def traffic(args):
-    fetch = counter_per_dispatch(args.fetch, "FETCH_SIZE")
-    write = counter_per_dispatch(args.write, "WRITE_SIZE")
-    cf = counter_per_dispatch(args.copy_fetch, "FETCH_SIZE")
-    cw = counter_per_dispatch(args.copy_write, "WRITE_SIZE")
+    fetch = counter_per_microbatch(args.fetch, "FETCH_SIZE")
+    write = counter_per_microbatch(args.write, "WRITE_SIZE")
+    cf = counter_per_microbatch(args.copy_fetch, "FETCH_SIZE")
+    cw = counter_per_microbatch(args.copy_write, "WRITE_SIZE")
     copy = COPY_NAMES[0]
     # the largest copy dispatch is the calibration copy
     f_scale = args.copy_bytes / (cf[copy] * 1024.0)
@@ -144,8 +141,8 @@ def traffic(args):
         fb = fetch.get(k, 0.0) * 1024.0 * f_scale
         wb = write.get(k, 0.0) * 1024.0 * w_scale
         rec["kernels"]["%s:%s" % (args.workload, k)] = {
-            "fetch_bytes_per_dispatch": round(fb), "write_bytes_per_dispatch": round(wb),
-            "bytes_per_dispatch": round(fb + wb), "source_sha256": sources_digest(k)}
+            "fetch_bytes_per_microbatch": round(fb), "write_bytes_per_microbatch": round(wb),
+            "bytes_per_microbatch": round(fb + wb), "source_sha256": sources_digest(k)}
     rec.setdefault("commands", [])
     if args.command:
         rec["commands"].append(args.command)
@@ -227,7 +224,7 @@ def flop_per_mfma(kernel: str) -> int:
 
 
 def mfma_util(path: str):
-    """Per GEMM kernel: mean over its dispatches of the duration, the clock
+    """Per FFN kernel: mean over its dispatches of the duration, the clock
     (GRBM_GUI_ACTIVE per XCD over the duration), the MFMA instructions and
     FLOP executed, and the MFMA pipes' busy fraction at that clock and at
     the nominal 2.4 GHz."""
@@ -235,7 +232,7 @@ def mfma_util(path: str):
     per = collections.defaultdict(dict)
     for r in rows:
         n = r["Kernel_Name"]
-        if "moe::k_gemm" not in n and "moe::k_ffn" not in n:
+        if "moe::k_ffn" not in n:
             continue
         d = per[(n.split("(")[0], r["Dispatch_Id"])]
         d[r["Counter_Name"]] = float(r["Counter_Value"])

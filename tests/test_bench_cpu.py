@@ -48,7 +48,7 @@ def _write_counters(path, kernel, ns, values):
         w.writeheader()
         for disp in (1, 2):
             for name, v in values.items():
-                w.writerow({"Dispatch_Id": disp, "Kernel_Name": kernel + "(moe::GemmArgs)",
+                w.writerow({"Dispatch_Id": disp, "Kernel_Name": kernel + "(moe::FfnArgs)",
                             "Counter_Name": name, "Counter_Value": v,
                             "Start_Timestamp": 1000, "End_Timestamp": 1000 + ns})
 
@@ -57,10 +57,10 @@ def test_mfma_util_reduction(tmp_path):
     # 1e6 bf16 MFMAs (32 busy cycles each) in 100 us, GRBM summed over 8 XCDs at 2.0 GHz
     ns = 100_000
     n = 1_000_000
-    _write_counters(tmp_path / "run_counter_collection.csv", "void moe::k_gemm_bf16<true>", ns,
+    _write_counters(tmp_path / "run_counter_collection.csv", "void moe::k_ffn_bf16<true>", ns,
                     {"SQ_INSTS_MFMA": n, "SQ_VALU_MFMA_BUSY_CYCLES": 32 * n,
                      "GRBM_GUI_ACTIVE": 8 * 2.0 * ns, "SQ_BUSY_CU_CYCLES": 0})
-    r = profiling.mfma_util(str(tmp_path))["void moe::k_gemm_bf16<true>"]
+    r = profiling.mfma_util(str(tmp_path))["void moe::k_ffn_bf16<true>"]
     assert r["dispatches"] == 2
     assert r["clock_ghz"] == pytest.approx(2.0)
     assert r["executed_tflops"] == pytest.approx(n * 32768 / ns / 1e3)
@@ -71,8 +71,54 @@ def test_mfma_util_reduction(tmp_path):
 
 
 def test_fp8_mfma_counts_double_flop():
-    assert profiling.flop_per_mfma("void moe::k_gemm_fp8<true, 8>") == 2 * profiling.flop_per_mfma(
-        "void moe::k_gemm_bf16<true>")
+    assert profiling.flop_per_mfma("moe::k_ffn_fp8") == 2 * profiling.flop_per_mfma(
+        "void moe::k_ffn_bf16<true>")
+
+
+def test_figures_are_per_microbatch(tmp_path):
+    """Two micro-batches, one whose products ran in one launch and one with a
+    launch each: the groups' times and counters are sums over two."""
+    runs = [("moe::k_hist", 1), ("moe::k_place", 2), ("void moe::k_ffn_bf16<true>", 90), ("moe::k_combine", 7),
+            ("moe::k_hist", 1), ("moe::k_place", 2), ("void moe::k_ffn_bf16<true>", 60),
+            ("void moe::k_ffn_bf16<true>", 40), ("moe::k_combine", 9), ("moe::k_quantize_fp8", 5)]
+    with open(tmp_path / "run_counter_collection.csv", "w", newline="") as f:
+        w = csv.DictWriter(f, fieldnames=["Dispatch_Id", "Kernel_Name", "Counter_Name", "Counter_Value"])
+        w.writeheader()
+        for i, (name, v) in enumerate(runs):
+            w.writerow({"Dispatch_Id": i, "Kernel_Name": name + "(int)", "Counter_Name": "FETCH_SIZE",
+                        "Counter_Value": v})
+    want = {"dispatch_index": 3.0, "ffn": 95.0, "combine": 8.0, "quantize_fp8": 5.0}
+    assert profiling.counter_per_microbatch(str(tmp_path), "FETCH_SIZE") == want
+    with open(tmp_path / "run_kernel_stats.csv", "w", newline="") as f:
+        w = csv.DictWriter(f, fieldnames=["Name", "Calls", "TotalDurationNs", "AverageNs"])
+        w.writeheader()
+        for name in sorted({n for n, _ in runs}):
+            v = [t for n, t in runs if n == name]
+            w.writerow({"Name": name + "(int)", "Calls": len(v), "TotalDurationNs": sum(v) * 1e6,
+                        "AverageNs": sum(v) * 1e6 / len(v)})
+    got = profiling.kernel_stats(str(tmp_path))
+    assert {k: e["avg_ms"] for k, e in got.items()} == want
+    assert got["ffn"]["launches"] == 3
+
+
+def test_every_step_group_can_have_a_traffic_record():
+    """The groups that the step's roofline asks for are groups that the counter
+    summary writes, with sources of their own."""
+    kinds = {k for _, k in profiling.NAME_MAP}
+    for group in bench.STEP_GROUPS:
+        for k in {group, "ffn_fp8" if group == "ffn" else group}:
+            assert k in kinds and profiling.KERNEL_SOURCES[k], k
+    for files in profiling.KERNEL_SOURCES.values():
+        for rel in files:
+            assert os.path.exists(os.path.join(profiling.PKG, rel)), rel
+
+
+def test_ffn_roofline_covers_both_products():
+    from paper_2606_22541_amd import inputs
+    acct = dict(g1_flop=4e12, g2_flop=2e12, g1_bytes=1e9, g2_bytes=0.5e9)
+    ro = bench.roofline_for(dict(cfg=inputs.CONFIGS["c1p"], acct=acct, kern={"ffn": 4.0}))
+    assert ro["kernel"] == "ffn" and ro["bound"] == "mfma"
+    assert ro["achieved"] == pytest.approx(1500.0) and ro["algorithmic_bytes"] == 1.5e9
 
 
 def test_stream_accounting_bytes():
