@@ -21,12 +21,16 @@ struct Deal {
     int total0 = 0, total1 = 0;
 
     // P workgroups; g gate/up and d down items, of which the launch runs those
-    // of `phases` (1, 2, or 3 for both); row_bytes: of an activation row.
-    constexpr void deal(int P, int g, int d, int phases, int64_t row_bytes)
+    // of `phases` (1, 2, or 3 for both).
+    constexpr void count(int P, int g, int d, int phases)
     {
         lg = (P & (kLists - 1)) ? 0 : kListsLog2;
         total0 = (phases & 1) ? g : 0;
         total1 = (phases & 2) ? d : 0;
+    }
+    // The run lengths, after count(); row_bytes: of an activation row.
+    constexpr void deal(int P, int g, int d, int64_t row_bytes)
+    {
         // One item for each of a list's workgroups.  Fewer items than
         // workgroups are shared evenly: in runs of P / lists they fill the first
         // lists only, and their weights come through those XCDs (32 items of one

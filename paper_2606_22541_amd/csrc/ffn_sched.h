@@ -99,6 +99,7 @@ struct SchedLds {
     int32_t claimed, wait;     // begin(): the fixed item was taken; next(): what the wait found
     int32_t item, rti, nt;     // the next item and its tile (bit 30 of rti: a large one)
     int32_t ahead;             // done(): the next item is known
+    int32_t run[2];            // run lengths of the two products' items
     int32_t stage;     // thread 0: list being drained (0 gate/up, 1 down, 2 the others')
     uint64_t w[2], ws[2];   // weights of the two products, and their scales
 };
@@ -142,7 +143,8 @@ struct Items : Deal {
     int nrtd, sd;              // row tiles of down, the start of their table
     int ntl0, ntl1, nts0, nts1, band;
 
-    template <bool LARGE, bool OWN>
+    // FIRST: the run lengths are computed; otherwise they are in LDS.
+    template <bool LARGE, bool OWN, bool FIRST = false>
     __device__ __forceinline__ void load(const SchedLds &l, int phases, ArgTiles &ct)
     {
         nrt = __builtin_amdgcn_readfirstlane(l.hdr[0]);
@@ -155,8 +157,11 @@ struct Items : Deal {
         nts0 = ct.nts[0];
         nts1 = ct.nts[1];
         band = ct.band;
-        deal(gridDim.x, nl0 * ntl0 + (nrt - nl0) * nts0, nl1 * ntl1 + (nrtd - nl1) * nts1, phases, ct.row_bytes);
-        C1 = __builtin_amdgcn_readfirstlane(C1);
+        const int g = nl0 * ntl0 + (nrt - nl0) * nts0, d = nl1 * ntl1 + (nrtd - nl1) * nts1;
+        count(gridDim.x, g, d, phases);
+        if constexpr (FIRST) deal(gridDim.x, g, d, ct.row_bytes);
+        C = __builtin_amdgcn_readfirstlane(FIRST ? C : l.run[0]);
+        C1 = __builtin_amdgcn_readfirstlane(FIRST ? C1 : l.run[1]);
         x = blockIdx.x & ((1 << lg) - 1);
     }
     // gate/up tiles that the count of gate/up row tile rt comes to
@@ -185,7 +190,9 @@ struct Worker {
         else if (tid == 128) l.claimed = (phases & 1) ? agent_swap(&s.claim[b], 1) : 1;
         __syncthreads();
         Items q;
-        q.load<LARGE, OWN>(l, phases, ct);
+        q.load<LARGE, OWN, true>(l, phases, ct);
+        l.run[0] = q.C;          // (every wave the same, and each reads its own)
+        l.run[1] = q.C1;
         all_done = false;
         pending = -1;
         pre = -1;

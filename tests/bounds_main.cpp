@@ -76,7 +76,8 @@ static int deal()
     int P, g, d, phases, bytes;
     if (std::scanf("%d %d %d %d %d", &P, &g, &d, &phases, &bytes) != 5) return 2;
     Deal q;
-    q.deal(P, g, d, phases, bytes);
+    q.count(P, g, d, phases);
+    q.deal(P, g, d, bytes);
     std::printf("%d %d ", 1 << q.lg, q.C);
     for (int b = 0; b < P; ++b) std::printf("%d ", q.fixed(b));
     for (int p = 0; p < 2; ++p)
