@@ -154,9 +154,9 @@ def traffic(args):
 def overlap(path: str, steps_skip: int, steps_use: int):
     """Per-step overlap of the stage's kernels in a --kernel-trace of a
     workload whose micro-batches run on their own streams.  The stage's
-    dispatches, in issue order, are cut into steps of equal kernel count
-    (every step issues the same kernels); of those, `steps_use` steps after
-    the first `steps_skip` are reduced.  Per step: the span (first start to
+    dispatches, in issue order, are cut into steps at the first kernel of the
+    first stream; of those, `steps_use` steps after the first `steps_skip` are
+    reduced.  Per step: the span (first start to
     last end), the sum of kernel durations, the busy time of each stream
     (union of its kernels' intervals) and of the device (union of all), and
     the sum per kernel group.  overlap = sum of durations / device busy time
@@ -165,12 +165,11 @@ def overlap(path: str, steps_skip: int, steps_use: int):
             if kind_of(r["Kernel_Name"]) not in (None, "quantize_fp8")]
     rows.sort(key=lambda r: int(r["Dispatch_Id"]))
     streams = sorted({r["Stream_Id"] for r in rows})
-    # kernels per step: the number of dispatches between consecutive
-    # dispatches of the first kernel name seen on the first stream
+    # where steps begin: at the first kernel name seen on the first stream (the
+    # first step's FFN passes may be a launch each, later ones two)
     first = rows[0]["Kernel_Name"]
     idx = [i for i, r in enumerate(rows) if r["Kernel_Name"] == first and
            r["Stream_Id"] == rows[0]["Stream_Id"]]
-    per_step = idx[1] - idx[0]
 
     def union(iv):
         iv = sorted(iv)
@@ -187,9 +186,10 @@ def overlap(path: str, steps_skip: int, steps_use: int):
     acc = collections.defaultdict(float)
     n = 0
     for st in range(steps_skip, steps_skip + steps_use):
-        chunk = rows[st * per_step:(st + 1) * per_step]
-        if len(chunk) < per_step:
+        if st + 1 >= len(idx):
             break
+        chunk = rows[idx[st]:idx[st + 1]]
+        acc["kernels_per_step"] += len(chunk)
         iv = [(int(r["Start_Timestamp"]), int(r["End_Timestamp"])) for r in chunk]
         acc["span_us"] += (max(e for _, e in iv) - min(s_ for s_, _ in iv)) / 1e3
         acc["sum_kernels_us"] += sum(e - s_ for s_, e in iv) / 1e3
@@ -204,7 +204,6 @@ def overlap(path: str, steps_skip: int, steps_use: int):
         n += 1
     out = {k: round(v / n, 2) for k, v in acc.items()}
     out["steps"] = n
-    out["kernels_per_step"] = per_step
     out["overlap"] = round(out["sum_kernels_us"] / out["device_busy_us"], 3)
     return out
 
@@ -224,32 +223,31 @@ def flop_per_mfma(kernel: str) -> int:
 
 
 def mfma_util(path: str):
-    """Per FFN kernel: mean over its dispatches of the duration, the clock
-    (GRBM_GUI_ACTIVE per XCD over the duration), the MFMA instructions and
-    FLOP executed, and the MFMA pipes' busy fraction at that clock and at
-    the nominal 2.4 GHz."""
+    """Per FFN kernel, over all its launches: the time and the MFMA instructions
+    per micro-batch, the FLOP rate executed, the clock (GRBM_GUI_ACTIVE per XCD
+    over the time), and the MFMA pipes' busy fraction at that clock and at the
+    nominal 2.4 GHz."""
     rows = list(csv.DictReader(open(_find_csv(path, "counter_collection.csv"))))
-    per = collections.defaultdict(dict)
+    n_mb = len({r["Dispatch_Id"] for r in rows if r["Kernel_Name"].startswith(PER_MICROBATCH)})
+    per = collections.defaultdict(lambda: collections.defaultdict(float))
+    launches = collections.defaultdict(dict)
     for r in rows:
         n = r["Kernel_Name"]
         if "moe::k_ffn" not in n:
             continue
-        d = per[(n.split("(")[0], r["Dispatch_Id"])]
-        d[r["Counter_Name"]] = float(r["Counter_Value"])
-        d["ns"] = float(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
-    by_kernel = collections.defaultdict(list)
-    for (name, _), d in per.items():
-        by_kernel[name].append(d)
+        n = n.split("(")[0]
+        per[n][r["Counter_Name"]] += float(r["Counter_Value"])
+        launches[n][r["Dispatch_Id"]] = int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
     out = {}
-    for name, ds in by_kernel.items():
-        m = {k: sum(d.get(k, 0.0) for d in ds) / len(ds) for k in ds[0]}
-        ns, gui = m["ns"], m["GRBM_GUI_ACTIVE"] / XCDS
+    for name, m in per.items():
+        ns, gui = float(sum(launches[name].values())), m["GRBM_GUI_ACTIVE"] / XCDS
         busy, n_mfma = m["SQ_VALU_MFMA_BUSY_CYCLES"], m["SQ_INSTS_MFMA"]
         out[name] = {
-            "dispatches": len(ds),
-            "avg_us": ns / 1e3,
+            "launches": len(launches[name]),
+            "microbatches": n_mb,
+            "us_per_microbatch": ns / 1e3 / n_mb,
             "clock_ghz": gui / ns if ns else 0.0,
-            "mfma_per_dispatch": n_mfma,
+            "mfma_per_microbatch": n_mfma / n_mb,
             "busy_cycles_per_mfma": busy / n_mfma if n_mfma else 0.0,
             "executed_tflops": n_mfma * flop_per_mfma(name) / ns / 1e3 if ns else 0.0,
             "mfma_busy_at_clock": busy / (gui * SIMDS) if gui else 0.0,

@@ -46,11 +46,13 @@ def _write_counters(path, kernel, ns, values):
         w = csv.DictWriter(f, fieldnames=["Dispatch_Id", "Kernel_Name", "Counter_Name",
                                           "Counter_Value", "Start_Timestamp", "End_Timestamp"])
         w.writeheader()
-        for disp in (1, 2):
-            for name, v in values.items():
-                w.writerow({"Dispatch_Id": disp, "Kernel_Name": kernel + "(moe::FfnArgs)",
-                            "Counter_Name": name, "Counter_Value": v,
-                            "Start_Timestamp": 1000, "End_Timestamp": 1000 + ns})
+        # two micro-batches; the second one's products are a launch each
+        for disp, name, t in ((0, "moe::k_place", 0.1), (1, kernel, 1.0), (2, "moe::k_place", 0.1),
+                              (3, kernel, 0.75), (4, kernel, 0.25)):
+            for counter, v in values.items():
+                w.writerow({"Dispatch_Id": disp, "Kernel_Name": name + "(moe::FfnArgs)",
+                            "Counter_Name": counter, "Counter_Value": v * t if name == kernel else 7,
+                            "Start_Timestamp": 1000, "End_Timestamp": 1000 + int(ns * t)})
 
 
 def test_mfma_util_reduction(tmp_path):
@@ -61,7 +63,9 @@ def test_mfma_util_reduction(tmp_path):
                     {"SQ_INSTS_MFMA": n, "SQ_VALU_MFMA_BUSY_CYCLES": 32 * n,
                      "GRBM_GUI_ACTIVE": 8 * 2.0 * ns, "SQ_BUSY_CU_CYCLES": 0})
     r = profiling.mfma_util(str(tmp_path))["void moe::k_ffn_bf16<true>"]
-    assert r["dispatches"] == 2
+    assert r["launches"] == 3 and r["microbatches"] == 2
+    assert r["us_per_microbatch"] == pytest.approx(100.0)
+    assert r["mfma_per_microbatch"] == pytest.approx(n)
     assert r["clock_ghz"] == pytest.approx(2.0)
     assert r["executed_tflops"] == pytest.approx(n * 32768 / ns / 1e3)
     # busy cycles over all 1024 SIMDs at 2.0 GHz for 100 us
