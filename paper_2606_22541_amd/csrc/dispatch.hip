@@ -97,8 +97,8 @@ __device__ __forceinline__ int wave_sum(int v)
 }
 
 // The row tiles of the FFN pass (ffn_sched.h) over G = E_loc (+1 shared)
-// groups, built by one workgroup; a group's rows are the local
-// expert's token count (tot), or T for the shared expert.
+// groups, built by one workgroup; a group's rows are the local expert's token
+// count (tot), or T for the shared expert.
 //
 // A large group is split evenly into as few row tiles of at most h 32-row
 // blocks as hold its rows.  h is the largest height, which does the most

@@ -12,8 +12,8 @@
 //
 // Design for gfx950:
 //  * one persistent workgroup per CU runs items (128-token x 256-feature
-//    tiles) of both products in one launch, from the lists of ffn_sched.h: a
-//    down item starts once the gate/up tiles of its rows are written, so no
+//    tiles) of both products in one launch (or in one each, split_products()),
+//    from the lists of ffn_sched.h: a down item starts once the gate/up tiles of its rows are written, so no
 //    idle last round and no launch gap lies between the products (T = 32768,
 //    d = 7168, f = 2048, 8 experts, with dispatch and combine: 539 -> 497 us;
 //    T = 2049: 132 -> 128).  Row tiles are rastered in bands of up to 8 so that each weight
