@@ -31,17 +31,21 @@ struct Deal {
     // The run lengths, after count(); row_bytes: of an activation row.
     constexpr void deal(int P, int g, int d, int64_t row_bytes)
     {
-        // One item for each of a list's workgroups.  Fewer items than
-        // workgroups are shared evenly: in runs of P / lists they fill the first
-        // lists only, and their weights come through those XCDs (32 items of one
-        // expert, d = 7168, f = 2048, 16 rows, a layer: 79.0 us, shared 69.8; fp8,
-        // two experts 80.4 and 58.8).  Not where rows are so short that the
-        // weights do not count: latencies are lower with h in one L2 then (4
+        // One item for each of a list's workgroups.  Up to three quarters as
+        // many items as workgroups are shared evenly: in runs of P / lists they
+        // fill the first lists only, and their weights come through those XCDs
+        // (32 items of one expert, d = 7168, f = 2048, 16 rows, a layer: 79.0 us,
+        // shared 69.8; fp8, two experts 80.4 and 58.8).  With more the lists are
+        // nearly full, and runs that begin where a group does share its rows and
+        // panels in one L2 (fp8, d = 7168, f = 2048, 192 items 114.5 and shared 112.4, 208
+        // 112.8 and 113.3, 240 112.5 and 115.3; bf16, 100 rows an expert, 192 items
+        // 123.7 and 123.1, 224 130.2 and 133.5).  Nor where rows are so short that
+        // the weights do not count: latencies are lower with h in one L2 then (4
         // experts, f = d / 2, 64 tokens, shared and in runs: fp8, d = 512 31.8 and
         // 30.8, bf16, d = 256 25.5 and 24.2; bf16, d = 512, rows of 1 KB, 27.6 and
         // 28.1).
         const int share = (g + (1 << lg) - 1) >> lg, most = P >> lg;
-        C = row_bytes < kShortRow ? most : share < 1 ? 1 : share < most ? share : most;
+        C = row_bytes < kShortRow || 4 * share > 3 * most ? most : share > 1 ? share : 1;
         // A list's down items are those of the row tiles that it did the
         // gate/up items of (as far as runs of one length allow): they are ready
         // when its own gate/up items are.

@@ -107,11 +107,11 @@ def test_a_stalled_pass_is_reported_before_any_other_error(driver):
 @pytest.mark.parametrize("P", [1, 3, 7, 8, 16, 24, 248, 256, 304])
 def test_every_item_is_dealt_once_and_few_are_spread(driver, P, phases, row_bytes):
     """All items of both products are in the lists exactly once, the fixed ones
-    are the first of each list, and with fewer gate/up items than workgroups no
-    list has more than its even share (rows of 1 KB and more; shorter ones fill
-    the lists one after the other)."""
+    are the first of each list, and with up to three quarters as many gate/up items
+    as workgroups no list has more than its even share (rows of 1 KB and more;
+    shorter rows, and more items, fill the lists one after the other)."""
     rng = np.random.default_rng(P)
-    sizes = [(0, 0), (1, 1), (8, 8), (9, 1), (32, 56), (128, 448), (255, 1), (256, 224), (257, 3000)]
+    sizes = [(0, 0), (1, 1), (8, 8), (9, 1), (32, 56), (128, 448), (192, 9), (193, 9), (255, 1), (256, 224), (257, 3000)]
     sizes += [tuple(int(v) for v in 2**rng.uniform(0, 12, 2)) for _ in range(12)]
     for g, d in sizes:
         out = _run(driver, "deal", P, g, d, phases, row_bytes)
@@ -127,9 +127,11 @@ def test_every_item_is_dealt_once_and_few_are_spread(driver, P, phases, row_byte
             assert sorted(i for y in range(lists) for i in got[p, y]) == list(range(n)), (P, g, d, p)
         for y in range(lists):
             assert [f for f in fixed[y::lists] if f >= 0] == got[0, y][:run], (P, g, d, y)
-            if phases & 1 and 0 < g <= P and row_bytes >= 1024:
-                assert len(got[0, y]) <= -(-g // lists), (P, g, d, y)
-            if phases & 1 and g <= P and row_bytes < 1024:
+            share = -(-g // lists)
+            few = row_bytes >= 1024 and 4 * share <= 3 * (P // lists)
+            if phases & 1 and few:
+                assert len(got[0, y]) <= max(share, 1), (P, g, d, y)
+            if phases & 1 and g <= P and not few:
                 assert len(got[0, y]) == min(P // lists, max(0, g - y * (P // lists))), (P, g, d, y)
 
 
