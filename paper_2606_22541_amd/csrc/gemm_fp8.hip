@@ -16,7 +16,7 @@
 //    from the lists of ffn_sched.h: a down item starts once the gate/up tiles of its rows are written, so no
 //    idle last round and no launch gap lies between the products (T = 32768,
 //    d = 7168, f = 2048, 8 experts, with dispatch and combine: 539 -> 497 us;
-//    T = 2049: 132 -> 128).  Row tiles are rastered in bands of up to 8 so that each weight
+//    T = 2049: 132 -> 126).  Row tiles are rastered in bands of up to 8 so that each weight
 //    panel is read by one XCD;
 //  * the product is formed transposed, D[feature][token] = W X^T: the
 //    weights are the MFMA's row operand and the tokens its column operand,
